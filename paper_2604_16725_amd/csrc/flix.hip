@@ -12,6 +12,7 @@
 #include "../../include/flix.h"
 #include "flix_build.hpp"
 #include "flix_device.hpp"
+#include "flix_direct.hpp"
 #include "flix_drain.hpp"
 #include "flix_epoch.hpp"
 #include "flix_group.hpp"
@@ -98,6 +99,7 @@ struct flix_store {
   u64* occ = nullptr;    // bucket occupancy summary [occ_words(nb_alloc)]
   OccLevels occl{};      // its three levels for the current bucket count
   u32* cuts = nullptr;   // read-share cuts [(max_batch + nb_alloc) / 512 + 2]
+  void* dir = nullptr;   // directory search levels above mkba [dir_entries(nb_alloc)]
   u32* mktop = nullptr;  // [257] first MKBA entry of every top key digit
   // bucket groups of the read path (flix_group.hpp)
   bool grp_ok = false;   // the store's shape fits the group kernels
@@ -295,18 +297,22 @@ int alloc_dir(flix_store* s, u32 nb) {
   u32* bn = nullptr;
   u64* oc = nullptr;
   u32* cu = nullptr;
+  void* dr = nullptr;
   int rc;
-  if ((rc = dev_alloc(&mk, (u64)nb * s->ksz)) || (rc = dev_alloc(&bn, (u64)nb * sizeof(u32))) ||
+  if ((rc = dev_alloc(&mk, dir_round(nb) * s->ksz)) ||
+      (rc = dev_alloc(&dr, s->kb == 32 ? dir_entries<u32>(nb) * 4 : dir_entries<u64>(nb) * 8)) || (rc = dev_alloc(&bn, (u64)nb * sizeof(u32))) ||
       (rc = dev_alloc(&oc, occ_words(nb) * sizeof(u64))) ||
       (rc = dev_alloc(&cu, (cuts_for(s->max_batch, nb) * sizeof(u32))))) {
-    dev_free(&mk); dev_free(&bn); dev_free(&oc); dev_free(&cu);
+    dev_free(&mk); dev_free(&bn); dev_free(&oc); dev_free(&cu); dev_free(&dr);
     return rc;
   }
   dev_free(&s->mkba);
   dev_free(&s->bnodes);
   dev_free(&s->cuts);
   dev_free(&s->occ);
+  dev_free(&s->dir);
   s->mkba = mk;
+  s->dir = dr;
   s->bnodes = bn;
   s->occ = oc;
   s->cuts = cu;
@@ -522,11 +528,53 @@ int read_batch_groups(flix_store* s, int op, const K* keys, u64 n, void* out_k, 
   return FLIX_OK;
 }
 
+// Read batches up to this length are answered in input order.  Sorting a batch
+// pays nowhere below it: 2^26 u32 keys, lookups, direct against sorted: 2^17
+// 17 against 42 us, 2^20 94 against 109, 2^22 342 against 488, 2^23 669
+// against 728; on stores that fit the caches by more (2^20 keys, 2^23
+// lookups: 307 against 1045), on skewed batches (2^20 Zipf 64 against 351)
+// and on ranges with many results (2^16 ranges of 256 keys: 107 against 236)
+// too.  At 12.3 M lookups the two meet (1.00 against 1.02 ms).
+constexpr u64 kDirectMax = 1ull << 23;
+
+// Read batch answered in input order (flix_direct.hpp).
+template <typename K>
+int read_direct(flix_store* s, int op, const K* keys, u64 n, void* out_k, void* out_v,
+                const void* hi, u32* counts, u32 maxpq, hipStream_t st) {
+  ReadArgs<K> a;
+  a.skeys = keys;
+  a.sidx = nullptr;
+  a.m = (u32)n;
+  a.mkba = (const K*)s->mkba;
+  a.nb = s->nb;
+  a.hdr = s->hdr;
+  a.nkeys = (const K*)s->nkeys;
+  a.nvals = (const K*)s->nvals;
+  a.cap = s->cap;
+  a.share = 0;
+  a.out_v = (K*)out_v;
+  a.out_k = (K*)out_k;
+  a.hi = (const K*)hi;
+  a.counts = counts;
+  a.maxpq = maxpq;
+  a.pool = s->pool;
+  a.err = &s->ctl->status;
+  a.occ = s->occl.w0;
+  a.cuts = nullptr;
+  const TmTok t = tm_arm(s, F_READ);
+  launch_direct<K>(a, dir_tree<K>((const K*)s->mkba, (const K*)s->dir, s->nb), op, st, t.b, t.e);
+  tm_done(s, F_READ, t);
+  HIP_TRY(hipGetLastError());
+  return FLIX_OK;
+}
+
 template <typename K>
 int read_batch(flix_store* s, int op, const void* keys, u64 n, void* out_k, void* out_v,
                const void* hi, u32* counts, u32 maxpq, hipStream_t st) {
   if (s->cfg.read_path == FLIX_READ_GROUPS && s->grp_ok && n <= (u64)kGroupTilesMax * kPartTile)
     return read_batch_groups<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
+  if (n <= kDirectMax)
+    return read_direct<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
   int r;
   // the run sort also writes the read kernel's share cuts when it can
   RunCuts<K> rc_args{};
@@ -1069,6 +1117,20 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL((k_mk_top<K>), dim3(1), dim3(256), 0, st, (const K*)s->mkba, nbk, s->mktop);
   HIP_TRY(hipGetLastError());
+  // search levels above the directory
+  {
+    K* lo = (K*)s->mkba;
+    K* hi = (K*)s->dir;
+    for (u32 n = nbk; n > DirTop<K>::n;) {
+      const u32 m = (n + kDirFan - 1) / kDirFan;
+      hipLaunchKernelGGL((k_dir_level<K>), dim3((u32)((dir_round(m) + 255) / 256)), dim3(256), 0,
+                         st, lo, n, hi, m);
+      lo = hi;
+      hi += dir_round(m);
+      n = m;
+    }
+    HIP_TRY(hipGetLastError());
+  }
   // occupancy summary of the new directory
   s->occl.w0 = s->occ;
   s->occl.w1 = s->occ + occ_words0(nbk);
@@ -1239,6 +1301,7 @@ int check_args(flix_store* s, u64 n, std::initializer_list<const void*> ptrs) {
 
 void destroy_all(flix_store* s) {
   dev_free(&s->mkba);
+  dev_free(&s->dir);
   dev_free(&s->cuts);
   dev_free(&s->split);
   dev_free(&s->gpre);

@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "flix_direct.hpp"
 #include "flix_drain.hpp"
 #include "flix_group.hpp"
 #include "flix_read2.hpp"
@@ -18,6 +19,11 @@ namespace flix {
 template <typename K>
 void launch_read2(u32 gl, u32 cap, const ReadArgs<K>& a, int op, u32 grid, hipStream_t st,
                   hipEvent_t e0, hipEvent_t e1);
+
+// Direct read kernel (flix_direct.hpp): a.skeys holds the batch in input order.
+template <typename K>
+void launch_direct(const ReadArgs<K>& a, const DirTree<K>& t, int op, hipStream_t st,
+                   hipEvent_t e0, hipEvent_t e1);
 
 // Bucket-group read kernel (k_group_read); `chunk` items per workgroup.
 template <typename K>

@@ -105,16 +105,47 @@ void launch_group(u32 gl, u32 cap, const GroupArgs<K>& ga, const ReadArgs<K>& a,
   }
 }
 
+template <typename K>
+void launch_direct(const ReadArgs<K>& a, const DirTree<K>& t, int op, hipStream_t st,
+                   hipEvent_t e0, hipEvent_t e1) {
+  constexpr int NT = 256;
+  // ranges: fewer queries per wave while that leaves the chip under 32 waves
+  // per CU (the results of a range are copied by its wave)
+  u32 qpw = 64;
+  if (op == kOpRange)
+    while (qpw > 4 && (u64)qpw * 8192u > a.m) qpw >>= 1;
+  const u32 per = qpw * (NT / 64);
+  const dim3 g((a.m + per - 1) / per), b(NT);
+  switch (op) {
+    case kOpLookup:
+      launch_timed(e0, e1, k_read_direct<K, NT, kOpLookup>, g, b, 0, st, a, t, qpw);
+      break;
+    case kOpSuccessor:
+      launch_timed(e0, e1, k_read_direct<K, NT, kOpSuccessor>, g, b, 0, st, a, t, qpw);
+      break;
+    case kOpRange:
+      launch_timed(e0, e1, k_read_direct<K, NT, kOpRange>, g, b, 0, st, a, t, qpw);
+      break;
+    default:
+      launch_timed(e0, e1, k_read_direct<K, NT, kOpPredecessor>, g, b, 0, st, a, t, qpw);
+      break;
+  }
+}
+
 // The library builds this file once per key width (FLIX_READ_KEY_BITS = 32 or
 // 64), so the two halves of the read kernels compile in parallel.
 #if FLIX_READ_KEY_BITS == 32
 template void launch_read2<u32>(u32, u32, const ReadArgs<u32>&, int, u32, hipStream_t, hipEvent_t,
                                 hipEvent_t);
+template void launch_direct<u32>(const ReadArgs<u32>&, const DirTree<u32>&, int, hipStream_t,
+                                 hipEvent_t, hipEvent_t);
 template void launch_group<u32>(u32, u32, const GroupArgs<u32>&, const ReadArgs<u32>&, int, u32,
                                 hipStream_t, hipEvent_t, hipEvent_t);
 #elif FLIX_READ_KEY_BITS == 64
 template void launch_read2<u64>(u32, u32, const ReadArgs<u64>&, int, u32, hipStream_t, hipEvent_t,
                                 hipEvent_t);
+template void launch_direct<u64>(const ReadArgs<u64>&, const DirTree<u64>&, int, hipStream_t,
+                                 hipEvent_t, hipEvent_t);
 template void launch_group<u64>(u32, u32, const GroupArgs<u64>&, const ReadArgs<u64>&, int, u32,
                                 hipStream_t, hipEvent_t, hipEvent_t);
 #else
