@@ -1011,6 +1011,7 @@ int publish_layout(flix_store* s) {
   L.nb = s->nb;
   L.pool = s->pool;
   L.occ = s->occl;
+  L.dir = s->dir;
   HIP_TRY(hipMemcpy(s->d_layout, &L, sizeof(L), hipMemcpyHostToDevice));
   return FLIX_OK;
 }

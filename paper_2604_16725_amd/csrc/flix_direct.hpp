@@ -116,7 +116,7 @@ __device__ __forceinline__ u32 quad_sum(u32 v) {
 // Of the first `valid` of N sorted keys at p (16-byte aligned, the first `lim`
 // of them readable): how many are below x, and with LE how many are not above
 // y.  FULL: all N are valid.  All lanes of the wave call, each with a block of
-// its own; `valid` may be 0.  Every load is issued before the first count.
+// its own; `valid` may be 0.  quad_fetch issues every load, quad_count counts.
 template <typename K, int N, int R>
 __device__ __forceinline__ void quad_load(const K* p, u32 lim, KeyVec<K, 16 / (int)sizeof(K)>* v) {
   constexpr int E = 16 / (int)sizeof(K);
@@ -150,72 +150,63 @@ __device__ __forceinline__ void quad_tally(const KeyVec<K, 16 / (int)sizeof(K)>*
   lt |= a << (8 * R);
   if (LE) le |= b << (8 * R);
 }
-template <typename K, int N, bool LE, bool FULL>
-__device__ __forceinline__ void quad_count(const K* p, u32 lim, u32 valid, K x, K y, u32* n_lt,
-                                           u32* n_le) {
+template <typename K, int N>
+struct QuadBlock {
   KeyVec<K, 16 / (int)sizeof(K)> v[N * sizeof(K) / 16];
-  quad_load<K, N, 0>(p, lim, v);
-  quad_load<K, N, 1>(p, lim, v);
-  quad_load<K, N, 2>(p, lim, v);
-  quad_load<K, N, 3>(p, lim, v);
+};
+template <typename K, int N>
+__device__ __forceinline__ void quad_fetch(const K* p, u32 lim, QuadBlock<K, N>& r) {
+  quad_load<K, N, 0>(p, lim, r.v);
+  quad_load<K, N, 1>(p, lim, r.v);
+  quad_load<K, N, 2>(p, lim, r.v);
+  quad_load<K, N, 3>(p, lim, r.v);
+}
+template <typename K, int N, bool LE, bool FULL>
+__device__ __forceinline__ void quad_count(const QuadBlock<K, N>& r, u32 valid, K x, K y, u32* n_lt,
+                                           u32* n_le) {
   u32 lt = 0, le = 0;
-  quad_tally<K, N, LE, FULL, 0>(v, valid, x, y, lt, le);
-  quad_tally<K, N, LE, FULL, 1>(v, valid, x, y, lt, le);
-  quad_tally<K, N, LE, FULL, 2>(v, valid, x, y, lt, le);
-  quad_tally<K, N, LE, FULL, 3>(v, valid, x, y, lt, le);
+  quad_tally<K, N, LE, FULL, 0>(r.v, valid, x, y, lt, le);
+  quad_tally<K, N, LE, FULL, 1>(r.v, valid, x, y, lt, le);
+  quad_tally<K, N, LE, FULL, 2>(r.v, valid, x, y, lt, le);
+  quad_tally<K, N, LE, FULL, 3>(r.v, valid, x, y, lt, le);
   const u32 s = 8u * (threadIdx.x & 3u);
   *n_lt = (quad_sum(lt) >> s) & 0xFFu;
   if (LE) *n_le = (quad_sum(le) >> s) & 0xFFu;
 }
 
-// First of the n (<= DirTop) entries in LDS that is >= x; the last entry is
-// KEY_MAX, so one exists.
-template <typename K>
-__device__ __forceinline__ u32 top_search(const K* s_top, u32 n, K x) {
-  u32 pos = 0;
+// Buckets of Q queries per lane: the first maxBucket entry >= x.  The searches
+// of a lane advance together, so Q of its loads are in flight at a time.  All
+// lanes of the wave call.  (s_top holds the top level; every level ends in
+// KEY_MAX, so an entry >= x exists.)
+template <typename K, int Q>
+__device__ __forceinline__ void find_buckets(const DirTree<K>& t, const K* s_top, u32 nb,
+                                             const K (&x)[Q], u32 (&i)[Q]) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q) i[q] = 0;
   for (u32 s = DirTop<K>::n / 2; s > 0; s >>= 1) {
-    if (pos + s <= n && s_top[pos + s - 1] < x) pos += s;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (i[q] + s <= t.ntop && s_top[i[q] + s - 1] < x[q]) i[q] += s;
   }
-  return pos < n ? pos : n - 1;
-}
-
-// Bucket of x: the first maxBucket entry >= x.  All lanes of the wave call.
-template <typename K>
-__device__ __forceinline__ u32 find_bucket(const DirTree<K>& t, const K* s_top, u32 nb, K x) {
-  u32 i = top_search<K>(s_top, t.ntop, x);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) i[q] = i[q] < t.ntop ? i[q] : t.ntop - 1;
 #pragma unroll
   for (int l = kDirMaxLev - 1; l >= 0; --l) {
     if ((u32)l < t.nlev) {
-      u32 c, none;
-      quad_count<K, kDirFan, false, true>(t.lev[l] + (u64)i * kDirFan, kDirFan, kDirFan, x, x,
-                                          &c, &none);
-      i = i * kDirFan + (c < kDirFan - 1 ? c : kDirFan - 1);
+      QuadBlock<K, (int)kDirFan> e[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        quad_fetch<K, (int)kDirFan>(t.lev[l] + (u64)i[q] * kDirFan, kDirFan, e[q]);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        u32 c, none;
+        quad_count<K, (int)kDirFan, false, true>(e[q], kDirFan, x[q], x[q], &c, &none);
+        i[q] = i[q] * kDirFan + (c < kDirFan - 1 ? c : kDirFan - 1);
+      }
     }
   }
-  return i < nb ? i : nb - 1;
-}
-
-// First slot of the 64-byte block of a node that holds the first key >= x
-// (UPPER: > x), of its last block if there is none.  Each step reads the last
-// key of a block; `mid_key` is the key at slot cap/4 - 1 (the middle of a
-// bulk-loaded node), loaded by the caller together with the header, used when
-// `have_mid`.
-template <typename K, bool UPPER>
-__device__ __forceinline__ u32 node_block(const K* keys, u32 cap, u32 size, K x, K mid_key,
-                                          bool have_mid) {
-  constexpr u32 B = 64 / sizeof(K);
-  u32 lo = 0, hi = size ? (size - 1) / B : 0u;
-  const u32 q = cap / 4;
-  if (have_mid && q >= B && size >= q) {
-    if (UPPER ? mid_key <= x : mid_key < x) lo = q / B < hi ? q / B : hi;
-    else hi = q / B - 1;
-  }
-  while (lo < hi) {
-    const u32 mid = (lo + hi) >> 1;
-    const K k = keys[mid * B + (B - 1)];
-    if (UPPER ? k <= x : k < x) lo = mid + 1; else hi = mid;
-  }
-  return lo * B;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) i[q] = i[q] < nb ? i[q] : nb - 1;
 }
 
 // Inclusive scan over the wave.
@@ -277,115 +268,186 @@ __device__ __forceinline__ void wave_copy_runs(const ReadArgs<K>& a, u64 src, u6
   }
 }
 
-// Answer of query j (live: it exists).  All lanes of the wave call.
-template <typename K, int OP>
+// Answers of queries j[0..Q) of every lane (live: it exists).  All lanes of
+// the wave call.
+template <typename K, int OP, int Q>
 __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<K>& t,
-                                            const K* s_top, u32 j, bool live) {
+                                            const K* s_top, const u32 (&j)[Q],
+                                            const bool (&live)[Q]) {
   constexpr u32 B = 64 / sizeof(K);
+  constexpr bool UPPER = OP == kOpPredecessor;   // bound: first key > x, else >= x
   const K NF = key_max<K>();
-  const K x = live ? a.skeys[j] : K(0);
-  const K hi = (OP == kOpRange && live) ? a.hi[j] : K(0);
-  u32 b = find_bucket<K>(t, s_top, a.nb, x);
-  // header (size and next) and the middle key of the bucket's head node
-  NodeHdr h;
-  u32 node = b;
-  const u64 w = *reinterpret_cast<const u64*>(&a.hdr[b].size);
-  const K mid = a.nkeys[(u64)b * a.cap + (a.cap / 4 - 1)];
-  h.fence = 0;
-  h.size = (u32)w;
-  h.next = (u32)(w >> 32);
-  const bool single = h.next == kNil;
-  if (!single && OP != kOpPredecessor) node = locate_node(a.hdr, a.pool, b, (u64)x, &h);
-  bool bad = node == kBadLink || h.size > a.cap;
-  if (bad) {
-    node = b;
-    h.size = 0;
-    h.next = kNil;
-  }
-  // slot of x in the node: its 64-byte block, then the keys in it
-  const u64 nb0 = (u64)node * a.cap;
-  const K* keys = a.nkeys + nb0;
-  u32 lt, le;
-  const u32 base = node_block<K, OP == kOpPredecessor>(keys, a.cap, h.size, x, mid, single);
-  const u32 valid = h.size - base < B ? h.size - base : B;
-  quad_count<K, (int)B, true, false>(keys + base, a.cap, valid, x, OP == kOpRange ? hi : x, &lt,
-                                     &le);
   const OccLevels occ = occ_levels(a.occ, a.nb);
-  const u64 at = nb0 + base;
-  if (OP == kOpLookup) {
-    K rv = NF;
-    // a value is read once, from a random line: a non-temporal load leaves
-    // the cache to the lines that are read again
-    if (le > lt) rv = __builtin_nontemporal_load(&a.nvals[at + lt]);
-    if (live) a.out_v[j] = rv;
-  } else if (OP == kOpSuccessor) {
-    u64 slot = at + lt;
-    if (lt >= valid && !bad) {   // past the node: the next node that holds a key
-      NodeHdr g;
-      const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b, h, &g);
-      bad = nn == kBadLink;
-      slot = nn == kNil ? ~0ull : (u64)nn * a.cap;
+  K x[Q], hi[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    x[q] = live[q] ? a.skeys[j[q]] : K(0);
+    hi[q] = (OP == kOpRange && live[q]) ? a.hi[j[q]] : x[q];
+  }
+  u32 b[Q];
+  find_buckets<K, Q>(t, s_top, a.nb, x, b);
+
+  // header (size and next) and the key at slot cap/4 - 1, the middle of a
+  // bulk-loaded node, of the buckets' head nodes
+  u64 w[Q];
+  K mid[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    w[q] = *reinterpret_cast<const u64*>(&a.hdr[b[q]].size);
+    mid[q] = a.nkeys[(u64)b[q] * a.cap + (a.cap / 4 - 1)];
+  }
+  u32 node[Q], size[Q], next[Q], lo[Q], hb[Q];
+  bool single[Q], bad[Q];
+  const u32 qs = a.cap / 4;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    node[q] = b[q];
+    size[q] = (u32)w[q];
+    next[q] = (u32)(w[q] >> 32);
+    single[q] = next[q] == kNil;
+    if (!single[q] && OP != kOpPredecessor) {
+      NodeHdr h;
+      h.size = 0;
+      h.next = kNil;
+      node[q] = locate_node(a.hdr, a.pool, b[q], (u64)x[q], &h);
+      size[q] = h.size;
+      next[q] = h.next;
     }
-    K rk = NF, rv = NF;
-    if (!bad && slot != ~0ull) {
-      rk = a.nkeys[slot];
-      rv = __builtin_nontemporal_load(&a.nvals[slot]);
+    bad[q] = node[q] == kBadLink || size[q] > a.cap;
+    if (bad[q]) {
+      node[q] = b[q];
+      size[q] = 0;
+      next[q] = kNil;
     }
-    if (live) {
-      a.out_k[j] = rk;
-      a.out_v[j] = rv;
+    // 64-byte blocks [lo, hb] of the node that may hold the bound
+    lo[q] = 0;
+    hb[q] = size[q] ? (size[q] - 1) / B : 0u;
+    if (single[q] && qs >= B && size[q] >= qs) {
+      if (UPPER ? mid[q] <= x[q] : mid[q] < x[q]) lo[q] = qs / B < hb[q] ? qs / B : hb[q];
+      else hb[q] = qs / B - 1;
     }
-  } else if (OP == kOpPredecessor) {
-    u64 slot = at + le - 1;
-    // nothing up to x in the block: the key before it, in the chain or in an
-    // earlier bucket (a block after a node's first follows a key <= x)
-    if (!bad && (le == 0 || !single)) {
-      if (base > 0 && single) slot = at - 1;
-      else slot = predecessor_slot<K>(a.hdr, a.nkeys, occ, a.pool, a.cap, b, x, &bad);
+  }
+  // the block: each step reads the last key of the middle one
+  bool open = true;
+  while (open) {
+    K k[Q];
+    open = false;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (lo[q] < hb[q])
+        k[q] = a.nkeys[(u64)node[q] * a.cap + ((lo[q] + hb[q]) >> 1) * B + (B - 1)];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (lo[q] < hb[q]) {
+        const u32 m = (lo[q] + hb[q]) >> 1;
+        if (UPPER ? k[q] <= x[q] : k[q] < x[q]) lo[q] = m + 1; else hb[q] = m;
+      }
+      open = open || lo[q] < hb[q];
     }
-    K rk = K(0), rv = NF;
-    if (!bad && slot != ~0ull) {
-      rk = a.nkeys[slot];
-      rv = __builtin_nontemporal_load(&a.nvals[slot]);
+  }
+  // the keys of the block below x (lt) and not above x or hi (le)
+  u32 lt[Q], le[Q], valid[Q];
+  u64 at[Q];
+  {
+    QuadBlock<K, (int)B> blk[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      at[q] = (u64)node[q] * a.cap + lo[q] * B;
+      valid[q] = size[q] - lo[q] * B < B ? size[q] - lo[q] * B : B;
+      quad_fetch<K, (int)B>(a.nkeys + at[q], a.cap, blk[q]);
     }
-    if (live) {
-      a.out_k[j] = rk;
-      a.out_v[j] = rv;
-    }
-  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      quad_count<K, (int)B, true, false>(blk[q], valid[q], x[q], hi[q], &lt[q], &le[q]);
+  }
+
+  if constexpr (OP == kOpRange) {
     // the range's keys node by node: [p, ub) of each, copied by the wave
-    bool more = live && !bad && x <= hi;
-    const u64 ob = (u64)j * a.maxpq;
-    u32 cnt = 0, p = base + lt;
-    u32 ub = base + le;
-    if (more && le == valid && ub < h.size)   // every key of the block is in the range
-      ub = upper_bound_idx<K>(keys, ub, h.size, hi);
-    while (wave_ballot(more)) {
-      const u32 got = more ? ub - p : 0u;
-      const u32 room = cnt < a.maxpq ? a.maxpq - cnt : 0u;
-      wave_copy_runs<K>(a, (u64)node * a.cap + p, ob + cnt, got < room ? got : room);
-      cnt += got;
-      if (more && ub < h.size) more = false;   // a key above hi ends the range
-      if (more) {
-        NodeHdr g;
-        const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b, h, &g);
-        if (nn == kNil || nn == kBadLink || g.size > a.cap) {
-          bad = nn != kNil;
-          more = false;
-        } else {
-          node = nn;
-          h = g;
-          p = 0;
-          // a fence bounds its node's keys from above
-          ub = h.fence <= (u64)hi
-                   ? h.size
-                   : upper_bound_idx<K>(a.nkeys + (u64)node * a.cap, 0u, h.size, hi);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      bool more = live[q] && !bad[q] && x[q] <= hi[q];
+      const u64 ob = (u64)j[q] * a.maxpq;
+      u32 cnt = 0, p = lo[q] * B + lt[q];
+      u32 ub = lo[q] * B + le[q];
+      NodeHdr h;
+      h.fence = 0;
+      h.size = size[q];
+      h.next = next[q];
+      if (more && le[q] == valid[q] && ub < h.size)   // every key of the block is in the range
+        ub = upper_bound_idx<K>(a.nkeys + (u64)node[q] * a.cap, ub, h.size, hi[q]);
+      while (wave_ballot(more)) {
+        const u32 got = more ? ub - p : 0u;
+        const u32 room = cnt < a.maxpq ? a.maxpq - cnt : 0u;
+        wave_copy_runs<K>(a, (u64)node[q] * a.cap + p, ob + cnt, got < room ? got : room);
+        cnt += got;
+        if (more && ub < h.size) more = false;   // a key above hi ends the range
+        if (more) {
+          NodeHdr g;
+          const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
+          if (nn == kNil || nn == kBadLink || g.size > a.cap) {
+            bad[q] = nn != kNil;
+            more = false;
+          } else {
+            node[q] = nn;
+            h = g;
+            p = 0;
+            // a fence bounds its node's keys from above
+            ub = h.fence <= (u64)hi[q]
+                     ? h.size
+                     : upper_bound_idx<K>(a.nkeys + (u64)nn * a.cap, 0u, h.size, hi[q]);
+          }
         }
       }
+      if (live[q]) a.counts[j[q]] = bad[q] ? 0u : cnt;
     }
-    if (live) a.counts[j] = bad ? 0u : cnt;
+  } else {
+    // slot of the answer, ~0 when there is none
+    u64 slot[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (OP == kOpLookup) {
+        slot[q] = le[q] > lt[q] ? at[q] + lt[q] : ~0ull;
+      } else if (OP == kOpSuccessor) {
+        slot[q] = at[q] + lt[q];
+        if (lt[q] >= valid[q] && !bad[q]) {   // past the node: the next one that holds a key
+          NodeHdr h, g;
+          h.next = next[q];
+          const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
+          bad[q] = nn == kBadLink;
+          slot[q] = nn == kNil ? ~0ull : (u64)nn * a.cap;
+        }
+      } else {
+        slot[q] = at[q] + le[q] - 1;
+        // nothing up to x in the block: the key before it, in the chain or in
+        // an earlier bucket (a block after a node's first follows a key <= x)
+        if (!bad[q] && (le[q] == 0 || !single[q]) && !(lo[q] > 0 && single[q]))
+          slot[q] = predecessor_slot<K>(a.hdr, a.nkeys, occ, a.pool, a.cap, b[q], x[q], &bad[q]);
+      }
+      if (bad[q]) slot[q] = ~0ull;
+    }
+    K rv[Q], rk[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      rv[q] = NF;
+      rk[q] = OP == kOpPredecessor ? K(0) : NF;
+      if (slot[q] != ~0ull) {
+        if (OP != kOpLookup) rk[q] = a.nkeys[slot[q]];
+        // a value is read once, from a random line: a non-temporal load leaves
+        // the cache to the lines that are read again
+        rv[q] = __builtin_nontemporal_load(&a.nvals[slot[q]]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (live[q]) {
+        if (OP != kOpLookup) a.out_k[j[q]] = rk[q];
+        a.out_v[j[q]] = rv[q];
+      }
+    }
   }
-  if (live && bad) atomicCAS(a.err, 0u, kErrInternal);
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (live[q] && bad[q]) atomicCAS(a.err, 0u, kErrInternal);
 }
 
 // The top directory level into LDS.
@@ -410,8 +472,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   __shared__ __align__(16) K s_top[DirTop<K>::n];
   load_top<K, NT>(t, s_top);
   const u32 lane = threadIdx.x & 63u;
-  const u32 j = (blockIdx.x * (NT / 64) + (threadIdx.x >> 6)) * qpw + lane;
-  direct_read<K, OP>(a, t, s_top, j, lane < qpw && j < a.m);
+  const u32 j[1] = {(blockIdx.x * (NT / 64) + (threadIdx.x >> 6)) * qpw + lane};
+  const bool live[1] = {lane < qpw && j[0] < a.m};
+  direct_read<K, OP, 1>(a, t, s_top, j, live);
 }
 
 }  // namespace flix

@@ -1,10 +1,18 @@
 // Persistent fused drain: one co-resident grid executes a whole queue of
 // mixed-type batches (lookup, successor, range, insert, delete) in order.
-// Every batch runs the same phases as the per-batch launches (histogram,
-// onesweep passes, then the read kernel or slices + update kernel), with a
-// grid barrier between phases instead of a kernel boundary.  The queue lives
-// in device memory, so one launch (or one hipGraph replay) drains it, and the
-// batches can change between replays.
+// Read batches are answered in input order by the searches of flix_direct.hpp
+// and run into one another: the grid meets at a barrier before a read batch
+// only where its buffers overlap those of a batch since the last barrier.
+// Update batches run the phases of the per-batch launches (histogram, onesweep
+// passes, slices + update kernel) with a grid barrier between them instead of
+// a kernel boundary.  The queue lives in device memory, so one launch (or one
+// hipGraph replay) drains it, and the batches can change between replays.
+//
+// What bounds it: a barrier of the grid costs 11 to 20 us (the release of each
+// workgroup writes its XCD's L2 back).  While every batch was sorted, with
+// P + 3 barriers, 40 batches of 2^8 to 2^20 operations on 2^26 keys (4.9 M
+// reads, eight updates of 0.5 k to 49 k keys) took 8.7 ms; they take 2.26 ms,
+// about 1.4 of it in the eight updates.
 //
 // Ordering and memory: a grid barrier is arrive (agent-scope release +
 // atomic) / wait (generation word) / agent-scope acquire.  Tiles of a pass are
@@ -15,7 +23,7 @@
 #pragma once
 
 #include "flix_device.hpp"
-#include "flix_read2.hpp"
+#include "flix_direct.hpp"
 #include "flix_sort.hpp"
 #include "flix_update.hpp"
 
@@ -67,6 +75,8 @@ struct alignas(16) StoreLayout {
   u32 pool;
   u32 pad[2];
   OccLevels occ;
+  const void* dir;   // search levels above mkba (flix_direct.hpp)
+  const void* pad2;
 };
 
 template <typename K>
@@ -149,33 +159,90 @@ __device__ __forceinline__ bool grid_sync(DrainCtl* c, u32 nblocks) {
 
 template <typename K, int RB, int GL, int KPL>
 struct DrainSmemSize {
-  static constexpr int U = KPL >= 16 ? 2 : 4;
   static constexpr size_t hist = sizeof(HistSmem<K, RB>);
-  static constexpr size_t pass_idx = sizeof(OnesweepSmem<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayIndex>);
   static constexpr size_t pass_val = sizeof(OnesweepSmem<K, K, RB, kDrainSortNT, kDrainSortIPT, kPayValue>);
   static constexpr size_t pass_none = sizeof(OnesweepSmem<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayNone>);
-  static constexpr size_t read = sizeof(ReadSmem<K, 512, 256>);
   static constexpr size_t slices = sizeof(SliceSmem<K, (sizeof(K) == 4 ? 1024 : 512), 256>);
   static constexpr size_t fixed() {
     size_t m = hist;
-    m = m > pass_idx ? m : pass_idx;
     m = m > pass_val ? m : pass_val;
     m = m > pass_none ? m : pass_none;
-    m = m > read ? m : read;
     m = m > slices ? m : slices;
     return m;
   }
 };
+
+// Memory a batch reads and writes outside the store, as [begin, end) pairs.
+struct BatchSpans {
+  u64 in[2][2];
+  u64 out[3][2];
+};
+template <typename K>
+__device__ __forceinline__ BatchSpans batch_spans(const DrainBatch& d, u32 max_batch) {
+  BatchSpans s;
+  const u64 n = (d.n > max_batch || d.op > kOpLast) ? 0 : d.n;
+  const bool range = d.op == kOpRange;
+  const u64 pairs = range ? n * d.maxpq : n;
+  const bool outs = n != 0 && d.op != kOpInsert && d.op != kOpDelete;
+  const bool keyed = range || d.op == kOpSuccessor || d.op == kOpPredecessor;
+  auto put = [](u64 (&r)[2], const void* p, u64 bytes) {
+    r[0] = (u64)p;
+    r[1] = p ? (u64)p + bytes : 0;
+  };
+  put(s.in[0], n ? d.keys : nullptr, n * sizeof(K));
+  put(s.in[1], n && (range || d.op == kOpInsert) ? d.aux : nullptr, n * sizeof(K));
+  put(s.out[0], outs ? d.out_v : nullptr, pairs * sizeof(K));
+  put(s.out[1], outs && keyed ? d.out_k : nullptr, pairs * sizeof(K));
+  put(s.out[2], outs && range ? d.counts : nullptr, n * sizeof(u32));
+  return s;
+}
+__device__ __forceinline__ bool spans_conflict(const BatchSpans& a, const BatchSpans& b) {
+  bool c = false;
+  auto meet = [](const u64 (&x)[2], const u64 (&y)[2]) { return x[0] < y[1] && y[0] < x[1]; };
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c = c || meet(a.out[i], b.out[k]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c = c || meet(a.out[i], b.in[k]) || meet(a.in[k], b.out[i]);
+  }
+  return c;
+}
+
+// Read batch of a drain: units of Q * 64 queries go to the waves of the grid
+// in turn, from wave `rot` on.  Returns whether this wave had any.
+template <typename K, int OP, int Q>
+__device__ __forceinline__ bool drain_read(const ReadArgs<K>& ra, const DirTree<K>& tree,
+                                           const K* s_top, u32 wave, u32 waves, u32 rot) {
+  const u32 lane = threadIdx.x & 63u;
+  const u32 units = (ra.m + 64 * Q - 1) / (64 * Q);
+  bool any = false;
+  for (u32 u = wave >= rot ? wave - rot : wave + waves - rot; u < units; u += waves) {
+    u32 j[Q];
+    bool live[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      j[q] = (u * Q + q) * 64u + lane;
+      live[q] = j[q] < ra.m;
+    }
+    direct_read<K, OP, Q>(ra, tree, s_top, j, live);
+    any = true;
+  }
+  return any;
+}
 
 template <typename K, int RB, int GL, int KPL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_drain(DrainArgs<K> a) {
   extern __shared__ unsigned char smem[];
   __shared__ UpdShared s_upd;
   __shared__ u32 s_epoch;
+  __shared__ __align__(16) K s_top[DirTop<K>::n];
   constexpr int R = RadixShape<K, RB>::R;
   constexpr int P = RadixShape<K, RB>::P;
-  constexpr int U = KPL >= 16 ? 2 : 4;
-  constexpr int SR = 512;                       // read share
+  // queries per lane in flight: the registers of the update phases leave the
+  // grid two or three waves per SIMD, so a wave has to bring its own
+  // parallelism
+  constexpr int Q = sizeof(K) == 4 ? 4 : 2;
   constexpr int SS = sizeof(K) == 4 ? 1024 : 512;  // slice share
   const u32 G = gridDim.x;
   const u32 blk = blockIdx.x;
@@ -184,6 +251,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const K* const mkba = (const K*)L.mkba;
   K* const nkeys = (K*)L.nkeys;
   K* const nvals = (K*)L.nvals;
+  const DirTree<K> tree = dir_tree<K>(mkba, (const K*)L.dir, L.nb);
+  load_top<K, 256>(tree, s_top);
+  const u32 waves = G * 4u;
+  const u32 wave = (threadIdx.x >> 6) * G + blk;   // neighbouring units on different CUs
 
   // Epochs: every workgroup reads the base before anyone advances it (the
   // advance happens after the first barrier, by the most this drain can use,
@@ -203,30 +274,98 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   // both histogram slots start at zero
   if (blk == 0)
     for (int i = threadIdx.x; i < 2 * P * R; i += 256) a.hist[i] = 0;
-  if (blk == 0 && threadIdx.x == 0 && a.tstamp) a.tstamp[0] = wall_clock64();
+  if (a.tstamp)
+    for (u64 i = (u64)blk * 256 + threadIdx.x; i <= a.nbatch; i += (u64)G * 256)
+      a.tstamp[i] = i == 0 ? wall_clock64() : 0ull;
   const u32 epoch_end = epoch + need_epochs;
   const bool failed0 = grid_sync(dc, G);
   if (blk == 0 && threadIdx.x == 0)
     __hip_atomic_store(&dc->epoch, epoch_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (failed0) return;
 
-  u32 nz = 0;   // batches processed so far: selects the histogram slot
+  u32 nz = 0;     // update batches processed so far: selects the histogram slot
+  u32 rot = 0;    // wave that takes the next read unit
+  u32 pend = 0;   // first batch since the last barrier
   for (u32 bi = 0; bi < a.nbatch; ++bi) {
-    const DrainBatch d = a.batches[bi];
+    const DrainBatch d = a.batches[bi];   // uniform
     const u32 n = d.n;
     if (n > a.max_batch || d.op > kOpLast) {   // rewritten descriptor out of range
       if (blk == 0 && threadIdx.x == 0) atomicOr(&dc->err, 4u);
       continue;
     }
     if (n == 0) {
-      if (blk == 0 && threadIdx.x == 0 && a.tstamp) a.tstamp[bi + 1] = wall_clock64();
+      if (blk == 0 && threadIdx.x == 0 && a.tstamp)
+        atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
       continue;
     }
     const bool is_update = d.op == kOpInsert || d.op == kOpDelete;
+    // Read batches run into one another: a barrier comes before a batch only
+    // where it reads what a batch since the last barrier writes, or writes
+    // what one reads or writes.  One lane compares with each of those batches
+    // (at most 64).
+    {
+      const u32 npend = bi - pend;
+      bool wait = npend >= 64u;
+      if (!wait && npend > 0) {
+        const u32 lane = threadIdx.x & 63u;
+        bool c = false;
+        if (lane < npend)
+          c = spans_conflict(batch_spans<K>(a.batches[pend + lane], a.max_batch),
+                             batch_spans<K>(d, a.max_batch));
+        wait = wave_ballot(c) != 0;
+      }
+      if (wait) {
+        if (grid_sync(dc, G)) return;
+        pend = bi;
+      }
+    }
+    if (!is_update) {
+      ReadArgs<K> ra;
+      ra.skeys = (const K*)d.keys;
+      ra.sidx = nullptr;
+      ra.m = n;
+      ra.mkba = mkba;
+      ra.nb = L.nb;
+      ra.hdr = L.hdr;
+      ra.nkeys = nkeys;
+      ra.nvals = nvals;
+      ra.cap = a.cap;
+      ra.share = 0;
+      ra.out_v = (K*)d.out_v;
+      ra.out_k = (K*)d.out_k;
+      ra.hi = (const K*)d.aux;
+      ra.counts = d.counts;
+      ra.maxpq = d.maxpq;
+      ra.pool = L.pool;
+      ra.err = &a.ctl->status;
+      ra.occ = L.occ.w0;
+      ra.cuts = nullptr;
+      bool any;
+      u32 per = 64 * Q;
+      switch (d.op) {
+        case kOpLookup: any = drain_read<K, kOpLookup, Q>(ra, tree, s_top, wave, waves, rot); break;
+        case kOpSuccessor:
+          any = drain_read<K, kOpSuccessor, Q>(ra, tree, s_top, wave, waves, rot);
+          break;
+        case kOpRange:
+          any = drain_read<K, kOpRange, 1>(ra, tree, s_top, wave, waves, rot);
+          per = 64;
+          break;
+        default:
+          any = drain_read<K, kOpPredecessor, Q>(ra, tree, s_top, wave, waves, rot);
+          break;
+      }
+      rot = (u32)((rot + (n + per - 1) / per) % waves);
+      if (any && a.tstamp) {   // the last wave to end leaves its time
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if ((threadIdx.x & 63u) == 0) atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
+      }
+      continue;
+    }
     const u32 slot = nz & 1u;
     ++nz;
     u32* hist = a.hist + slot * (P * R);
-    if (is_update && blk == 0) {
+    if (blk == 0) {
       if (threadIdx.x == 0) {
         a.ctl->need = 0;
         a.ctl->call_err = 0;
@@ -269,17 +408,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         for (u32 t = blk; t < ntiles; t += G)
           onesweep_tile<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayNone>(
               pa, t, *reinterpret_cast<OnesweepSmem<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayNone>*>(smem));
-      } else {
-        PassArgs<K, u32> pa;
-        pa.kin = ki;
-        pa.vin = (p == 0) ? nullptr : (const u32*)((p & 1) ? bp0 : bp1);
-        pa.kout = ko;
-        pa.vout = (u32*)((p & 1) ? bp1 : bp0);
-        pa.n = n; pa.shift = (u32)(p * RB); pa.hist_p = hist + p * R;
-        pa.status = a.status; pa.status_cl = a.status_cl; pa.epoch = epoch; pa.err = &dc->err;
-        for (u32 t = blk; t < ntiles; t += G)
-          onesweep_tile<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayIndex>(
-              pa, t, *reinterpret_cast<OnesweepSmem<K, u32, RB, kDrainSortNT, kDrainSortIPT, kPayIndex>*>(smem));
       }
       if (grid_sync(dc, G)) return;
     }
@@ -289,34 +417,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     if (blk == 0)
       for (int i = threadIdx.x; i < P * R; i += 256) a.hist[(slot ^ 1u) * (P * R) + i] = 0;
     // ---- apply
-    if (!is_update) {
-      ReadArgs<K> ra;
-      ra.skeys = a.bk[r];
-      ra.sidx = (const u32*)a.bp[r];
-      ra.m = n;
-      ra.mkba = mkba;
-      ra.nb = L.nb;
-      ra.hdr = L.hdr;
-      ra.nkeys = nkeys;
-      ra.nvals = nvals;
-      ra.cap = a.cap;
-      ra.share = SR;
-      ra.out_v = (K*)d.out_v;
-      ra.out_k = (K*)d.out_k;
-      ra.hi = (const K*)d.aux;
-      ra.counts = d.counts;
-      ra.maxpq = d.maxpq;
-      ra.pool = L.pool;
-      ra.err = &a.ctl->status;
-      ra.occ = L.occ.w0;
-      ra.cuts = nullptr;   // each share searches its own cuts
-      const u32 nshares = (u32)(((u64)n + L.nb + SR - 1) / SR);
-      for (u32 vb = blk; vb < nshares; vb += G) {
-        read_share<K, 256, SR, GL, KPL, U>(ra, (int)d.op, vb,
-                                          *reinterpret_cast<ReadSmem<K, SR, 256>*>(smem));
-        __syncthreads();
-      }
-    } else {
+    {
       SliceArgs<K> sa;
       sa.skeys = a.bk[r];
       sa.svals = d.op == kOpInsert ? (const K*)a.bp[r] : nullptr;
@@ -362,7 +463,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         delete_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
     }
     if (grid_sync(dc, G)) return;
-    if (blk == 0 && threadIdx.x == 0 && a.tstamp) a.tstamp[bi + 1] = wall_clock64();
+    pend = bi + 1;
+    if (blk == 0 && threadIdx.x == 0 && a.tstamp) atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
+  }
+  if (a.tstamp) {
+    // the stamps of overlapping batches in batch order: running maximum
+    if (grid_sync(dc, G)) return;
+    if (blk == 0 && threadIdx.x < 64) {
+      unsigned long long run = 0;
+      for (u32 i0 = 0; i0 <= a.nbatch; i0 += 64) {
+        const u32 i = i0 + threadIdx.x;
+        u64 v = i <= a.nbatch ? ld_agent((const u64*)&a.tstamp[i]) : 0ull;
+#pragma unroll
+        for (u32 o = 1; o < 64; o <<= 1) {
+          const u64 y = shfl64(v, threadIdx.x >= o ? threadIdx.x - o : threadIdx.x);
+          if (threadIdx.x >= o) v = v > y ? v : y;
+        }
+        v = v > run ? v : run;
+        run = shfl64(v, 63);
+        if (i <= a.nbatch) a.tstamp[i] = v;
+      }
+    }
   }
 }
 
