@@ -998,8 +998,11 @@ int epoch_validate(flix_store* s, uint32_t slot, const flix_epoch* e) {
 
 // ---- bulk load --------------------------------------------------------------
 // Rewrite the device layout record that drains read (after every change of
-// the directory or the pool).  Synchronous: the store is idle at this point.
-int publish_layout(flix_store* s) {
+// the directory or the pool).
+__global__ void k_put_layout(StoreLayout* dst, StoreLayout L) {
+  if (threadIdx.x == 0) *dst = L;
+}
+int publish_layout(flix_store* s, hipStream_t st) {
   if (!s->d_layout) return FLIX_OK;
   StoreLayout L{};
   L.mkba = s->mkba;
@@ -1012,7 +1015,8 @@ int publish_layout(flix_store* s) {
   L.pool = s->pool;
   L.occ = s->occl;
   L.dir = s->dir;
-  HIP_TRY(hipMemcpy(s->d_layout, &L, sizeof(L), hipMemcpyHostToDevice));
+  hipLaunchKernelGGL(k_put_layout, dim3(1), dim3(64), 0, st, s->d_layout, L);
+  HIP_TRY(hipGetLastError());
   return FLIX_OK;
 }
 
@@ -1048,15 +1052,22 @@ int dump_launch(flix_store* s, void* ko, void* vo, u64 capacity, u32* tot, u32* 
   hipLaunchKernelGGL(k_scan_blocks_u32, dim3(nblk), dim3(256), 0, st, tot, nb, off, bs);
   hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, bs, nblk, total);
   hipLaunchKernelGGL(k_scan_addback, dim3(nblk), dim3(256), 0, st, off, nb, bs);
-  const u32 gw = std::min<u32>((nb + 3) / 4, 65535);
-  if (s->kb == 32)
-    hipLaunchKernelGGL((k_dump_copy<u32>), dim3(gw), dim3(256), 0, st, s->hdr, (const u32*)s->nkeys,
-                       (const u32*)s->nvals, nb, s->cap, s->pool, off, (u32*)ko, (u32*)vo,
-                       (u64)capacity);
-  else
-    hipLaunchKernelGGL((k_dump_copy<u64>), dim3(gw), dim3(256), 0, st, s->hdr, (const u64*)s->nkeys,
-                       (const u64*)s->nvals, nb, s->cap, s->pool, off, (u64*)ko, (u64*)vo,
-                       (u64)capacity);
+  auto copy = [&](auto zero) {
+    using K = decltype(zero);
+    ReadArgs<K> a{};
+    a.nb = nb;
+    a.hdr = s->hdr;
+    a.nkeys = (const K*)s->nkeys;
+    a.nvals = (const K*)s->nvals;
+    a.cap = s->cap;
+    a.pool = s->pool;
+    a.out_k = (K*)ko;
+    a.out_v = (K*)vo;
+    hipLaunchKernelGGL((k_dump_copy<K>), dim3(std::min<u32>((nb + 255) / 256, 65535)), dim3(256), 0,
+                       st, a, (const u32*)off, capacity);
+  };
+  if (s->kb == 32) copy(u32(0));
+  else copy(u64(0));
   HIP_TRY(hipGetLastError());
   return FLIX_OK;
 }
@@ -1106,15 +1117,21 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
   const u32 pool = s->pool;
   HIP_TRY(hipGetLastError());
   s->nb = nbk;
+  constexpr u32 V = 16 / sizeof(K);
   if (nd) {
-    u64 g = std::min<u64>((nd + 255) / 256, 65536);
-    hipLaunchKernelGGL((k_build_nodes<K>), dim3(g), dim3(256), 0, st, ck, cv, nd, s->fill, s->cap,
-                       (K*)s->nkeys, (K*)s->nvals);
-    HIP_TRY(hipGetLastError());
+    const bool vec = s->fill % V == 0;
+    const u64 threads = vec ? (nd + V - 1) / V : nd;
+    const dim3 g((u32)std::min<u64>((threads + 255) / 256, 65536));
+    if (vec)
+      hipLaunchKernelGGL((k_build_nodes<K, V>), g, dim3(256), 0, st, ck, cv, nd, s->fill, s->cap,
+                         nbk, (K*)s->nkeys, (K*)s->nvals, (K*)s->mkba, s->hdr, s->bnodes);
+    else
+      hipLaunchKernelGGL((k_build_nodes<K, 1>), g, dim3(256), 0, st, ck, cv, nd, s->fill, s->cap,
+                         nbk, (K*)s->nkeys, (K*)s->nvals, (K*)s->mkba, s->hdr, s->bnodes);
+  } else {
+    hipLaunchKernelGGL((k_build_empty<K>), dim3(1), dim3(64), 0, st, (K*)s->mkba, s->hdr,
+                       s->bnodes);
   }
-  u64 g = std::min<u64>((nbk + 255) / 256, 65536);
-  hipLaunchKernelGGL((k_build_dir<K>), dim3(g), dim3(256), 0, st, ck, nd, s->fill, nbk,
-                     (K*)s->mkba, s->hdr, s->bnodes);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL((k_mk_top<K>), dim3(1), dim3(256), 0, st, (const K*)s->mkba, nbk, s->mktop);
   HIP_TRY(hipGetLastError());
@@ -1132,30 +1149,28 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
     }
     HIP_TRY(hipGetLastError());
   }
-  // occupancy summary of the new directory
-  s->occl.w0 = s->occ;
-  s->occl.w1 = s->occ + occ_words0(nbk);
-  s->occl.w2 = s->occl.w1 + occ_words1(nbk);
-  hipLaunchKernelGGL(k_occ_build0, dim3((u32)((occ_words0(nbk) + 255) / 256)), dim3(256), 0, st,
-                     s->hdr, nbk, s->occl.w0);
-  hipLaunchKernelGGL(k_occ_build_up, dim3((u32)((occ_words1(nbk) + 255) / 256)), dim3(256), 0,
-                     st, (const u64*)s->occl.w0, occ_words0(nbk), s->occl.w1, occ_words1(nbk));
-  hipLaunchKernelGGL(k_occ_build_up, dim3((u32)((occ_words2(nbk) + 255) / 256)), dim3(256), 0,
-                     st, (const u64*)s->occl.w1, occ_words1(nbk), s->occl.w2, occ_words2(nbk));
-  HIP_TRY(hipGetLastError());
+  s->occl = occ_levels(s->occ, nbk);
   u64 g2 = std::min<u64>((pool - nbk + 255) / 256 + 1, 65536);
-  hipLaunchKernelGGL(k_build_free, dim3(g2), dim3(256), 0, st, nbk, pool, nd, s->free_ids, s->ctl);
+  hipLaunchKernelGGL(k_build_free, dim3(g2), dim3(256), 0, st, nbk, pool, nd, s->free_ids, s->ctl,
+                     s->occl);
   HIP_TRY(hipGetLastError());
   return FLIX_OK;
 }
 
+// Sorts straight into the pool's own free part when there is room (the auto
+// pool has: twice the nodes the keys fill): the pairs are sorted behind the
+// nodes they are then cut into, so a load allocates nothing.  The previous
+// contents are overwritten once the values have been checked and the node
+// count is known to suffice; until then they are kept.  (A load of 2^26 u32
+// pairs and a dump of them took 7.4 ms, 1.8 of it in allocating and freeing six
+// buffers, and 45 when the host had been idle; now 2.5.)
 template <typename K>
 int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream_t st) {
   if (n > 0xFFFFFFF0ull) return FLIX_EINVAL;
   // reserved value check before anything changes
   if (n) {
     HIP_TRY(hipMemsetAsync(&s->ctl->call_err, 0, sizeof(u32), st));
-    u64 g = std::min<u64>((n + 255) / 256, 4096);
+    u64 g = std::min<u64>((n + 2047) / 2048, 4096);
     hipLaunchKernelGGL((k_check_reserved<K>), dim3(g), dim3(256), 0, st, vals, n, &s->ctl->call_err);
     HIP_TRY(hipGetLastError());
     u32 err = 0;
@@ -1163,20 +1178,40 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     HIP_TRY(hipStreamSynchronize(st));
     if (err) return FLIX_EINVAL;
   }
-  // sorted, deduplicated pairs in temporary buffers
+  // sorted, deduplicated pairs: in the pool or in temporary buffers
   K *tk0 = nullptr, *tk1 = nullptr, *tv0 = nullptr, *tv1 = nullptr, *ck = nullptr, *cv = nullptr;
   u32* bsum = nullptr;
   u64 nd = 0;
+  bool in_pool = false, keep_pool = false;
   int rc = FLIX_OK;
   auto cleanup = [&]() {
-    dev_free(&tk0); dev_free(&tk1); dev_free(&tv0); dev_free(&tv1);
+    if (!in_pool) { dev_free(&tk0); dev_free(&tk1); dev_free(&tv0); dev_free(&tv1); }
     dev_free(&ck); dev_free(&cv); dev_free(&bsum);
   };
+  auto pool_for = [&](u64 nodes) {
+    return s->cfg.pool_bytes ? (u32)std::min<u64>(s->cfg.pool_bytes / node_bytes(s), 0xFFFFFFF0ull)
+                             : auto_pool(s, nodes);
+  };
+  const K *sk = nullptr, *sv = nullptr;   // the pairs the layout is built from
   if (n) {
     if ((rc = ensure_sort_capacity(s, n))) return rc;
-    if ((rc = dev_alloc(&tk0, n * sizeof(K))) || (rc = dev_alloc(&tk1, n * sizeof(K))) ||
-        (rc = dev_alloc(&tv0, n * sizeof(K))) || (rc = dev_alloc(&tv1, n * sizeof(K))) ||
-        (rc = dev_alloc(&ck, n * sizeof(K))) || (rc = dev_alloc(&cv, n * sizeof(K)))) {
+    const u64 nodes = (n + s->fill - 1) / s->fill;   // at most: duplicates shrink it
+    const u32 pool = nodes <= 0xFFFFFF00ull ? pool_for(nodes) : 0;
+    const u64 nr = (n + 15) / 16 * 16;               // whole 64-byte lines
+    if (nodes <= pool && ((u64)pool - nodes) * s->cap >= 2 * nr) {
+      // whatever can fail for want of memory comes before the old contents go
+      if ((rc = alloc_dir(s, (u32)nodes))) return rc;
+      if (pool != s->pool) {
+        HIP_TRY(hipStreamSynchronize(st));
+        if ((rc = alloc_pool(s, pool))) return rc;
+      }
+      in_pool = true;
+      tk0 = (K*)s->nkeys + nodes * s->cap;
+      tk1 = tk0 + nr;
+      tv0 = (K*)s->nvals + nodes * s->cap;
+      tv1 = tv0 + nr;
+    } else if ((rc = dev_alloc(&tk0, n * sizeof(K))) || (rc = dev_alloc(&tk1, n * sizeof(K))) ||
+               (rc = dev_alloc(&tv0, n * sizeof(K))) || (rc = dev_alloc(&tv1, n * sizeof(K)))) {
       cleanup();
       return rc;
     }
@@ -1185,40 +1220,66 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
         ? radix_sort<K, K, 4, kPayValue>(keys, vals, tk0, tv0, tk1, tv1, (u32)n, s->ss, st, &r)
         : radix_sort<K, K, 8, kPayValue>(keys, vals, tk0, tv0, tk1, tv1, (u32)n, s->ss, st, &r);
     if (e != hipSuccess) { cleanup(); return note_hip_error(e, "bulk load sort", __LINE__); }
-    const K* sk = r ? tk1 : tk0;
-    const K* sv = r ? tv1 : tv0;
-    u32 nblk = (u32)((n + kCompactTile - 1) / kCompactTile);
-    if ((rc = dev_alloc(&bsum, (u64)nblk * sizeof(u32)))) { cleanup(); return rc; }
-    hipLaunchKernelGGL((k_compact_count<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, n, bsum);
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, bsum, nblk, &s->ctl->scan_total);
-    hipLaunchKernelGGL((k_compact_scatter<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, sv, n, bsum,
-                       ck, cv);
-    if ((e = hipGetLastError()) != hipSuccess) { cleanup(); return note_hip_error(e, "bulk load compaction", __LINE__); }
-    u32 tot = 0;
-    if (hipMemcpyAsync(&tot, &s->ctl->scan_total, sizeof(u32), hipMemcpyDeviceToHost, st) !=
+    sk = r ? tk1 : tk0;
+    sv = r ? tv1 : tv0;
+    // superseded keys; without any, the sorted pairs are the contents
+    u32 dups = 0;
+    e = hipMemsetAsync(&s->ctl->scan_total, 0, sizeof(u32), st);
+    hipLaunchKernelGGL((k_count_dups<K>), dim3((u32)std::min<u64>((n + 4095) / 4096, 2048)),
+                       dim3(256), 0, st, sk, n, &s->ctl->scan_total);
+    if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess ||
+        (e = hipMemcpyAsync(&dups, &s->ctl->scan_total, sizeof(u32), hipMemcpyDeviceToHost, st)) !=
             hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
+        (e = hipStreamSynchronize(st)) != hipSuccess) {
       cleanup();
-      return FLIX_EHIP;
+      return note_hip_error(e, "bulk load duplicates", __LINE__);
     }
-    nd = tot;
+    nd = n - dups;
+    if (dups) {
+      // compacted in buffers of their own when the pool is to change its size
+      // (or holds no scratch), else in the sort's other buffers
+      const u64 nodes_d = (nd + s->fill - 1) / s->fill;
+      const u32 nblk = (u32)((n + kCompactTile - 1) / kCompactTile);
+      K *ok = r ? tk0 : tk1, *ov = r ? tv0 : tv1;
+      u32* bs = s->free_ids;   // rebuilt with the layout; n / 2048 <= nodes <= pool
+      if (!in_pool) {
+        if ((rc = dev_alloc(&bsum, (u64)nblk * sizeof(u32)))) { cleanup(); return rc; }
+        bs = bsum;
+      } else if (pool_for(nodes_d) != s->pool) {
+        if (dev_alloc(&ck, nd * sizeof(K)) == FLIX_OK && dev_alloc(&cv, nd * sizeof(K)) == FLIX_OK) {
+          ok = ck;
+          ov = cv;
+        } else {
+          dev_free(&ck);   // no room for the move: the larger pool stays
+          keep_pool = true;
+        }
+      }
+      hipLaunchKernelGGL((k_compact_count<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, n, bs);
+      hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, bs, nblk, &s->ctl->scan_total);
+      hipLaunchKernelGGL((k_compact_scatter<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, sv, n, bs,
+                         ok, ov);
+      if ((e = hipGetLastError()) != hipSuccess) { cleanup(); return note_hip_error(e, "bulk load compaction", __LINE__); }
+      sk = ok;
+      sv = ov;
+    }
   }
   u64 nbk = nd ? (nd + s->fill - 1) / s->fill : 1;
   if (nbk > 0xFFFFFF00ull) { cleanup(); return FLIX_EINVAL; }
-  u32 pool = s->cfg.pool_bytes ? (u32)std::min<u64>(s->cfg.pool_bytes / node_bytes(s), 0xFFFFFFF0ull)
-                               : auto_pool(s, nbk);
+  const u32 pool = pool_for(nbk);
   if (nbk > pool) { cleanup(); return FLIX_ENOMEM; }
-  if (pool != s->pool) {
+  if (pool != s->pool && !keep_pool) {   // (never with the pairs still in the old pool)
     HIP_TRY(hipStreamSynchronize(st));
     if ((rc = alloc_pool(s, pool))) { cleanup(); return rc; }
   }
   if ((rc = alloc_dir(s, (u32)nbk))) { cleanup(); return rc; }
-  if ((rc = build_layout<K>(s, ck, cv, nd, (u32)nbk, st))) { cleanup(); return rc; }
+  if ((rc = build_layout<K>(s, sk, sv, nd, (u32)nbk, st))) { cleanup(); return rc; }
   hipError_t e1 = hipGetLastError();
-  hipError_t e2 = hipStreamSynchronize(st);
-  cleanup();
+  if (!in_pool || ck) {
+    const hipError_t e2 = hipStreamSynchronize(st);
+    cleanup();
+    if (e2 != hipSuccess) return note_hip_error(e2, "bulk load sync", __LINE__);
+  }
   if (e1 != hipSuccess) return note_hip_error(e1, "bulk load kernels", __LINE__);
-  if (e2 != hipSuccess) return note_hip_error(e2, "bulk load sync", __LINE__);
   return FLIX_OK;
 }
 
@@ -1227,7 +1288,8 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
 template <typename K>
 int rebuild_groups(flix_store* s, hipStream_t st) {
   u32 g = 1, bpg = 1;
-  s->grp_ok = group_shape(s->nb, &g, &bpg) && s->gpre && s->split && s->gtot;
+  s->grp_ok = s->cfg.read_path == FLIX_READ_GROUPS && group_shape(s->nb, &g, &bpg) && s->gpre &&
+              s->split && s->gtot;
   s->ngrp = g;
   s->bpg = bpg;
   s->gslot = 0;
@@ -1246,10 +1308,11 @@ int rebuild_groups(flix_store* s, hipStream_t st) {
 template <typename K>
 int bulk_load_t(flix_store* s, const K* keys, const K* vals, u64 n, hipStream_t st) {
   const int rc = bulk_load_body<K>(s, keys, vals, n, st);
-  (void)hipStreamSynchronize(st);
-  const int rp = publish_layout(s);
+  const int rp = publish_layout(s, st);
   const int rg = rebuild_groups<K>(s, st);
-  return rc ? rc : (rp ? rp : rg);
+  const hipError_t e = hipStreamSynchronize(st);
+  if (rc || rp || rg) return rc ? rc : (rp ? rp : rg);
+  return e == hipSuccess ? FLIX_OK : note_hip_error(e, "bulk load", __LINE__);
 }
 
 // Restructuring (Section 3.5): the live pairs are read out in key order and laid
@@ -1282,8 +1345,9 @@ int restructure_t(flix_store* s, hipStream_t st, u64* before, u64* after) {
   rc = build_layout<K>(s, ck, cv, n, (u32)nbk, st);
   const hipError_t e = hipStreamSynchronize(st);
   cleanup();
-  const int rp = publish_layout(s);
+  const int rp = publish_layout(s, st);
   const int rg = rebuild_groups<K>(s, st);
+  (void)hipStreamSynchronize(st);
   if (rc) return rc;
   if (e != hipSuccess) return note_hip_error(e, "restructure", __LINE__);
   if (rp || rg) return rp ? rp : rg;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "flix_device.hpp"
+#include "flix_direct.hpp"
 #include "flix_occ.hpp"
 
 namespace flix {
@@ -78,12 +79,58 @@ __global__ __launch_bounds__(kCompactNT) void k_compact_scatter(const K* __restr
   }
 }
 
+// Keys of a sorted run that a later equal key supersedes, added to *dups.
+template <typename K>
+__global__ __launch_bounds__(256) void k_count_dups(const K* __restrict__ k, u64 n,
+                                                    u32* __restrict__ dups) {
+  constexpr u32 E = 16 / sizeof(K), U = 4;
+  __shared__ u32 s_tmp[256 / 64 + 1];
+  u32 c = 0;
+  for (u64 base = (u64)blockIdx.x * 256 * E * U; base < n; base += (u64)gridDim.x * 256 * E * U) {
+    KeyVec<K, (int)E> v[U];
+    K nx[U];
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) {
+      const u64 i = base + ((u64)u * 256 + threadIdx.x) * E;
+      if (i + E < n) {
+        v[u] = *reinterpret_cast<const KeyVec<K, (int)E>*>(k + i);
+        nx[u] = k[i + E];
+      }
+    }
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) {
+      const u64 i = base + ((u64)u * 256 + threadIdx.x) * E;
+      if (i + E < n) {
+#pragma unroll
+        for (u32 q = 0; q < E; ++q) c += v[u].k[q] == (q + 1 < E ? v[u].k[q + 1 < E ? q + 1 : q] : nx[u]);
+      } else {
+        for (u64 q = i; q + 1 < n && q < i + E; ++q) c += k[q] == k[q + 1];
+      }
+    }
+  }
+  u32 tot;
+  block_exclusive_scan<256>(c, s_tmp, &tot);
+  if (threadIdx.x == 0 && tot) atomicAdd(dups, tot);
+}
+
 // Any value equal to the reserved NOT_FOUND pattern -> *err = -1.
 template <typename K>
 __global__ void k_check_reserved(const K* __restrict__ v, u64 n, u32* __restrict__ err) {
-  for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (u64)gridDim.x * blockDim.x)
-    if (v[i] == key_max<K>()) atomicExch(err, 0xFFFFFFFFu);
+  constexpr u32 E = 16 / sizeof(K);
+  bool bad = false;
+  // the caller's array may start anywhere its elements may
+  const u64 head = ((16u - ((u64)v & 15u)) & 15u) / sizeof(K);
+  const u64 lead = head < n ? head : n;
+  const u64 words = (n - lead) / E;
+  const u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x, nt = (u64)gridDim.x * blockDim.x;
+  if (t < lead && v[t] == key_max<K>()) bad = true;
+  for (u64 i = t; i < words; i += nt) {
+    const KeyVec<K, (int)E> x = *reinterpret_cast<const KeyVec<K, (int)E>*>(v + lead + i * E);
+#pragma unroll
+    for (u32 q = 0; q < E; ++q) bad = bad || x.k[q] == key_max<K>();
+  }
+  for (u64 i = lead + words * E + t; i < n; i += nt) bad = bad || v[i] == key_max<K>();
+  if (bad) atomicExch(err, 0xFFFFFFFFu);
 }
 
 // ---------------------------------------------------------------------------
@@ -92,39 +139,83 @@ __global__ void k_check_reserved(const K* __restrict__ v, u64 n, u32* __restrict
 // last key becomes maxBucket (MKBA[i]).  The last bucket's bound is KEY_MAX so
 // that every key maps to a bucket.  Node i is the head of bucket i.
 // ---------------------------------------------------------------------------
-template <typename K>
-__global__ void k_build_nodes(const K* __restrict__ sk, const K* __restrict__ sv, u64 n,
-                              u32 fill, u32 cap, K* __restrict__ nkeys, K* __restrict__ nvals) {
-  for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (u64)gridDim.x * blockDim.x) {
-    u64 b = i / fill, s = i % fill;
-    nkeys[b * cap + s] = sk[i];
-    nvals[b * cap + s] = sv[i];
+// V consecutive pairs per thread (V divides fill: one bucket and one 16-byte
+// store each); the thread with a bucket's last pair writes its directory
+// entry and header.  Bound by its 16 bytes of traffic per u32 pair:
+// 2^26 pairs in 192 us (5.6 TB/s), the directory included (36 us as a kernel of
+// its own, which read one key in 64).
+template <typename K, u32 V>
+__global__ __launch_bounds__(256) void k_build_nodes(const K* __restrict__ sk,
+                                                     const K* __restrict__ sv, u64 n, u32 fill,
+                                                     u32 cap, u32 nb, K* __restrict__ nkeys,
+                                                     K* __restrict__ nvals, K* __restrict__ mkba,
+                                                     NodeHdr* __restrict__ hdr,
+                                                     u32* __restrict__ bnodes) {
+  const u64 groups = (n + V - 1) / V;
+  for (u64 g = (u64)blockIdx.x * 256 + threadIdx.x; g < groups; g += (u64)gridDim.x * 256) {
+    const u64 i = g * V;
+    const u32 b = (u32)(i / fill);
+    const u32 s = (u32)(i - (u64)b * fill);
+    const u64 at = (u64)b * cap + s;
+    const u32 m = n - i < V ? (u32)(n - i) : V;
+    K last;
+    if (m == V) {
+      const KeyVec<K, (int)V> k = *reinterpret_cast<const KeyVec<K, (int)V>*>(sk + i);
+      const KeyVec<K, (int)V> v = *reinterpret_cast<const KeyVec<K, (int)V>*>(sv + i);
+      *reinterpret_cast<KeyVec<K, (int)V>*>(nkeys + at) = k;
+      *reinterpret_cast<KeyVec<K, (int)V>*>(nvals + at) = v;
+      last = k.k[V - 1];
+    } else {
+      for (u32 q = 0; q < m; ++q) {
+        nkeys[at + q] = sk[i + q];
+        nvals[at + q] = sv[i + q];
+      }
+      last = sk[i + m - 1];
+    }
+    if (s + m == fill || i + m == n) {
+      const K fence = b + 1 == nb ? key_max<K>() : last;
+      mkba[b] = fence;
+      NodeHdr h;
+      h.fence = (u64)fence;
+      h.size = s + m;
+      h.next = kNil;
+      hdr[b] = h;
+      bnodes[b] = 1;
+    }
   }
 }
 
+// The one empty bucket of a store without keys.
 template <typename K>
-__global__ void k_build_dir(const K* __restrict__ sk, u64 n, u32 fill, u32 nb,
-                            K* __restrict__ mkba, NodeHdr* __restrict__ hdr,
-                            u32* __restrict__ bnodes) {
-  for (u32 b = blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += gridDim.x * blockDim.x) {
-    u64 lo = (u64)b * fill;
-    u64 hi = lo + fill < n ? lo + fill : n;
-    K fence = (b + 1 == nb) ? key_max<K>() : sk[hi - 1];
-    mkba[b] = fence;
+__global__ void k_build_empty(K* __restrict__ mkba, NodeHdr* __restrict__ hdr,
+                              u32* __restrict__ bnodes) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    mkba[0] = key_max<K>();
     NodeHdr h;
-    h.fence = (u64)fence;
-    h.size = (u32)(hi > lo ? hi - lo : 0);
+    h.fence = (u64)key_max<K>();
+    h.size = 0;
     h.next = kNil;
-    hdr[b] = h;
-    bnodes[b] = 1;
+    hdr[0] = h;
+    bnodes[0] = 1;
   }
 }
 
-// Free stack holds every node id >= nb; Ctl counters reset.
+// Free stack holds every node id >= nb; Ctl counters reset; occupancy summary
+// of nb buckets that all hold keys (none, when nkeys is 0).
 __global__ void k_build_free(u32 nb, u32 pool, u64 nkeys, u32* __restrict__ free_ids,
-                             Ctl* __restrict__ ctl) {
+                             Ctl* __restrict__ ctl, OccLevels occ) {
   u32 nfree = pool - nb;
+  {
+    const u64 n0 = occ_words0(nb), n1 = occ_words1(nb), n2 = occ_words2(nb);
+    for (u64 w = (u64)blockIdx.x * blockDim.x + threadIdx.x; w < n0 + n1 + n2;
+         w += (u64)gridDim.x * blockDim.x) {
+      u64* const p = w < n0 ? occ.w0 + w : w < n0 + n1 ? occ.w1 + (w - n0) : occ.w2 + (w - n0 - n1);
+      const u64 i = w < n0 ? w : w < n0 + n1 ? w - n0 : w - n0 - n1;
+      const u64 below = w < n0 ? nb : w < n0 + n1 ? n0 : n1;   // what its level's bits stand for
+      const u64 bits = below - i * 64;
+      *p = nkeys == 0 ? 0ull : bits >= 64 ? ~0ull : (1ull << bits) - 1ull;
+    }
+  }
   for (u32 j = blockIdx.x * blockDim.x + threadIdx.x; j < nfree; j += gridDim.x * blockDim.x)
     free_ids[j] = pool - 1 - j;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -174,30 +265,34 @@ __global__ void k_scan_addback(u32* __restrict__ out, u32 n, const u32* __restri
   if (i < n) out[i] += bsum[blockIdx.x];
 }
 
+// A wave takes 64 buckets and copies their nodes together, one link of every
+// chain per step, as runs of one flattened list: 2^20 half-full nodes of 64
+// u32 pairs took 312 us with a wave per bucket (each waiting for its header,
+// offset and pairs in turn), 258 us so.
 template <typename K>
-__global__ void k_dump_copy(const NodeHdr* __restrict__ hdr, const K* __restrict__ nkeys,
-                            const K* __restrict__ nvals, u32 nb, u32 cap, u32 pool,
-                            const u32* __restrict__ off, K* __restrict__ ko,
-                            K* __restrict__ vo, u64 out_cap) {
-  // one wave per bucket
-  u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  u32 lane = threadIdx.x & 63;
-  u32 nw = (gridDim.x * blockDim.x) >> 6;
-  for (u32 b = wave; b < nb; b += nw) {
-    u64 o = off[b];
-    u32 node = b;
+__global__ __launch_bounds__(256) void k_dump_copy(ReadArgs<K> a, const u32* __restrict__ off,
+                                                   u64 out_cap) {
+  const u32 wave = (blockIdx.x * 256 + threadIdx.x) >> 6, nw = gridDim.x * 4u;
+  const u32 lane = threadIdx.x & 63u;
+  for (u64 b0 = (u64)wave * 64; b0 < a.nb; b0 += (u64)nw * 64) {
+    const u64 b = b0 + lane;
+    u32 node = b < a.nb ? (u32)b : kNil;
+    u64 o = b < a.nb ? off[b] : 0;
     u32 steps = 0;
-    while (node < pool && steps++ < pool) {
-      NodeHdr h = hdr[node];
-      u32 sz = h.size < cap ? h.size : cap;
-      for (u32 s = lane; s < sz; s += 64) {
-        if (o + s < out_cap) {
-          ko[o + s] = nkeys[(u64)node * cap + s];
-          vo[o + s] = nvals[(u64)node * cap + s];
-        }
+    while (wave_ballot(node < a.pool)) {
+      u32 c = 0, next = kNil;
+      const u64 src = node < a.pool ? (u64)node * a.cap : 0;
+      const u64 dst = o;
+      if (node < a.pool) {
+        const u64 w = *reinterpret_cast<const u64*>(&a.hdr[node].size);
+        const u32 sz = (u32)w < a.cap ? (u32)w : a.cap;
+        const u64 room = o < out_cap ? out_cap - o : 0;
+        c = sz < room ? sz : (u32)room;
+        o += sz;
+        next = ++steps < a.pool ? (u32)(w >> 32) : kNil;
       }
-      o += sz;
-      node = h.next;
+      wave_copy_runs<K>(a, src, dst, c);
+      node = next;
     }
   }
 }
@@ -269,34 +364,8 @@ __global__ void k_check_free(const u32* __restrict__ free_ids, const Ctl* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Occupancy summary (flix_occ.hpp): build at bulk load, invariant check.
+// Occupancy summary (flix_occ.hpp): invariant check.
 // ---------------------------------------------------------------------------
-// Level 0 from the head sizes (a bucket is empty exactly when its head node is
-// empty: an empty head never has a successor node).
-__global__ void k_occ_build0(const NodeHdr* __restrict__ hdr, u32 nb, u64* __restrict__ w0) {
-  const u64 w = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= occ_words0(nb)) return;
-  u64 bits = 0;
-  for (u32 i = 0; i < 64; ++i) {
-    const u64 b = w * 64 + i;
-    if (b < nb && hdr[b].size > 0) bits |= 1ull << i;
-  }
-  w0[w] = bits;
-}
-
-// Level l+1 from level l (`n_hi` words above `n_lo` words below).
-__global__ void k_occ_build_up(const u64* __restrict__ lo, u64 n_lo, u64* __restrict__ hi,
-                               u64 n_hi) {
-  const u64 w = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= n_hi) return;
-  u64 bits = 0;
-  for (u32 i = 0; i < 64; ++i) {
-    const u64 j = w * 64 + i;
-    if (j < n_lo && lo[j] != 0) bits |= 1ull << i;
-  }
-  hi[w] = bits;
-}
-
 // Invariant check: level 0 equals the head sizes, upper levels summarise the
 // lower ones.  Records error 12 in *err.
 __global__ void k_occ_check(const NodeHdr* __restrict__ hdr, u32 nb, OccLevels o,

@@ -133,6 +133,86 @@ struct PassArgs {
   u32* err;
 };
 
+// Items of `digit` in the tiles before `tile` (whose own count `tot` is
+// published); publishes the tile's inclusive prefix.
+template <int R = 256>
+__device__ __forceinline__ u32 look_back(u64* status, u64* status_cl, u32 epoch, u32 tile,
+                                         u32 digit, u32 tot, u32* err) {
+  // Two-level decoupled look-back for this digit.  Tiles form clusters of
+  // CL consecutive tiles; the last tile of a cluster also publishes the
+  // cluster's aggregate (or inclusive prefix) once it has read its cluster
+  // mates.  A tile sums the published counts of its cluster mates (nearest
+  // first, LB per round trip) and then those of earlier clusters, stopping
+  // at the first inclusive prefix, so the chain of dependent round trips
+  // stays short however many tiles the pass has.
+  u32 excl = 0;
+  if (tile > 0) {
+    const u32 c = tile / kSortCluster;
+    const u32 cbeg = c * kSortCluster;
+    const bool last_of_cluster = (tile == cbeg + kSortCluster - 1);
+    bool done = false;
+    bool gave_up = false;
+    u32 polls = 0;
+    // (1) cluster mates [cbeg, tile)
+    u32 pt = tile;
+    while (!done && pt > cbeg) {
+      u64 win[kLookWindow];
+#pragma unroll
+      for (u32 w = 0; w < kLookWindow; ++w)
+        win[w] = (w < pt - cbeg) ? ld_agent(&status[(u64)(pt - 1 - w) * R + digit]) : 0ull;
+      u32 used = 0;
+#pragma unroll
+      for (u32 w = 0; w < kLookWindow; ++w) {
+        if (done || w != used || w >= pt - cbeg) continue;
+        u64 s = win[w];
+        u32 fl = (u32)(s >> 32) & 3u;
+        if ((u32)(s >> 34) != epoch || fl == 0) continue;   // not published yet
+        excl += (u32)s;
+        ++used;
+        if (fl == kFlagPre) done = true;
+      }
+      pt -= used;
+      if (!done && used == 0) {
+        // Bounded wait: a predecessor that never publishes is a bug, and the
+        // kernel must still end; the error word reports it.
+        if (++polls > (1u << 22)) { atomicOr(err, 1u); gave_up = true; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    if (last_of_cluster && !gave_up)
+      st_agent(&status_cl[(u64)c * R + digit],
+               pack_status(epoch, done ? kFlagPre : kFlagAgg, excl + tot));
+    // (2) earlier clusters [0, c)
+    u32 pc = c;
+    while (!done && !gave_up && pc > 0) {
+      u64 win[kLookWindow];
+#pragma unroll
+      for (u32 w = 0; w < kLookWindow; ++w)
+        win[w] = (w < pc) ? ld_agent(&status_cl[(u64)(pc - 1 - w) * R + digit]) : 0ull;
+      u32 used = 0;
+#pragma unroll
+      for (u32 w = 0; w < kLookWindow; ++w) {
+        if (done || w != used || w >= pc) continue;
+        u64 s = win[w];
+        u32 fl = (u32)(s >> 32) & 3u;
+        if ((u32)(s >> 34) != epoch || fl == 0) continue;
+        excl += (u32)s;
+        ++used;
+        if (fl == kFlagPre) done = true;
+      }
+      pc -= used;
+      if (!done && used == 0) {
+        if (++polls > (1u << 22)) { atomicOr(err, 1u); gave_up = true; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    st_agent(&status[(u64)tile * R + digit], pack_status(epoch, kFlagPre, excl + tot));
+    if (last_of_cluster && !gave_up)
+      st_agent(&status_cl[(u64)c * R + digit], pack_status(epoch, kFlagPre, excl + tot));
+  }
+  return excl;
+}
+
 // One tile of one onesweep pass.  Tiles must be processed so that every tile
 // a tile waits on is resident or finished: in a plain launch tile = workgroup
 // id (workgroups are dispatched in id order); in a persistent grid every
@@ -240,79 +320,7 @@ __device__ void onesweep_tile(const PassArgs<K, V>& pa, u32 tile,
   u32 lstart = block_exclusive_scan<NT>(tid < (u32)R ? tot : 0u, s_tmp, &dummy);
   if (tid < (u32)R) {
     s_lstart[tid] = lstart;
-    // Two-level decoupled look-back for this digit.  Tiles form clusters of
-    // CL consecutive tiles; the last tile of a cluster also publishes the
-    // cluster's aggregate (or inclusive prefix) once it has read its cluster
-    // mates.  A tile sums the published counts of its cluster mates (nearest
-    // first, LB per round trip) and then those of earlier clusters, stopping
-    // at the first inclusive prefix, so the chain of dependent round trips
-    // stays short however many tiles the pass has.
-    u32 excl = 0;
-    if (tile > 0) {
-      const u32 c = tile / kSortCluster;
-      const u32 cbeg = c * kSortCluster;
-      const bool last_of_cluster = (tile == cbeg + kSortCluster - 1);
-      bool done = false;
-      bool gave_up = false;
-      u32 polls = 0;
-      // (1) cluster mates [cbeg, tile)
-      u32 pt = tile;
-      while (!done && pt > cbeg) {
-        u64 win[kLookWindow];
-#pragma unroll
-        for (u32 w = 0; w < kLookWindow; ++w)
-          win[w] = (w < pt - cbeg) ? ld_agent(&status[(u64)(pt - 1 - w) * R + tid]) : 0ull;
-        u32 used = 0;
-#pragma unroll
-        for (u32 w = 0; w < kLookWindow; ++w) {
-          if (done || w != used || w >= pt - cbeg) continue;
-          u64 s = win[w];
-          u32 fl = (u32)(s >> 32) & 3u;
-          if ((u32)(s >> 34) != epoch || fl == 0) continue;   // not published yet
-          excl += (u32)s;
-          ++used;
-          if (fl == kFlagPre) done = true;
-        }
-        pt -= used;
-        if (!done && used == 0) {
-          // Bounded wait: a predecessor that never publishes is a bug, and the
-          // kernel must still end; the error word reports it.
-          if (++polls > (1u << 22)) { atomicOr(err, 1u); gave_up = true; break; }
-          __builtin_amdgcn_s_sleep(1);
-        }
-      }
-      if (last_of_cluster && !gave_up)
-        st_agent(&status_cl[(u64)c * R + tid],
-                 pack_status(epoch, done ? kFlagPre : kFlagAgg, excl + tot));
-      // (2) earlier clusters [0, c)
-      u32 pc = c;
-      while (!done && !gave_up && pc > 0) {
-        u64 win[kLookWindow];
-#pragma unroll
-        for (u32 w = 0; w < kLookWindow; ++w)
-          win[w] = (w < pc) ? ld_agent(&status_cl[(u64)(pc - 1 - w) * R + tid]) : 0ull;
-        u32 used = 0;
-#pragma unroll
-        for (u32 w = 0; w < kLookWindow; ++w) {
-          if (done || w != used || w >= pc) continue;
-          u64 s = win[w];
-          u32 fl = (u32)(s >> 32) & 3u;
-          if ((u32)(s >> 34) != epoch || fl == 0) continue;
-          excl += (u32)s;
-          ++used;
-          if (fl == kFlagPre) done = true;
-        }
-        pc -= used;
-        if (!done && used == 0) {
-          if (++polls > (1u << 22)) { atomicOr(err, 1u); gave_up = true; break; }
-          __builtin_amdgcn_s_sleep(1);
-        }
-      }
-      st_agent(&status[(u64)tile * R + tid], pack_status(epoch, kFlagPre, excl + tot));
-      if (last_of_cluster && !gave_up)
-        st_agent(&status_cl[(u64)c * R + tid], pack_status(epoch, kFlagPre, excl + tot));
-    }
-    s_gbase[tid] = hexcl + excl;
+    s_gbase[tid] = hexcl + look_back<R>(status, status_cl, epoch, tile, tid, tot, err);
   }
   __syncthreads();
 
@@ -352,6 +360,143 @@ template <typename K, typename V, int RB, int NT, int IPT, int PAY>
 __global__ __launch_bounds__(NT) void k_onesweep(PassArgs<K, V> pa) {
   __shared__ OnesweepSmem<K, V, RB, NT, IPT, PAY> sm;
   onesweep_tile<K, V, RB, NT, IPT, PAY>(pa, blockIdx.x, sm);
+}
+
+// One pass of a long sort (8-bit digits): the same pass over tiles of 6144 to
+// 10240 items.  A tile writes a run of 24 to 40 items per digit on average
+// instead of 8: with 2048-item tiles a pass over 2^26 u32 pairs took 945 us
+// (1.1 TB/s: 32-byte runs), these take 400 (2.7 TB/s; a copy of the same bytes
+// 224).  Keys and payloads go through the same LDS buffer one after the other,
+// so two (64-bit) or three (32-bit) workgroups share a CU.  Items per thread
+// as measured, pairs of 2^26 u32 / 2^24 u64: 12 492 / 178 us, 16 437 / 200, 20
+// 400 / 206 (u64 keys with indexes: 145, 133, 160); 256 and 1024 threads were
+// slower at every tile size.
+constexpr int kBigNT = 512;
+template <typename K, int PAY>
+struct BigTile {
+  static constexpr int IPT = sizeof(K) == 4 ? 20 : PAY == kPayValue ? 12 : 16;
+  static constexpr int N = kBigNT * IPT;
+};
+
+template <typename K, typename V, int PAY>
+struct BigPassSmem {
+  union {
+    K k[BigTile<K, PAY>::N];
+    V v[PAY == kPayNone ? 1 : BigTile<K, PAY>::N];
+  };
+  u32 wc[kBigNT / 64][256];
+  u32 lstart[256];
+  u32 gofs[256];
+  u32 tmp[kBigNT / 64 + 1];
+  u32 trivial;
+};
+
+template <typename K, typename V, int PAY>
+__global__ __launch_bounds__(kBigNT) void k_onesweep_big(PassArgs<K, V> pa) {
+  constexpr int NT = kBigNT, IPT = BigTile<K, PAY>::IPT, WAVES = NT / 64, R = 256;
+  constexpr u32 TILE = BigTile<K, PAY>::N;
+  extern __shared__ __align__(16) unsigned char s_raw[];
+  BigPassSmem<K, V, PAY>& sm = *reinterpret_cast<BigPassSmem<K, V, PAY>*>(s_raw);
+  const u32 tile = blockIdx.x;
+  const u32 tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+  const u32 n = pa.n;
+  const u32 tile0 = tile * TILE;
+  const u32 nv = n - tile0 < TILE ? n - tile0 : TILE;
+  if (tid == 0) sm.trivial = 0;
+  for (int i = tid; i < WAVES * R; i += NT) (&sm.wc[0][0])[i] = 0;
+  const u32 first = w * 64u * IPT + lane;   // wave-striped, as in onesweep_tile
+  K key[IPT];
+  V pay[PAY == kPayNone ? 1 : IPT];
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const u32 i = first + (u32)k * 64u;
+    key[k] = i < nv ? pa.kin[tile0 + i] : K(0);
+  }
+  if (PAY != kPayNone) {
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 i = first + (u32)k * 64u;
+      if (PAY == kPayIndex && pa.vin == nullptr) pay[k] = (V)(tile0 + i);
+      else pay[k] = i < nv ? pa.vin[tile0 + i] : V(0);
+    }
+  }
+  const u32 hcount = tid < (u32)R ? pa.hist_p[tid] : 0u;
+  __syncthreads();
+  if (tid < (u32)R && hcount == n) sm.trivial = 1;
+  u32 htotal;
+  const u32 hexcl = block_exclusive_scan<NT>(hcount, sm.tmp, &htotal);
+  if (sm.trivial) {   // one digit: the stable permutation is the identity
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 i = first + (u32)k * 64u;
+      if (i < nv) {
+        pa.kout[tile0 + i] = key[k];
+        if (PAY != kPayNone) pa.vout[tile0 + i] = pay[k];
+      }
+    }
+    return;
+  }
+  u32 pos[IPT];   // rank among the wave's items of the digit, then the LDS slot
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const bool valid = first + (u32)k * 64u < nv;
+    const u32 d = digit_of<K, 8>(key[k], pa.shift);
+    const u64 m = match_digit<8>(d, wave_ballot(valid));
+    const u32 below = rank_below(m), cnt = (u32)__popcll(m);
+    const u32 base = valid ? sm.wc[w][d] : 0u;
+    pos[k] = base + below;
+    if (valid && below == cnt - 1) sm.wc[w][d] = base + cnt;
+  }
+  __syncthreads();
+  u32 tot = 0;
+  if (tid < (u32)R) {
+#pragma unroll
+    for (int ww = 0; ww < WAVES; ++ww) {
+      const u32 c = sm.wc[ww][tid];
+      sm.wc[ww][tid] = tot;
+      tot += c;
+    }
+    st_agent(&pa.status[(u64)tile * R + tid],
+             pack_status(pa.epoch, tile == 0 ? kFlagPre : kFlagAgg, tot));
+  }
+  u32 dummy;
+  const u32 lstart = block_exclusive_scan<NT>(tid < (u32)R ? tot : 0u, sm.tmp, &dummy);
+  if (tid < (u32)R) sm.lstart[tid] = lstart;
+  __syncthreads();
+  // the tile's keys in digit order in LDS, while other tiles publish
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    if (first + (u32)k * 64u < nv) {
+      const u32 d = digit_of<K, 8>(key[k], pa.shift);
+      pos[k] += sm.lstart[d] + sm.wc[w][d];
+      sm.k[pos[k]] = key[k];
+    }
+  }
+  if (tid < (u32)R)
+    sm.gofs[tid] = hexcl + look_back(pa.status, pa.status_cl, pa.epoch, tile, tid, tot, pa.err) -
+                   lstart;
+  __syncthreads();
+  u32 g[IPT];   // output slot of item tid + r * NT of the digit order
+#pragma unroll
+  for (int r = 0; r < IPT; ++r) {
+    const u32 i = tid + (u32)r * NT;
+    g[r] = 0xFFFFFFFFu;
+    if (i < nv) {
+      const K kk = sm.k[i];
+      g[r] = sm.gofs[digit_of<K, 8>(kk, pa.shift)] + i;
+      if (g[r] < n) pa.kout[g[r]] = kk;   // always true for a consistent histogram
+    }
+  }
+  if (PAY != kPayNone) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k)
+      if (first + (u32)k * 64u < nv) sm.v[pos[k]] = pay[k];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; ++r)
+      if (g[r] < n) pa.vout[g[r]] = sm.v[tid + (u32)r * NT];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1644,6 +1789,24 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
     pa.epoch = epoch;
     pa.err = s.err;
     SortTimer t(s, 1);
+    if constexpr (RB == 8) {
+      if (!local) {
+        constexpr size_t lds = sizeof(BigPassSmem<K, V, PAY>);
+        static bool lds_set = false;
+        if (!lds_set && lds > 65536) {
+          e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_onesweep_big<K, V, PAY>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+          if (e != hipSuccess) return e;
+          lds_set = true;
+        }
+        launch_timed(t.e0, t.e1, k_onesweep_big<K, V, PAY>,
+                     dim3((n + BigTile<K, PAY>::N - 1) / BigTile<K, PAY>::N), dim3(kBigNT), (uint32_t)lds, st, pa);
+        t.end();
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        continue;
+      }
+    }
     launch_timed(t.e0, t.e1, k_onesweep<K, V, RB, kSortNT, kSortIPT, PAY>, dim3(ntiles),
                  dim3(kSortNT), 0, st, pa);
     t.end();
