@@ -19,6 +19,7 @@
 #include "flix_launch.hpp"
 #include "flix_read.hpp"
 #include "flix_read2.hpp"
+#include "flix_small.hpp"
 #include "flix_sort.hpp"
 #include "flix_update.hpp"
 
@@ -78,6 +79,8 @@ struct EpochSlot {
   SortScratch ss;
   int rl = 0, rr = 0, ru = 0;          // which ping-pong buffer holds each sorted list
   bool prepared = false;
+  bool l_direct = false, r_direct = false;   // read lists kept in input order (lk[0], rk[0])
+  bool u_small = false;                      // updates folded in one workgroup
   u64 n_lookup = 0, n_range = 0, n_update = 0;
 };
 
@@ -683,14 +686,11 @@ void launch_update(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, h
   }
 }
 
-// Slice discovery and the bucket kernel over an already sorted update list
-// (the per-call counters must have been reset on the stream before).
 template <typename K>
-int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* svals, u64 n,
-                        const u32* m_dev, hipStream_t st) {
+SliceArgs<K> slice_args(flix_store* s, const K* skeys, const K* svals, u64 n) {
   SliceArgs<K> sa;
   sa.skeys = skeys;
-  sa.svals = insert ? svals : nullptr;
+  sa.svals = svals;
   sa.m = (u32)n;
   sa.mkba = (const K*)s->mkba;
   sa.nb = s->nb;
@@ -701,39 +701,11 @@ int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* sva
   sa.work = s->work;
   sa.rcap = work_region_cap(s->max_batch);
   sa.ctl = s->ctl;
-  // a long slice into a single-node bucket (a dense run of new keys) is merged
-  // by a whole workgroup: the slice kernel lists those items
-  const bool wide = insert && !m_dev &&
-                    (s->cfg.insert_algo == FLIX_INSERT_TL_BULK ||
-                     s->cfg.insert_algo == FLIX_INSERT_ADAPTIVE) &&
-                    n >= wide_min_keys(s->cap);
-  // a long slice or a long chain of a delete goes to the workgroup-wide
-  // delete kernel
-  const bool wide_del = !insert && !m_dev && n >= kWideDelKeys;
-  if (wide || wide_del) {
-    sa.wide_min = wide_min_keys(s->cap);
-    sa.wide_cap = wide_slots(s->max_batch);
-    sa.wide = s->work + work_slots(s->max_batch);
-  }
-  constexpr int SS = SliceCfg<K>::S;
-  u64 grid = ((u64)n + s->nb + sa.share - 1) / sa.share;
-  TmTok t = tm_arm(s, F_PRE);
-  if (m_dev) {
-    if (insert)
-      launch_timed(t.b, t.e, k_slices_counted<K, 256, SS, true>, dim3(grid), dim3(256), 0, st, sa,
-                   m_dev);
-    else
-      launch_timed(t.b, t.e, k_slices_counted<K, 256, SS, false>, dim3(grid), dim3(256), 0, st, sa,
-                   m_dev);
-  } else {
-    if (insert)
-      launch_timed(t.b, t.e, k_slices<K, 256, SS, true>, dim3(grid), dim3(256), 0, st, sa);
-    else
-      launch_timed(t.b, t.e, k_slices<K, 256, SS, false>, dim3(grid), dim3(256), 0, st, sa);
-  }
-  tm_done(s, F_PRE, t);
-  HIP_TRY(hipGetLastError());
+  return sa;
+}
 
+template <typename K>
+UpdArgs<K> upd_args(flix_store* s, bool insert, const K* skeys, const K* svals, u64 n) {
   UpdArgs<K> ua;
   ua.mkba = (const K*)s->mkba;
   ua.skeys = skeys;
@@ -752,8 +724,79 @@ int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* sva
   ua.ctl = s->ctl;
   ua.status = &s->ctl->status;
   ua.occ = s->occl;
-  u32 lds_items = upd_lds_items(s);
-  u64 items = std::min<u64>(n, s->nb);
+  return ua;
+}
+
+// The lane-group apply kernel over at most `items` work items.
+template <typename K>
+int launch_apply(flix_store* s, bool insert, const UpdArgs<K>& ua, u64 items, const u32* m_dev,
+                 hipStream_t st) {
+  const u32 lds_items = upd_lds_items(s);
+  const TmTok t = tm_arm(s, insert ? F_INSERT : F_DELETE);
+  switch (s->gl) {
+    case 16: launch_update<K, 16>(s, insert, ua, items, st, lds_items, m_dev, t); break;
+    case 32: launch_update<K, 32>(s, insert, ua, items, st, lds_items, m_dev, t); break;
+    default: launch_update<K, 64>(s, insert, ua, items, st, lds_items, m_dev, t); break;
+  }
+  tm_done(s, insert ? F_INSERT : F_DELETE, t);
+  HIP_TRY(hipGetLastError());
+  return FLIX_OK;
+}
+
+// Slice discovery and the bucket kernel over an already sorted update list
+// (the per-call counters must have been reset on the stream before).
+template <typename K>
+int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* svals, u64 n,
+                        const u32* m_dev, hipStream_t st, bool small = false) {
+  SliceArgs<K> sa = slice_args<K>(s, skeys, insert ? svals : nullptr, n);
+  // a long slice into a single-node bucket (a dense run of new keys) is merged
+  // by a whole workgroup: the slice kernel lists those items
+  const bool wide = insert && !m_dev &&
+                    (s->cfg.insert_algo == FLIX_INSERT_TL_BULK ||
+                     s->cfg.insert_algo == FLIX_INSERT_ADAPTIVE) &&
+                    n >= wide_min_keys(s->cap);
+  // a long slice or a long chain of a delete goes to the workgroup-wide
+  // delete kernel
+  const bool wide_del = !insert && !m_dev && n >= kWideDelKeys;
+  if (wide || wide_del) {
+    sa.wide_min = wide_min_keys(s->cap);
+    sa.wide_cap = wide_slots(s->max_batch);
+    sa.wide = s->work + work_slots(s->max_batch);
+  }
+  constexpr int SS = SliceCfg<K>::S;
+  u64 grid = ((u64)n + s->nb + sa.share - 1) / sa.share;
+  TmTok t = tm_arm(s, F_PRE);
+  if (small) {
+    const DirTree<K> tree = dir_tree<K>((const K*)s->mkba, (const K*)s->dir, s->nb);
+    const dim3 g((u32)((n + kSliceKeys - 1) / kSliceKeys));
+    sa.parts = insert ? s->ctl->part : nullptr;
+    if (insert)
+      launch_timed(t.b, t.e, k_small_slices<K, true>, g, dim3(256), 0, st, sa, tree);
+    else
+      launch_timed(t.b, t.e, k_small_slices<K, false>, g, dim3(256), 0, st, sa, tree);
+  } else if (m_dev) {
+    if (insert)
+      launch_timed(t.b, t.e, k_slices_counted<K, 256, SS, true>, dim3(grid), dim3(256), 0, st, sa,
+                   m_dev);
+    else
+      launch_timed(t.b, t.e, k_slices_counted<K, 256, SS, false>, dim3(grid), dim3(256), 0, st, sa,
+                   m_dev);
+  } else {
+    if (insert)
+      launch_timed(t.b, t.e, k_slices<K, 256, SS, true>, dim3(grid), dim3(256), 0, st, sa);
+    else
+      launch_timed(t.b, t.e, k_slices<K, 256, SS, false>, dim3(grid), dim3(256), 0, st, sa);
+  }
+  tm_done(s, F_PRE, t);
+  HIP_TRY(hipGetLastError());
+
+  UpdArgs<K> ua = upd_args<K>(s, insert, skeys, svals, n);
+  if (small) {
+    ua.flat = true;
+    ua.parts = s->ctl->part;
+    ua.nparts = insert ? (u32)((n + kSliceKeys - 1) / kSliceKeys) : 0u;
+  }
+  const u64 items = small ? n : std::min<u64>(n, s->nb);
   // insert kernel choice: the single-lane kernel takes the items its selector
   // names, the lane-group kernel the complement
   u32 algo = (insert && !m_dev) ? s->cfg.insert_algo : (u32)FLIX_INSERT_TL_BULK;
@@ -787,14 +830,8 @@ int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* sva
     ua.sel = algo == FLIX_INSERT_ST_TL_MIXED ? kSelRoundL : kSelLong;
     ua.st_max = us.st_max;
   }
-  t = tm_arm(s, insert ? F_INSERT : F_DELETE);
-  switch (s->gl) {
-    case 16: launch_update<K, 16>(s, insert, ua, items, st, lds_items, m_dev, t); break;
-    case 32: launch_update<K, 32>(s, insert, ua, items, st, lds_items, m_dev, t); break;
-    default: launch_update<K, 64>(s, insert, ua, items, st, lds_items, m_dev, t); break;
-  }
-  tm_done(s, insert ? F_INSERT : F_DELETE, t);
-  HIP_TRY(hipGetLastError());
+  const int rc = launch_apply<K>(s, insert, ua, items, m_dev, st);
+  if (rc) return rc;
   if (wide_del) {
     ua.wide_min = sa.wide_min;
     ua.wide_cap = sa.wide_cap;
@@ -813,19 +850,7 @@ int update_apply_sorted(flix_store* s, bool insert, const K* skeys, const K* sva
 template <typename K>
 int update_slices_only(flix_store* s, const K* skeys, const K* svals, u64 n, const u32* m_dev,
                        hipStream_t st) {
-  SliceArgs<K> sa;
-  sa.skeys = skeys;
-  sa.svals = svals;
-  sa.m = (u32)n;
-  sa.mkba = (const K*)s->mkba;
-  sa.nb = s->nb;
-  sa.hdr = s->hdr;
-  sa.bnodes = s->bnodes;
-  sa.cap = s->cap;
-  sa.share = SliceCfg<K>::S;
-  sa.work = s->work;
-  sa.rcap = work_region_cap(s->max_batch);
-  sa.ctl = s->ctl;
+  SliceArgs<K> sa = slice_args<K>(s, skeys, svals, n);
   constexpr int SS = SliceCfg<K>::S;
   const u64 grid = ((u64)n + s->nb + sa.share - 1) / sa.share;
   hipLaunchKernelGGL((k_slices_counted<K, 256, SS, true>), dim3(grid), dim3(256), 0, st, sa, m_dev);
@@ -836,6 +861,20 @@ int update_slices_only(flix_store* s, const K* skeys, const K* svals, u64 n, con
 template <typename K>
 int update_batch(flix_store* s, bool insert, const void* keys, const void* vals, u64 n,
                  hipStream_t st) {
+  // short batches; the single-lane insert kernels choose by the work list of
+  // the general path
+  if (n <= kSmallMax &&
+      (!insert || s->cfg.insert_algo == FLIX_INSERT_TL_BULK ||
+       (s->cfg.insert_algo == FLIX_INSERT_ADAPTIVE && adaptive_st_max(s->cap) == 0))) {
+    const TmTok t = tm_arm(s, F_LOCAL);
+    launch_timed(t.b, t.e, k_rank_sort<K>, dim3((u32)((n + kRankKeys - 1) / kRankKeys)), dim3(256),
+                 0, st, (const K*)keys, (const K*)(insert ? vals : nullptr), (u32)n, (K*)s->bk[0],
+                 (K*)s->bp[0], s->ctl);
+    tm_done(s, F_LOCAL, t);
+    HIP_TRY(hipGetLastError());
+    return update_apply_sorted<K>(s, insert, (const K*)s->bk[0],
+                                  insert ? (const K*)s->bp[0] : nullptr, n, nullptr, st, true);
+  }
   hipLaunchKernelGGL(k_reset_call, dim3(1), dim3(kWorkRegions), 0, st, s->ctl, 1u);
   int r;
   int rc = sort_batch<K>(s, keys, vals, n, insert ? kPayValue : kPayNone, st, &r);
@@ -919,14 +958,34 @@ int ensure_slots(flix_store* s) {
 template <typename K, int RB>
 int epoch_prepare_rb(EpochSlot* es, const flix_epoch* e, hipStream_t st) {
   hipError_t err = hipSuccess;
-  if (e->n_lookup)
+  // read lists that are answered in input order are only kept for the apply
+  es->l_direct = e->n_lookup <= kDirectMax;
+  es->r_direct = e->n_range <= kDirectMax;
+  const u32 cl = es->l_direct ? (u32)e->n_lookup : 0u, cr = es->r_direct ? (u32)e->n_range : 0u;
+  if (cl + cr)
+    hipLaunchKernelGGL((k_epoch_copy<K>), dim3(std::min<u32>((cl + cr + 255) / 256, 2048)),
+                       dim3(256), 0, st, (const K*)e->d_lookup_keys, cl, (K*)es->lk[0],
+                       (const K*)e->d_range_lo, cr, (K*)es->rk[0]);
+  if (!es->l_direct)
     err = radix_sort<K, u32, RB, kPayIndex>((const K*)e->d_lookup_keys, nullptr, (K*)es->lk[0],
                                             (u32*)es->lp[0], (K*)es->lk[1], (u32*)es->lp[1],
                                             (u32)e->n_lookup, es->ss, st, &es->rl);
-  if (err == hipSuccess && e->n_range)
+  if (err == hipSuccess && !es->r_direct)
     err = radix_sort<K, u32, RB, kPayIndex>((const K*)e->d_range_lo, nullptr, (K*)es->rk[0],
                                             (u32*)es->rp[0], (K*)es->rk[1], (u32*)es->rp[1],
                                             (u32)e->n_range, es->ss, st, &es->rr);
+  es->u_small = e->n_update <= kSmallMax;
+  if (err == hipSuccess && e->n_update && es->u_small) {
+    const u32 n = (u32)e->n_update;
+    hipLaunchKernelGGL((k_rank_sort<K>), dim3((n + kRankKeys - 1) / kRankKeys), dim3(256), 0, st,
+                       (const K*)e->d_update_keys, (const K*)e->d_update_vals, n, (K*)es->uk[0],
+                       (K*)es->up[0], (Ctl*)nullptr);
+    hipLaunchKernelGGL((k_fold_small<K>), dim3(1), dim3(1024), 0, st, (const K*)es->uk[0],
+                       (const K*)es->up[0], n, (K*)es->ins_k, (K*)es->ins_v, (K*)es->del_k,
+                       es->counts);
+    HIP_TRY(hipGetLastError());
+    return FLIX_OK;
+  }
   if (err == hipSuccess && e->n_update)
     err = radix_sort<K, K, RB, kPayValue>((const K*)e->d_update_keys, (const K*)e->d_update_vals,
                                           (K*)es->uk[0], (K*)es->up[0], (K*)es->uk[1],
@@ -952,15 +1011,53 @@ int epoch_prepare_rb(EpochSlot* es, const flix_epoch* e, hipStream_t st) {
 template <typename K>
 int epoch_apply_t(flix_store* s, EpochSlot* es, const flix_epoch* e, hipStream_t st) {
   int rc;
-  if (e->n_lookup &&
-      (rc = read_apply_sorted<K>(s, kOpLookup, (const K*)es->lk[es->rl], (const u32*)es->lp[es->rl],
-                                 e->n_lookup, nullptr, e->d_lookup_vals, nullptr, nullptr, 0, st)))
-    return rc;
-  if (e->n_range &&
-      (rc = read_apply_sorted<K>(s, kOpRange, (const K*)es->rk[es->rr], (const u32*)es->rp[es->rr],
-                                 e->n_range, e->d_range_keys, e->d_range_vals, e->d_range_hi,
-                                 e->d_range_counts, e->range_max, st)))
-    return rc;
+  if (e->n_lookup) {
+    rc = es->l_direct
+             ? read_direct<K>(s, kOpLookup, (const K*)es->lk[0], e->n_lookup, nullptr,
+                              e->d_lookup_vals, nullptr, nullptr, 0, st)
+             : read_apply_sorted<K>(s, kOpLookup, (const K*)es->lk[es->rl],
+                                    (const u32*)es->lp[es->rl], e->n_lookup, nullptr,
+                                    e->d_lookup_vals, nullptr, nullptr, 0, st);
+    if (rc) return rc;
+  }
+  if (e->n_range) {
+    rc = es->r_direct
+             ? read_direct<K>(s, kOpRange, (const K*)es->rk[0], e->n_range, e->d_range_keys,
+                              e->d_range_vals, e->d_range_hi, e->d_range_counts, e->range_max, st)
+             : read_apply_sorted<K>(s, kOpRange, (const K*)es->rk[es->rr],
+                                    (const u32*)es->rp[es->rr], e->n_range, e->d_range_keys,
+                                    e->d_range_vals, e->d_range_hi, e->d_range_counts,
+                                    e->range_max, st);
+    if (rc) return rc;
+  }
+  if (e->n_update && es->u_small) {
+    // both lists' work items and the upserts' node bound in one launch, on the
+    // store before the deletes; a rejected epoch changes nothing
+    const u64 n = e->n_update;
+    const u32 units = (u32)((n + kSliceKeys - 1) / kSliceKeys);
+    SliceArgs<K> si = slice_args<K>(s, (const K*)es->ins_k, (const K*)es->ins_v, n);
+    SliceArgs<K> sd = slice_args<K>(s, (const K*)es->del_k, nullptr, n);
+    si.work = s->work + s->max_batch;   // (the list has two max_batch items)
+    si.parts = s->ctl->part;
+    sd.snapshot = false;
+    const TmTok t = tm_arm(s, F_PRE);
+    launch_timed(t.b, t.e, k_epoch_slices<K>, dim3(2 * units), dim3(256), 0, st, si, sd,
+                 dir_tree<K>((const K*)s->mkba, (const K*)s->dir, s->nb), (const u32*)es->counts,
+                 units);
+    tm_done(s, F_PRE, t);
+    HIP_TRY(hipGetLastError());
+    UpdArgs<K> ud = upd_args<K>(s, false, (const K*)es->del_k, nullptr, n);
+    ud.flat = true;
+    ud.parts = s->ctl->part;
+    ud.nparts = units;
+    if ((rc = launch_apply<K>(s, false, ud, n, es->counts + 1, st))) return rc;
+    UpdArgs<K> ui = upd_args<K>(s, true, (const K*)es->ins_k, (const K*)es->ins_v, n);
+    ui.flat = true;
+    ui.work = s->work + s->max_batch;
+    ui.parts = s->ctl->part;
+    ui.nparts = units;
+    return launch_apply<K>(s, true, ui, n, es->counts, st);
+  }
   if (e->n_update) {
     // the folded lists hold distinct keys, so deletes and upserts commute;
     // deletes go first and return nodes to the free list.  The upserts' node

@@ -31,6 +31,12 @@ static_assert(sizeof(NodeHdr) == 16 && offsetof(NodeHdr, size) == 8 && offsetof(
 // executed one at a time past the L2s).
 constexpr u32 kWorkRegions = 64;
 
+// Parts of the node bound of a short insert list, one per slice unit
+// (flix_small.hpp): the nodes in the low bits, kPartBad when the unit holds a
+// reserved value.
+constexpr u32 kSmallParts = 72;
+constexpr u64 kPartBad = 1ull << 63;
+
 // Device control block: counters and status words owned by one store.
 struct alignas(128) Ctl {
   u32 free_top;        // number of node ids on the free stack
@@ -47,6 +53,7 @@ struct alignas(128) Ctl {
   // per region: [0] items claimed, [1] first claim that did not fit (all
   // ones: none), so the region holds min([0], [1]) items
   alignas(128) u32 wreg[kWorkRegions][32];
+  u64 part[kSmallParts];
 };
 
 // Work-list slots of a store whose batches hold at most max_batch keys:

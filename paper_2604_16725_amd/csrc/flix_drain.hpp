@@ -24,6 +24,7 @@
 
 #include "flix_device.hpp"
 #include "flix_direct.hpp"
+#include "flix_small.hpp"
 #include "flix_sort.hpp"
 #include "flix_update.hpp"
 
@@ -168,6 +169,8 @@ struct DrainSmemSize {
     m = m > pass_val ? m : pass_val;
     m = m > pass_none ? m : pass_none;
     m = m > slices ? m : slices;
+    m = m > sizeof(RankSmem<K>) ? m : sizeof(RankSmem<K>);
+    m = m > sizeof(SliceUnitSmem) ? m : sizeof(SliceUnitSmem);
     return m;
   }
 };
@@ -360,6 +363,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if ((threadIdx.x & 63u) == 0) atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
       }
+      continue;
+    }
+    if (n <= kSmallMax) {
+      // short update: sort by counting, work items, apply
+      const bool ins = d.op == kOpInsert;
+      for (u32 u = blk; u * kRankKeys < n; u += G) {
+        __syncthreads();
+        rank_unit<K>((const K*)d.keys, ins ? (const K*)d.aux : nullptr, n, u, a.bk[0],
+                     (K*)a.bp[0], *reinterpret_cast<RankSmem<K>*>(smem));
+      }
+      if (grid_sync(dc, G)) return;
+      SliceArgs<K> sa;
+      sa.skeys = a.bk[0];
+      sa.svals = ins ? (const K*)a.bp[0] : nullptr;
+      sa.m = n;
+      sa.mkba = mkba;
+      sa.nb = L.nb;
+      sa.hdr = L.hdr;
+      sa.bnodes = L.bnodes;
+      sa.cap = a.cap;
+      sa.share = 0;
+      sa.work = a.work;
+      sa.rcap = 0;
+      sa.ctl = a.ctl;
+      sa.parts = a.ctl->part;
+      const u32 units = (n + kSliceKeys - 1) / kSliceKeys;
+      SliceUnitSmem& su = *reinterpret_cast<SliceUnitSmem*>(smem);
+      for (u32 u = blk; u < units; u += G) {
+        if (threadIdx.x == 0) su.bad = 0;
+        __syncthreads();
+        if (ins) slice_unit<K, true>(sa, tree, s_top, u, su);
+        else slice_unit<K, false>(sa, tree, s_top, u, su);
+      }
+      if (grid_sync(dc, G)) return;
+      UpdArgs<K> ua;
+      ua.mkba = mkba;
+      ua.skeys = a.bk[0];
+      ua.svals = sa.svals;
+      ua.m = n;
+      ua.hdr = L.hdr;
+      ua.nkeys = nkeys;
+      ua.nvals = nvals;
+      ua.bnodes = L.bnodes;
+      ua.free_ids = L.free_ids;
+      ua.cap = a.cap;
+      ua.chunk = a.chunk;
+      ua.pool = L.pool;
+      ua.work = a.work;
+      ua.rcap = 0;
+      ua.ctl = a.ctl;
+      ua.status = &a.ctl->status;
+      ua.occ = L.occ;
+      ua.flat = true;
+      ua.parts = a.ctl->part;
+      ua.nparts = ins ? units : 0u;
+      if (ins) insert_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
+      else delete_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
+      if (grid_sync(dc, G)) return;
+      pend = bi + 1;
+      if (blk == 0 && threadIdx.x == 0 && a.tstamp)
+        atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
       continue;
     }
     const u32 slot = nz & 1u;

@@ -60,6 +60,8 @@ struct SliceArgs {
                     // listed for the workgroup-wide insert kernel
   u32 wide_cap = 0;
   WorkItem* wide = nullptr;   // [wide_cap]
+  u64* parts = nullptr;       // short lists: where the units leave their bounds
+  bool snapshot = true;       // short lists: unit 0 records the free-list height
 };
 
 template <typename K, int S, int NT>
@@ -422,7 +424,36 @@ struct UpdArgs {
                       // their slice belong to the workgroup-wide insert kernel
   u32 wide_cap = 0;
   const WorkItem* wide = nullptr;   // those items, listed by the slice kernel
+  bool flat = false;  // short list: item i at position i (empty ones are no
+                      // bucket's first key), headers not yet read
+  u32 nparts = 0;     // > 0: the call's node bound is the sum of these parts
+  const u64* parts = nullptr;
 };
+
+// Whether the call as a whole is rejected, and the error to report (0: a
+// batch rejected before).  Every workgroup decides alike: the words it reads
+// are not written while the apply kernels run.  All lanes of a wave call.
+template <typename K>
+__device__ __forceinline__ bool call_rejected(const UpdArgs<K>& a, u32* err) {
+  const Ctl* ctl = a.ctl;
+  u64 need = ctl->need;
+  u32 e = ctl->call_err;
+  if (a.nparts) {
+    u64 v = 0;
+    bool bad = false;
+    for (u32 i = threadIdx.x & 63u; i < a.nparts; i += 64) {
+      const u64 w = a.parts[i];
+      bad = bad || (w & kPartBad) != 0;
+      v += w & ~kPartBad;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor((unsigned long long)v, o, 64);
+    need = v;
+    if (wave_ballot(bad)) e = kErrInval;
+  }
+  *err = e;
+  return e != 0 || need > ctl->free_snapshot || ctl->call_abort != 0;
+}
 
 // Work items of the workgroup-wide insert kernel (k_insert_wide).
 __device__ __forceinline__ bool is_wide(u32 wide_min, const WorkItem& w) {
@@ -485,17 +516,13 @@ __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   K* bv = gv + a.cap;
   if (threadIdx.x == 0) s_added = 0;
   __syncthreads();
-  const Ctl* ctl = a.ctl;
-  bool abort_all = ctl->call_err != 0 || ctl->need > ctl->free_snapshot || ctl->call_abort != 0;
-  if (abort_all) {
-    if (blk == 0 && threadIdx.x == 0 && ctl->call_err == 0)
-      atomicCAS(a.status, 0u, kErrNomem);
-    if (blk == 0 && threadIdx.x == 0 && ctl->call_err != 0)
-      atomicCAS(a.status, 0u, ctl->call_err);
+  u32 call_err;
+  if (call_rejected(a, &call_err)) {
+    if (blk == 0 && threadIdx.x == 0) atomicCAS(a.status, 0u, call_err != 0 ? call_err : kErrNomem);
     __syncthreads();
     return;
   }
-  const u32 nitems = load_work_map(ctl, sh.pre);
+  const u32 nitems = a.flat ? a.m : load_work_map(a.ctl, sh.pre);
   // a call-level choice that gives this kernel nothing ends it here (uniform)
   if ((a.sel == kSelRound || a.sel == kSelRoundL) && !sel_takes(a.sel, a.st_max, 0u, a.m, nitems))
     return;
@@ -505,13 +532,18 @@ __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   u32 it = blk * GPB + gid;
   WorkItem wnext;
   WorkCursor cur;
-  cur.seek(sh.pre, it);
-  if (it < nitems) wnext = a.work[cur.slot(it, a.rcap)];
+  if (!a.flat) cur.seek(sh.pre, it);
+  if (it < nitems) wnext = a.work[a.flat ? it : cur.slot(it, a.rcap)];
   for (; it < nitems; it += stride) {
-    const WorkItem w = wnext;
+    WorkItem w = wnext;
     if (it + stride < nitems) {   // prefetch
-      cur.move(sh.pre, it + stride);
-      wnext = a.work[cur.slot(it + stride, a.rcap)];
+      if (!a.flat) cur.move(sh.pre, it + stride);
+      wnext = a.work[a.flat ? it + stride : cur.slot(it + stride, a.rcap)];
+    }
+    if (a.flat) {
+      if (w.s == w.e) continue;   // no slice begins at this key
+      const u64 hw = *reinterpret_cast<const u64*>(&a.hdr[w.b].size);
+      w.head = (u32)(hw >> 32) == kNil ? ((u32)hw | kSingleNode) : (u32)hw;
     }
     if (!sel_takes(a.sel, a.st_max, w.e - w.s, a.m, nitems) || is_wide(a.wide_min, w)) continue;
     u32 X = w.b;
@@ -1220,8 +1252,8 @@ template <typename K, int NT>
 __global__ __launch_bounds__(NT) void k_insert_wide(UpdArgs<K> a) {
   __shared__ WideLds<K> L;
   const Ctl* ctl = a.ctl;
-  if (ctl->call_err != 0 || ctl->need > ctl->free_snapshot || ctl->call_abort != 0)
-    return;   // the other kernels report it
+  u32 call_err;
+  if (call_rejected(a, &call_err)) return;   // the other kernels report it
   const u32 n = ctl->wide_n < a.wide_cap ? ctl->wide_n : a.wide_cap;
   unsigned long long added = 0;
   for (u32 i = blockIdx.x; i < n; i += gridDim.x) {
@@ -1254,20 +1286,27 @@ __device__ void delete_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   if (threadIdx.x == 0) s_removed = 0;
   __syncthreads();
   if (a.ctl->call_abort != 0) return;   // an epoch rejected as a whole (uniform)
-  const u32 nitems = load_work_map(a.ctl, sh.pre);
+  u32 call_err;
+  if (a.nparts && call_rejected(a, &call_err)) return;   // (a short epoch: its upserts' bound)
+  const u32 nitems = a.flat ? a.m : load_work_map(a.ctl, sh.pre);
   const u32 f = a.cap / 2;
   u64 removed = 0;
   const u32 stride = nblk * GPB;
   u32 it = blk * GPB + gid;
   WorkItem wnext;
   WorkCursor cur;
-  cur.seek(sh.pre, it);
-  if (it < nitems) wnext = a.work[cur.slot(it, a.rcap)];
+  if (!a.flat) cur.seek(sh.pre, it);
+  if (it < nitems) wnext = a.work[a.flat ? it : cur.slot(it, a.rcap)];
   for (; it < nitems; it += stride) {
-    const WorkItem w = wnext;
+    WorkItem w = wnext;
     if (it + stride < nitems) {   // prefetch
-      cur.move(sh.pre, it + stride);
-      wnext = a.work[cur.slot(it + stride, a.rcap)];
+      if (!a.flat) cur.move(sh.pre, it + stride);
+      wnext = a.work[a.flat ? it + stride : cur.slot(it + stride, a.rcap)];
+    }
+    if (a.flat) {
+      if (w.s == w.e) continue;   // no slice begins at this key
+      const u64 hw = *reinterpret_cast<const u64*>(&a.hdr[w.b].size);
+      w.head = (u32)(hw >> 32) == kNil ? ((u32)hw | kSingleNode) : (u32)hw;
     }
     if (w.head & kWideItem) continue;   // k_delete_wide takes it
     // predecessor state (P), kept in registers; P == kNil before the head
