@@ -76,11 +76,11 @@ typedef struct {
   uint32_t reserved;        /* must be 0 */
 } flix_config;
 
-/* Read-batch pipelines (same results).  SORTED, the default, answers batches of
- * up to 2^23 queries in input order, one lane per query, by a search of the
- * maxBucket directory; longer batches go through Section 3.3 / 4.1: the whole
- * batch is sorted on the device (onesweep), then merge-path shares let every
- * bucket resolve its slice.  GROUPS splits the batch by groups of consecutive
+/* Read-batch pipelines (same results).  SORTED, the default, answers all but
+ * long batches (above 3 * 2^21 32-bit point reads, 2^24 others) in input order,
+ * one lane per query, by a search of the maxBucket directory; those go through
+ * Section 3.3 / 4.1: the whole batch is sorted on the device (onesweep), then
+ * merge-path shares let every bucket resolve its slice.  GROUPS splits the batch by groups of consecutive
  * buckets in one pass and sorts each group's items in LDS inside the resolving
  * workgroup (no device-wide sort). */
 #define FLIX_READ_SORTED 0

@@ -530,13 +530,17 @@ int read_batch_groups(flix_store* s, int op, const K* keys, u64 n, void* out_k, 
 }
 
 // Read batches up to this length are answered in input order.  Sorting a batch
-// pays nowhere below it: 2^26 u32 keys, lookups, direct against sorted: 2^17
-// 17 against 42 us, 2^20 94 against 109, 2^22 342 against 488, 2^23 669
-// against 728; on stores that fit the caches by more (2^20 keys, 2^23
-// lookups: 307 against 1045), on skewed batches (2^20 Zipf 64 against 351)
-// and on ranges with many results (2^16 ranges of 256 keys: 107 against 236)
-// too.  At 12.3 M lookups the two meet (1.00 against 1.02 ms).
-constexpr u64 kDirectMax = 1ull << 23;
+// first pays for long batches of 32-bit point reads (four passes; eight for
+// 64-bit keys), spread over a store that does not fit the caches; the others were
+// faster unsorted at every length measured, up to 12.3 M.  2^26 u32
+// keys, direct against sorted, us: lookups of 2^20 82, 121; 2^22 291, 322; 2^23
+// 572, 522; 12.3 M 845, 697; successors of 2^22 383, 375; 2^23 750, 637.  2^25
+// u64 keys, lookups of 2^23 590, 824; 12.3 M 860, 1246.  Ranges of 16 keys, 2^22
+// 778, 3520.  2^22 Zipf lookups 219, 400; on 2^20 keys 143, 408.
+template <typename K>
+constexpr u64 direct_max(int op) {
+  return sizeof(K) == 8 || op == kOpRange ? 1ull << 24 : 3ull << 21;
+}
 
 // Read batch answered in input order (flix_direct.hpp).
 template <typename K>
@@ -574,7 +578,7 @@ int read_batch(flix_store* s, int op, const void* keys, u64 n, void* out_k, void
                const void* hi, u32* counts, u32 maxpq, hipStream_t st) {
   if (s->cfg.read_path == FLIX_READ_GROUPS && s->grp_ok && n <= (u64)kGroupTilesMax * kPartTile)
     return read_batch_groups<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
-  if (n <= kDirectMax)
+  if (n <= direct_max<K>(op))
     return read_direct<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
   int r;
   int rc = sort_batch<K>(s, keys, nullptr, n, kPayIndex, st, &r);
@@ -945,8 +949,8 @@ template <typename K, int RB>
 int epoch_prepare_rb(EpochSlot* es, const flix_epoch* e, hipStream_t st) {
   hipError_t err = hipSuccess;
   // read lists that are answered in input order are only kept for the apply
-  es->l_direct = e->n_lookup <= kDirectMax;
-  es->r_direct = e->n_range <= kDirectMax;
+  es->l_direct = e->n_lookup <= direct_max<K>(kOpLookup);
+  es->r_direct = e->n_range <= direct_max<K>(kOpRange);
   const u32 cl = es->l_direct ? (u32)e->n_lookup : 0u, cr = es->r_direct ? (u32)e->n_range : 0u;
   if (cl + cr)
     hipLaunchKernelGGL((k_epoch_copy<K>), dim3(std::min<u32>((cl + cr + 255) / 256, 2048)),

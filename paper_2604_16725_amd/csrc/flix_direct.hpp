@@ -14,10 +14,13 @@
 // What bounds it: on a store that fits the L2s (2^18 keys) 2^20 lookups take
 // 35 us, about half of it the address unit (the lane-by-lane form of the
 // 64-byte block reads, 16 accesses per query instead of 7, took 69 us); on
-// 2^26 keys 94 us, at 4.5 L2 misses of 64 bytes per query (header, two or
-// three of the node's blocks, value, part of maxBucket: 50 G random
-// 64-byte requests/s).  Against the sorted form before: lookups of 2^20 keys
-// 109 -> 94 us, Zipf 351 -> 64, 256 lookups 22 -> 10 (one launch), 2^20 ranges
+// 2^26 keys 82 us, at nearly 4 L2 misses of 64 bytes per query (header, one or
+// two of the node's blocks, value, part of maxBucket: 50 G random 64-byte
+// requests/s).  The first block looked at is the one where the query lies
+// between the ends of its bucket (bisecting by the last keys of the blocks read
+// one more: lookups of 2^20 95 us, 108 on 2^25 u64 keys, now 83, and with 256
+// slots per node, now 74).  Against the sorted form before: lookups of 2^20 keys
+// 109 -> 82 us, Zipf 351 -> 60, 256 lookups 22 -> 10 (one launch), 2^20 ranges
 // of 16 keys each 918 -> 223 us, 2^16 of 256 keys 236 -> 107.
 #pragma once
 
@@ -287,23 +290,23 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
   u32 b[Q];
   find_buckets<K, Q>(t, s_top, a.nb, x, b);
 
-  // header (size and next) and the key at slot cap/4 - 1, the middle of a
-  // bulk-loaded node, of the buckets' head nodes
-  u64 w[Q];
-  K mid[Q];
+  // headers of the buckets' head nodes, and the key the bucket begins after
+  NodeHdr h0[Q];
+  K from[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    w[q] = *reinterpret_cast<const u64*>(&a.hdr[b[q]].size);
-    mid[q] = a.nkeys[(u64)b[q] * a.cap + (a.cap / 4 - 1)];
+    h0[q] = a.hdr[b[q]];
+    from[q] = b[q] ? a.mkba[b[q] - 1] : K(0);
   }
-  u32 node[Q], size[Q], next[Q], lo[Q], hb[Q];
-  bool single[Q], bad[Q];
-  const u32 qs = a.cap / 4;
+  // 64-byte blocks [lo, hb] of the node that may hold the bound, and the one to
+  // look at first: where the query lies between the ends of the bucket
+  u32 node[Q], size[Q], next[Q], lo[Q], hb[Q], m[Q];
+  bool single[Q], bad[Q], open[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     node[q] = b[q];
-    size[q] = (u32)w[q];
-    next[q] = (u32)(w[q] >> 32);
+    size[q] = h0[q].size;
+    next[q] = h0[q].next;
     single[q] = next[q] == kNil;
     if (!single[q] && OP != kOpPredecessor) {
       NodeHdr h;
@@ -319,46 +322,50 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
       size[q] = 0;
       next[q] = kNil;
     }
-    // 64-byte blocks [lo, hb] of the node that may hold the bound
     lo[q] = 0;
     hb[q] = size[q] ? (size[q] - 1) / B : 0u;
-    if (single[q] && qs >= B && size[q] >= qs) {
-      if (UPPER ? mid[q] <= x[q] : mid[q] < x[q]) lo[q] = qs / B < hb[q] ? qs / B : hb[q];
-      else hb[q] = qs / B - 1;
-    }
+    const K width = (K)h0[q].fence - from[q];
+    const float part = (float)(K)(x[q] - from[q]) * __builtin_amdgcn_rcpf((float)width);
+    const u32 g = single[q] ? (u32)(fminf(part, 1.0f) * (float)size[q]) / B : hb[q] / 2;
+    m[q] = g < hb[q] ? g : hb[q];
+    open[q] = true;
   }
-  // the block: each step reads the last key of the middle one
-  bool open = true;
-  while (open) {
-    K k[Q];
-    open = false;
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (lo[q] < hb[q])
-        k[q] = a.nkeys[(u64)node[q] * a.cap + ((lo[q] + hb[q]) >> 1) * B + (B - 1)];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      if (lo[q] < hb[q]) {
-        const u32 m = (lo[q] + hb[q]) >> 1;
-        if (UPPER ? k[q] <= x[q] : k[q] < x[q]) lo[q] = m + 1; else hb[q] = m;
-      }
-      open = open || lo[q] < hb[q];
-    }
-  }
-  // the keys of the block below x (lt) and not above x or hi (le)
+  // The keys of block m below x (lt) and not above x or hi (le).  When the bound
+  // is not in it the neighbour follows, then the middle of what is left.  (A
+  // bound at the start of a block may be left at the end of the one before.)
   u32 lt[Q], le[Q], valid[Q];
   u64 at[Q];
-  {
-    QuadBlock<K, (int)B> blk[Q];
+  for (u32 step = 0;; ++step) {
+    bool any = false;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      at[q] = (u64)node[q] * a.cap + lo[q] * B;
-      valid[q] = size[q] - lo[q] * B < B ? size[q] - lo[q] * B : B;
-      quad_fetch<K, (int)B>(a.nkeys + at[q], a.cap, blk[q]);
+      if (quad_sum(open[q] ? 1u : 0u) != 0) {   // whole quads
+        QuadBlock<K, (int)B> blk;
+        u32 c, d;
+        at[q] = (u64)node[q] * a.cap + m[q] * B;
+        valid[q] = size[q] - m[q] * B < B ? size[q] - m[q] * B : B;
+        quad_fetch<K, (int)B>(a.nkeys + at[q], a.cap, blk);
+        quad_count<K, (int)B, true, false>(blk, valid[q], x[q], hi[q], &c, &d);
+        lt[q] = c;
+        le[q] = d;
+        if (open[q]) {
+          const u32 in = UPPER ? d : c;
+          open[q] = false;
+          if (OP == kOpLookup && d > c) {
+          } else if (in == valid[q] && m[q] < hb[q]) {
+            lo[q] = m[q] + 1;
+            m[q] = step == 0 ? lo[q] : (lo[q] + hb[q]) / 2;
+            open[q] = true;
+          } else if (in == 0 && m[q] > lo[q]) {
+            hb[q] = m[q] - 1;
+            m[q] = step == 0 ? hb[q] : (lo[q] + hb[q]) / 2;
+            open[q] = true;
+          }
+        }
+      }
+      any = any || open[q];
     }
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      quad_count<K, (int)B, true, false>(blk[q], valid[q], x[q], hi[q], &lt[q], &le[q]);
+    if (!wave_ballot(any)) break;
   }
 
   if constexpr (OP == kOpRange) {
@@ -367,8 +374,8 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
     for (int q = 0; q < Q; ++q) {
       bool more = live[q] && !bad[q] && x[q] <= hi[q];
       const u64 ob = (u64)j[q] * a.maxpq;
-      u32 cnt = 0, p = lo[q] * B + lt[q];
-      u32 ub = lo[q] * B + le[q];
+      u32 cnt = 0, p = m[q] * B + lt[q];
+      u32 ub = m[q] * B + le[q];
       NodeHdr h;
       h.fence = 0;
       h.size = size[q];
@@ -409,7 +416,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
         slot[q] = le[q] > lt[q] ? at[q] + lt[q] : ~0ull;
       } else if (OP == kOpSuccessor) {
         slot[q] = at[q] + lt[q];
-        if (lt[q] >= valid[q] && !bad[q]) {   // past the node: the next one that holds a key
+        if (m[q] * B + lt[q] >= size[q] && !bad[q]) {   // past the node: the next one that holds a key
           NodeHdr h, g;
           h.next = next[q];
           const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
@@ -420,7 +427,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
         slot[q] = at[q] + le[q] - 1;
         // nothing up to x in the block: the key before it, in the chain or in
         // an earlier bucket (a block after a node's first follows a key <= x)
-        if (!bad[q] && (le[q] == 0 || !single[q]) && !(lo[q] > 0 && single[q]))
+        if (!bad[q] && (le[q] == 0 || !single[q]) && !(m[q] > 0 && single[q]))
           slot[q] = predecessor_slot<K>(a.hdr, a.nkeys, occ, a.pool, a.cap, b[q], x[q], &bad[q]);
       }
       if (bad[q]) slot[q] = ~0ull;

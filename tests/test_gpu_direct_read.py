@@ -92,3 +92,54 @@ def test_range_lengths(kb, m, span, maxpq):
     log(f"ranges kb={kb} m={m} span={span} maxpq={maxpq}")
     check_reads(s, o, kb, lo, maxpq=maxpq, lo=lo, hi=hi, where="ranges")
     s.close()
+
+
+@pytest.mark.parametrize("kb,cap,fill", [(32, 64, 64), (32, 256, 256), (32, 32, 31), (64, 64, 63),
+                                         (64, 256, 255), (64, 128, 128)])
+def test_keys_far_from_where_they_are_looked_for(kb, cap, fill):
+    """Nodes whose keys crowd at either end, lie in clumps or are spread evenly:
+    the first block looked at is right, next to the right one or far off."""
+    rng = np.random.default_rng(cap + fill + kb)
+    half = np.uint64(1) << np.uint64(kb - 10)
+    i = np.arange(fill, dtype=np.uint64)
+    bits = np.uint64(kb - 12)
+    grow = np.unique(np.concatenate([np.uint64(1) << (i % bits), i]))[:fill]
+    shapes = [i, half - i - np.uint64(1), grow, half - np.uint64(1) - grow[::-1],
+              i * (half // np.uint64(fill)), (i % np.uint64(3)) * (half // np.uint64(4)) + i]
+    k = np.unique(np.concatenate([np.uint64(1 + b) * half + np.uint64(5) + shapes[b % 6]
+                                  for b in range(300)])).astype(ktype(kb))
+    v = w.values_for(k, 6, kb)
+    s, o = new_pair(kb, cap=cap, max_batch=1 << 16, fill=fill)
+    s.bulk_load(to_dev(k), to_dev(v))
+    o.bulk_load(k, v)
+    for q in (k, k - ktype(kb)(1), k + ktype(kb)(1), _queries(rng, kb, k, 20011)):
+        log(f"kb={kb} cap={cap} fill={fill} n={q.size}")
+        check_reads(s, o, kb, q[: 1 << 16], maxpq=5)
+    d = k[rng.random(k.size) < 0.6]
+    s.delete(to_dev(d[: 1 << 16]))
+    o.delete(d[: 1 << 16])
+    check_reads(s, o, kb, _queries(rng, kb, k, 20011), maxpq=5, where="shrunken")
+    s.close()
+
+
+@pytest.mark.parametrize("n", [(3 << 21) - 1, 3 << 21, (3 << 21) + 1])
+def test_long_batches_either_side_of_the_rule(n):
+    rng = np.random.default_rng(n)
+    s, _ = new_pair(32, cap=32, max_batch=n)
+    k = np.unique(rng.integers(1, (1 << 32) - 2, 100000, dtype=np.uint64)).astype(np.uint32)
+    v = w.values_for(k, 6, 32)
+    s.bulk_load(to_dev(k), to_dev(v))
+    q = rng.integers(0, (1 << 32) - 2, n, dtype=np.uint64).astype(np.uint32)
+    q[::3] = k[rng.integers(0, k.size, q[::3].size)]
+    at = np.searchsorted(k, q)
+    ok = at < k.size
+    succ = np.where(ok, k[np.minimum(at, k.size - 1)], np.uint32(0xFFFFFFFF))
+    val = np.where(ok, v[np.minimum(at, k.size - 1)], np.uint32(0xFFFFFFFF))
+    dq = to_dev(q)
+    log(f"n={n}")
+    sk, sv = s.successor(dq)
+    assert np.array_equal(sk.cpu().numpy().view(np.uint32), succ)
+    assert np.array_equal(sv.cpu().numpy().view(np.uint32), val)
+    got = s.lookup(dq).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np.where(succ == q, val, np.uint32(0xFFFFFFFF)))
+    s.close()
