@@ -103,6 +103,7 @@ struct flix_store {
   OccLevels occl{};      // its three levels for the current bucket count
   u32* cuts = nullptr;   // read-share cuts [(max_batch + nb_alloc) / 512 + 2]
   void* dir = nullptr;   // directory search levels above mkba [dir_entries(nb_alloc)]
+  u32* mktop = nullptr;  // [257] first MKBA entry of every top key digit
   // bucket groups of the read path (flix_group.hpp)
   bool grp_ok = false;   // the store's shape fits the group kernels
   u32 ngrp = 1, bpg = 1;
@@ -234,14 +235,12 @@ void dev_free(T** p) {
   *p = nullptr;
 }
 
-// Row table, key spans and spill buffers of the run sort (batches of up to
+// Row table and long-run buffers of the two-launch sort (batches of up to
 // kSplitMaxItems items).
 int alloc_split_scratch(SortScratch& ss, u64 items) {
   const u64 want = items < kSplitMaxItems ? items : kSplitMaxItems;
   int rc;
   if (!ss.toff && (rc = dev_alloc(&ss.toff, (u64)kSplitMaxTiles * 256u * sizeof(u32)))) return rc;
-  if (!ss.span && (rc = dev_alloc(&ss.span, 2ull * kSpanParts * sizeof(u64)))) return rc;
-  if (!ss.spill && (rc = dev_alloc(&ss.spill, sizeof(SpillCtl)))) return rc;
   if (want <= ss.x_items) return FLIX_OK;
   dev_free(&ss.xk);
   dev_free(&ss.xv);
@@ -335,32 +334,32 @@ u32 auto_pool(const flix_store* s, u64 nbuckets) {
 // payload: 0 none, 1 index, 2 value.  Result in s->bk[r], s->bp[r].
 template <typename K>
 int sort_batch_t(flix_store* s, const K* keys, const K* vals, u32 n, int pay, hipStream_t st,
-                 int* r, Ctl* ctl = nullptr, bool* ctl_reset = nullptr) {
+                 int* r, const RunCuts<K>* cuts = nullptr, bool* cuts_done = nullptr) {
   hipError_t e;
   K* k0 = (K*)s->bk[0];
   K* k1 = (K*)s->bk[1];
+  if (cuts_done) *cuts_done = false;
   if (pay == kPayIndex) {
     u32* p0 = (u32*)s->bp[0];
     u32* p1 = (u32*)s->bp[1];
     e = s->rb == 4 ? radix_sort<K, u32, 4, kPayIndex>(keys, nullptr, k0, p0, k1, p1, n, s->ss, st, r)
-                   : radix_sort<K, u32, 8, kPayIndex>(keys, nullptr, k0, p0, k1, p1, n, s->ss, st, r);
+                   : radix_sort<K, u32, 8, kPayIndex>(keys, nullptr, k0, p0, k1, p1, n, s->ss, st, r,
+                                                      cuts, cuts_done);
   } else if (pay == kPayValue) {
     K* p0 = (K*)s->bp[0];
     K* p1 = (K*)s->bp[1];
     e = s->rb == 4 ? radix_sort<K, K, 4, kPayValue>(keys, vals, k0, p0, k1, p1, n, s->ss, st, r)
-                   : radix_sort<K, K, 8, kPayValue>(keys, vals, k0, p0, k1, p1, n, s->ss, st, r, ctl,
-                                                    ctl_reset);
+                   : radix_sort<K, K, 8, kPayValue>(keys, vals, k0, p0, k1, p1, n, s->ss, st, r);
   } else {
     e = s->rb == 4
             ? radix_sort<K, u32, 4, kPayNone>(keys, nullptr, k0, nullptr, k1, nullptr, n, s->ss, st, r)
-            : radix_sort<K, u32, 8, kPayNone>(keys, nullptr, k0, nullptr, k1, nullptr, n, s->ss, st, r,
-                                              ctl, ctl_reset);
+            : radix_sort<K, u32, 8, kPayNone>(keys, nullptr, k0, nullptr, k1, nullptr, n, s->ss, st, r);
   }
   return e == hipSuccess ? FLIX_OK : note_hip_error(e, "sort", __LINE__);
 }
 
-// Per-call counters are cleared before the slice kernel of every update call,
-// by its sort or by this one-block kernel.
+// Per-call counters are cleared by a one-block kernel at the start of every
+// update call (they are read by the kernels that follow on the stream).
 __global__ void k_reset_call(Ctl* ctl, u32 clear_abort) {
   if (threadIdx.x == 0) {
     ctl->need = 0;
@@ -398,8 +397,8 @@ void sort_hook_end(void* ctx, int fam, hipEvent_t e0, hipEvent_t e1) {
 
 template <typename K>
 int sort_batch(flix_store* s, const void* keys, const void* vals, u64 n, int pay, hipStream_t st,
-               int* r, Ctl* ctl = nullptr, bool* ctl_reset = nullptr) {
-  return sort_batch_t<K>(s, (const K*)keys, (const K*)vals, (u32)n, pay, st, r, ctl, ctl_reset);
+               int* r, const RunCuts<K>* cuts = nullptr, bool* cuts_done = nullptr) {
+  return sort_batch_t<K>(s, (const K*)keys, (const K*)vals, (u32)n, pay, st, r, cuts, cuts_done);
 }
 
 // ---- read path --------------------------------------------------------------
@@ -417,7 +416,8 @@ struct ReadCfg<u64> {
 // Bucket kernel over an already sorted read list (keys + original index).
 template <typename K>
 int read_apply_sorted(flix_store* s, int op, const K* skeys, const u32* sidx, u64 n, void* out_k,
-                      void* out_v, const void* hi, u32* counts, u32 maxpq, hipStream_t st) {
+                      void* out_v, const void* hi, u32* counts, u32 maxpq, hipStream_t st,
+                      bool cuts_ready = false) {
   ReadArgs<K> a;
   a.skeys = skeys;
   a.sidx = sidx;
@@ -441,7 +441,9 @@ int read_apply_sorted(flix_store* s, int op, const K* skeys, const u32* sidx, u6
   // cut list: half a wave per share boundary (the list holds cuts_for(max_batch,
   // nb_alloc) >= grid + 1 entries)
   a.cuts = nullptr;
-  if (s->cuts && grid + 1 <= cuts_for(s->max_batch, s->nb_alloc)) {
+  if (cuts_ready) {
+    a.cuts = s->cuts;   // written by the batch sort
+  } else if (s->cuts && grid + 1 <= cuts_for(s->max_batch, s->nb_alloc)) {
     const u32 ncuts = (u32)grid + 1u;
     const TmTok tc = tm_arm(s, F_CUTS);
     launch_timed(tc.b, tc.e, k_merge_cuts<K>, dim3((ncuts + 7) / 8), dim3(256), 0, st, skeys,
@@ -533,10 +535,10 @@ int read_batch_groups(flix_store* s, int op, const K* keys, u64 n, void* out_k, 
 // first pays for long batches of 32-bit point reads (four passes; eight for
 // 64-bit keys), spread over a store that does not fit the caches; the others were
 // faster unsorted at every length measured, up to 12.3 M.  2^26 u32
-// keys, direct against sorted, us: lookups of 2^20 82, 121; 2^22 291, 322; 2^23
-// 572, 522; 12.3 M 845, 697; successors of 2^22 383, 375; 2^23 750, 637.  2^25
+// keys, direct against sorted, us: lookups of 2^20 82, 107; 2^22 291, 451; 2^23
+// 572, 525; 12.3 M 845, 707; successors of 2^22 383, 524; 2^23 750, 634.  2^25
 // u64 keys, lookups of 2^23 590, 824; 12.3 M 860, 1246.  Ranges of 16 keys, 2^22
-// 778, 3520.  2^22 Zipf lookups 219, 400; on 2^20 keys 143, 408.
+// 778, 3520.  2^22 Zipf lookups 219, 1010; on 2^20 keys 143, 501.
 template <typename K>
 constexpr u64 direct_max(int op) {
   return sizeof(K) == 8 || op == kOpRange ? 1ull << 24 : 3ull << 21;
@@ -581,10 +583,24 @@ int read_batch(flix_store* s, int op, const void* keys, u64 n, void* out_k, void
   if (n <= direct_max<K>(op))
     return read_direct<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
   int r;
-  int rc = sort_batch<K>(s, keys, nullptr, n, kPayIndex, st, &r);
+  // the run sort also writes the read kernel's share cuts when it can
+  RunCuts<K> rc_args{};
+  const u64 grid = ((u64)n + s->nb + ReadCfg<K>::S - 1) / ReadCfg<K>::S;
+  const bool want = s->cuts && s->mktop && grid + 1 <= cuts_for(s->max_batch, s->nb_alloc);
+  if (want) {
+    rc_args.mk = (const K*)s->mkba;
+    rc_args.mktop = s->mktop;
+    rc_args.nb = s->nb;
+    rc_args.share = ReadCfg<K>::S;
+    rc_args.ncuts = (u32)grid + 1u;
+    rc_args.cuts = s->cuts;
+  }
+  bool cuts_done = false;
+  int rc = sort_batch<K>(s, keys, nullptr, n, kPayIndex, st, &r, want ? &rc_args : nullptr,
+                         &cuts_done);
   if (rc) return rc;
   return read_apply_sorted<K>(s, op, (const K*)s->bk[r], (const u32*)s->bp[r], n, out_k, out_v, hi,
-                              counts, maxpq, st);
+                              counts, maxpq, st, cuts_done);
 }
 
 // ---- update path ------------------------------------------------------------
@@ -863,11 +879,10 @@ int update_batch(flix_store* s, bool insert, const void* keys, const void* vals,
     return update_apply_sorted<K>(s, insert, (const K*)s->bk[0],
                                   insert ? (const K*)s->bp[0] : nullptr, n, nullptr, st, true);
   }
+  hipLaunchKernelGGL(k_reset_call, dim3(1), dim3(kWorkRegions), 0, st, s->ctl, 1u);
   int r;
-  bool reset = false;
-  int rc = sort_batch<K>(s, keys, vals, n, insert ? kPayValue : kPayNone, st, &r, s->ctl, &reset);
+  int rc = sort_batch<K>(s, keys, vals, n, insert ? kPayValue : kPayNone, st, &r);
   if (rc) return rc;
-  if (!reset) hipLaunchKernelGGL(k_reset_call, dim3(1), dim3(kWorkRegions), 0, st, s->ctl, 1u);
   return update_apply_sorted<K>(s, insert, (const K*)s->bk[r],
                                 insert ? (const K*)s->bp[r] : nullptr, n, nullptr, st);
 }
@@ -883,8 +898,7 @@ void free_slot(EpochSlot* e) {
   dev_free(&e->bsum); dev_free(&e->counts);
   dev_free(&e->ss.hist); dev_free(&e->ss.status); dev_free(&e->ss.status_cl);
   dev_free(&e->ss.tile_ctr); dev_free(&e->ss.err);
-  dev_free(&e->ss.toff); dev_free(&e->ss.span); dev_free(&e->ss.spill);
-  dev_free(&e->ss.xk); dev_free(&e->ss.xv);
+  dev_free(&e->ss.toff); dev_free(&e->ss.xk); dev_free(&e->ss.xv);
   e->ss.x_items = 0;
 }
 
@@ -1184,6 +1198,21 @@ int dump_body(flix_store* s, void* ko, void* vo, u64 capacity, hipStream_t st) {
 // per bucket, the last key of a group is its maxBucket, KEY_MAX for the last
 // bucket).  The pool and a directory of at least nbk buckets are allocated.
 // Asynchronous on st.
+// First MKBA entry of every top key digit (the block boundaries of the read
+// cuts that the run sort writes).
+template <typename K>
+__global__ void k_mk_top(const K* __restrict__ mk, u32 nb, u32* __restrict__ top) {
+  const u32 t = threadIdx.x;
+  const K x = (K)((K)t << (sizeof(K) * 8 - 8));
+  u32 lo = 0, hi = nb;
+  while (lo < hi) {
+    const u32 mid = (lo + hi) >> 1;
+    if (mk[mid] < x) lo = mid + 1; else hi = mid;
+  }
+  top[t] = lo;
+  if (t == 0) top[256] = nb;
+}
+
 template <typename K>
 int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipStream_t st) {
   const u32 pool = s->pool;
@@ -1204,6 +1233,8 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
     hipLaunchKernelGGL((k_build_empty<K>), dim3(1), dim3(64), 0, st, (K*)s->mkba, s->hdr,
                        s->bnodes);
   }
+  HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL((k_mk_top<K>), dim3(1), dim3(256), 0, st, (const K*)s->mkba, nbk, s->mktop);
   HIP_TRY(hipGetLastError());
   // search levels above the directory
   {
@@ -1458,11 +1489,10 @@ void destroy_all(flix_store* s) {
   dev_free(&s->ss.status_cl);
   dev_free(&s->ss.tile_ctr);
   dev_free(&s->ss.toff);
-  dev_free(&s->ss.span);
-  dev_free(&s->ss.spill);
   dev_free(&s->ss.xk);
   dev_free(&s->ss.xv);
   s->ss.x_items = 0;
+  dev_free(&s->mktop);
   dev_free(&s->d_status);
   dev_free(&s->d_status_cl);
   dev_free(&s->d_hist);
@@ -1577,7 +1607,7 @@ int flix_create(const flix_config* cfg, void* stream, flix_store** out) {
   s->max_batch = cfg->max_batch;
   int rc = FLIX_OK;
   u64 mb = cfg->max_batch;
-  if ((rc = dev_alloc(&s->ctl, sizeof(Ctl))) ||
+  if ((rc = dev_alloc(&s->ctl, sizeof(Ctl))) || (rc = dev_alloc(&s->mktop, 257 * sizeof(u32))) ||
       (rc = dev_alloc(&s->bk[0], mb * s->ksz)) ||
       (rc = dev_alloc(&s->bk[1], mb * s->ksz)) || (rc = dev_alloc(&s->bp[0], mb * 8)) ||
       (rc = dev_alloc(&s->bp[1], mb * 8)) || (rc = dev_alloc(&s->work, ((u64)work_slots(mb) + wide_slots(mb)) * sizeof(WorkItem))) ||

@@ -147,12 +147,6 @@ __device__ __forceinline__ u32 lane_id() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
 
-// KPL consecutive keys, loaded and stored as one word of up to 16 bytes.
-template <typename K, int KPL>
-struct alignas(sizeof(K) * KPL >= 16 ? 16 : sizeof(K) * KPL) KeyVec {
-  K k[KPL];
-};
-
 // popcount(mask & lanes-below-me)
 __device__ __forceinline__ u32 rank_below(u64 m) {
   return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
@@ -231,17 +225,18 @@ __device__ __forceinline__ u32 block_exclusive_scan(u32 v, u32* tmp, u32* total)
   }
   if (lane == 63) tmp[w] = x;
   __syncthreads();
-  // every wave scans the wave totals itself
-  constexpr u32 NW = NT / 64;
-  u32 t = lane < NW ? tmp[lane] : 0u;
-#pragma unroll
-  for (u32 off = 1; off < NW; off <<= 1) {
-    const u32 y = __shfl_up(t, off, 64);
-    if (lane >= off) t += y;
+  if (threadIdx.x == 0) {
+    u32 run = 0;
+    for (int i = 0; i < NT / 64; ++i) {
+      u32 t = tmp[i];
+      tmp[i] = run;
+      run += t;
+    }
+    tmp[NT / 64] = run;
   }
-  *total = __shfl(t, (int)NW - 1, 64);
-  const u32 before = __shfl(t, w ? (int)w - 1 : 0, 64);
-  const u32 res = (w ? before : 0u) + x - v;
+  __syncthreads();
+  u32 res = tmp[w] + x - v;
+  *total = tmp[NT / 64];
   __syncthreads();
   return res;
 }

@@ -61,6 +61,11 @@ struct SliceView {
 // holds more than this many of its results.
 constexpr u32 kLaneRangeMax = 16;
 
+template <typename K, int KPL>
+struct alignas(sizeof(K) * KPL >= 16 ? 16 : sizeof(K) * KPL) KeyVec {
+  K k[KPL];
+};
+
 template <typename K, int S, int NT>
 struct ReadSmem {
   K q[S];

@@ -14,7 +14,6 @@
 #pragma once
 
 #include "flix_direct.hpp"
-#include "flix_rank.hpp"
 #include "flix_update.hpp"
 
 namespace flix {
@@ -25,20 +24,105 @@ namespace flix {
 // against 118 (u64: 131 against 132).
 constexpr u32 kSmallMax = 12288;
 
+constexpr u32 kRankKeys = 32;     // keys ranked by a workgroup of 256
 constexpr u32 kSliceKeys = 255;   // keys of a slice unit (and the one before them)
 static_assert((kSmallMax + kSliceKeys - 1) / kSliceKeys <= kSmallParts, "one part per unit");
 
+template <typename K>
+struct RankSmem {
+  static constexpr u32 C = 16384 / sizeof(K);   // batch keys compared per round
+  K k[C];
+};
+
 // Keys [32 unit, 32 unit + 32) to their places in the stable order of the n
-// keys, with their values (vals may be null).  All 256 threads call.
+// keys, with their values (vals may be null).  A wave holds eight keys in
+// scalar registers and its lanes share the comparisons, so each batch key read
+// from LDS serves eight (eight lanes per key, a read per comparison, left LDS
+// the bound: 42 us for 16384 u64 keys, 31 so).  All 256 threads call.
 template <typename K>
 __device__ __forceinline__ void rank_unit(const K* __restrict__ keys, const K* __restrict__ vals,
                                           u32 n, u32 unit, K* __restrict__ ok, K* __restrict__ ov,
                                           RankSmem<K>& sm) {
-  u32 at, i;
-  K x;
-  if (rank_keys<K>([=](u32 j) { return keys[j]; }, n, unit, sm, &i, &x, &at)) {
-    ok[at] = x;
-    if (vals) ov[at] = vals[i];
+  constexpr u32 C = RankSmem<K>::C, E = 16 / sizeof(K), Q = kRankKeys / 4;
+  constexpr u32 G = 64 * E;   // keys a wave compares per step
+  const u32 tid = threadIdx.x, lane = tid & 63u;
+  const u32 i0 = unit * kRankKeys;
+  const u32 iw = i0 + Q * (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  K x[Q];
+  u32 rank[Q];
+#pragma unroll
+  for (u32 q = 0; q < Q; ++q) {
+    x[q] = iw + q < n ? keys[iw + q] : K(0);
+    rank[q] = 0;
+  }
+  // a round's loads are all in flight at a time, the next round's while this
+  // one is compared
+  constexpr u32 L = C / 256;
+  K buf[L];
+  auto fetch = [&](u32 c0) {
+#pragma unroll
+    for (u32 r = 0; r < L; ++r) {
+      const u32 j = c0 + r * 256 + tid;
+      if (c0 + r * 256 < n) buf[r] = j < n ? keys[j] : key_max<K>();
+    }
+  };
+  fetch(0);
+  for (u32 c0 = 0; c0 < n; c0 += C) {
+    __syncthreads();   // the previous round's keys are compared
+    const u32 cnt = n - c0 < C ? n - c0 : C;
+    const u32 cpad = (cnt + G - 1) / G * G;
+#pragma unroll
+    for (u32 r = 0; r < L; ++r)
+      if (r * 256 < cpad) sm.k[r * 256 + tid] = r * 256 < cnt ? buf[r] : key_max<K>();
+    __syncthreads();
+    if (c0 + C < n) fetch(c0 + C);
+    // before this unit's keys equal keys count, after them they do not; among
+    // them positions decide (the padding is after every key and below none)
+    const u32 lo = i0 > c0 ? (i0 - c0 < cpad ? i0 - c0 : cpad) / G * G : 0u;
+    const u32 last = i0 + kRankKeys > c0 ? (i0 + kRankKeys - c0 + G - 1) / G * G : 0u;
+    const u32 mid = last > lo ? (last < cpad ? last : cpad) : lo;
+    const u32 at = lane * E;
+#pragma unroll 2
+    for (u32 j = at; j < lo; j += G) {
+      const KeyVec<K, (int)E> v = *reinterpret_cast<const KeyVec<K, (int)E>*>(&sm.k[j]);
+#pragma unroll
+      for (u32 q = 0; q < Q; ++q)
+#pragma unroll
+        for (u32 e = 0; e < E; ++e) rank[q] += v.k[e] <= x[q] ? 1u : 0u;
+    }
+    for (u32 j = lo + at; j < mid; j += G) {
+      const KeyVec<K, (int)E> v = *reinterpret_cast<const KeyVec<K, (int)E>*>(&sm.k[j]);
+#pragma unroll
+      for (u32 q = 0; q < Q; ++q)
+#pragma unroll
+        for (u32 e = 0; e < E; ++e)
+          rank[q] += (v.k[e] < x[q] || (v.k[e] == x[q] && c0 + j + e < iw + q)) ? 1u : 0u;
+    }
+#pragma unroll 2
+    for (u32 j = mid + at; j < cpad; j += G) {
+      const KeyVec<K, (int)E> v = *reinterpret_cast<const KeyVec<K, (int)E>*>(&sm.k[j]);
+#pragma unroll
+      for (u32 q = 0; q < Q; ++q)
+#pragma unroll
+        for (u32 e = 0; e < E; ++e) rank[q] += v.k[e] < x[q] ? 1u : 0u;
+    }
+  }
+  // lane q takes key q's rank
+  u32 mine = 0;
+  K xm = K(0);
+#pragma unroll
+  for (u32 q = 0; q < Q; ++q) {
+    u32 r = rank[q];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) r += (u32)__shfl_xor((int)r, o, 64);
+    if (lane == q) {
+      mine = r;
+      xm = x[q];
+    }
+  }
+  if (lane < Q && iw + lane < n && mine < n) {
+    ok[mine] = xm;
+    if (vals) ov[mine] = vals[iw + lane];
   }
 }
 

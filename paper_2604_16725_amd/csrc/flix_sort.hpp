@@ -217,23 +217,7 @@ __device__ __forceinline__ u32 look_back(u64* status, u64* status_cl, u32 epoch,
 // a tile waits on is resident or finished: in a plain launch tile = workgroup
 // id (workgroups are dispatched in id order); in a persistent grid every
 // workgroup walks its tiles in increasing order.
-// AGENT: items are read and written at agent scope (no workgroup's L2 then holds
-// them, and the next pass of the same launch needs no cache written back or
-// invalidated).
-template <typename T, bool AGENT>
-__device__ __forceinline__ T sweep_ld(const T* p) {
-  if constexpr (!AGENT) return *p;
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <bool AGENT, typename T>
-__device__ __forceinline__ void sweep_st(T* p, T v) {
-  if constexpr (!AGENT)
-    *p = v;
-  else
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <typename K, typename V, int RB, int NT, int IPT, int PAY, bool AGENT = false>
+template <typename K, typename V, int RB, int NT, int IPT, int PAY>
 __device__ void onesweep_tile(const PassArgs<K, V>& pa, u32 tile,
                               OnesweepSmem<K, V, RB, NT, IPT, PAY>& sm) {
   constexpr int R = 1 << RB;
@@ -273,15 +257,15 @@ __device__ void onesweep_tile(const PassArgs<K, V>& pa, u32 tile,
   for (int k = 0; k < IPT; ++k) {
     u32 idx = tile0 + w * 64u * IPT + (u32)k * 64u + lane;
     if (idx < n) {
-      key[k] = sweep_ld<K, AGENT>(&kin[idx]);
-      if (PAY == kPayIndex) pay[k] = vin ? sweep_ld<V, AGENT>(&vin[idx]) : (V)idx;
-      if (PAY == kPayValue) pay[k] = sweep_ld<V, AGENT>(&vin[idx]);
+      key[k] = kin[idx];
+      if (PAY == kPayIndex) pay[k] = vin ? vin[idx] : (V)idx;
+      if (PAY == kPayValue) pay[k] = vin[idx];
     } else {
       key[k] = K(0);
       if (PAY != kPayNone) pay[k] = V(0);
     }
   }
-  u32 hcount = (tid < (u32)R) ? sweep_ld<u32, AGENT>(&hist_p[tid]) : 0u;
+  u32 hcount = (tid < (u32)R) ? hist_p[tid] : 0u;
 
   // Global exclusive digit offsets of this pass, and the trivial-pass test
   // (all keys share one digit: the stable permutation is the identity).
@@ -294,8 +278,8 @@ __device__ void onesweep_tile(const PassArgs<K, V>& pa, u32 tile,
     for (int k = 0; k < IPT; ++k) {
       u32 idx = tile0 + w * 64u * IPT + (u32)k * 64u + lane;
       if (idx < n) {
-        sweep_st<AGENT>(&kout[idx], key[k]);
-        if (PAY != kPayNone) sweep_st<AGENT>(&vout[idx], pay[k]);
+        kout[idx] = key[k];
+        if (PAY != kPayNone) vout[idx] = pay[k];
       }
     }
     __syncthreads();
@@ -364,8 +348,8 @@ __device__ void onesweep_tile(const PassArgs<K, V>& pa, u32 tile,
       u32 d = digit_of<K, RB>(kk, shift);
       u32 g = s_gbase[d] + (i - s_lstart[d]);
       if (g < n) {   // always true for a consistent histogram
-        sweep_st<AGENT>(&kout[g], kk);
-        if (PAY != kPayNone) sweep_st<AGENT>(&vout[g], s_v[i]);
+        kout[g] = kk;
+        if (PAY != kPayNone) vout[g] = s_v[i];
       }
     }
   }
@@ -516,145 +500,391 @@ __global__ __launch_bounds__(kBigNT) void k_onesweep_big(PassArgs<K, V> pa) {
 }
 
 // ---------------------------------------------------------------------------
-// Batches of at most kSplitMaxItems items with 8-bit digits: three launches
-// and no device-wide look-back chain.
-//   k_key_span:   smallest and largest key of the batch, per workgroup;
-//   k_tile_split: every tile of kSplitTile items is split stably in LDS into the
-//     256ths of that span and written back in place, with the start
-//     of every digit inside the tile (one 256-entry row per tile);
-//   k_run_sort:   one workgroup per digit.  It reads its column of the row
-//     table (where its segment lies in every tile), publishes the run's
-//     length, gathers the segments in tile order (a stable concatenation),
-//     sorts the run in LDS and writes it at the sum of the lengths published
-//     by the lower digits.  A batch with a run longer than LDS holds is sorted
-//     by further workgroups of the launch (spill_sort).
-// A workgroup only waits on lower workgroups, which were dispatched before it
-// and publish before they wait on anything.
+// Batches of at most kLocalMaxItems items with 8-bit digits: one onesweep pass
+// on the most significant digit splits the batch into 256 runs (stably), then
+// k_local_sort gives every run one workgroup that sorts it on the remaining
+// digits.  A run of at most kLocalCap items stays in LDS for all of its
+// passes; a longer one (skewed keys) is sorted in global memory, chunk by
+// chunk, in the two buffers of its run.  Every pass is a stable counting sort
+// whose ranks come from wave ballots over wave-striped items (as in a
+// onesweep tile), so the sort stays stable.  This replaces P - 1 device-wide
+// passes, each with its look-back, by work that stays inside one CU.
 constexpr int kLocalNT = 1024;
 constexpr int kLocalIPT = 8;
 constexpr u32 kLocalCap = kLocalNT * kLocalIPT;
+constexpr u32 kLocalMaxItems = 1u << 22;
+
+constexpr int kLocalMaxPass = 7;   // digits below the top one (64-bit keys)
 
 struct LocalSortHead {
   u32 wc[kLocalNT / 64][256];   // per-wave digit counts, then their prefixes
-  u32 dstart[256];              // first slot of every digit in the run
+  u32 dstart[256];              // first slot of every digit in the run or chunk
+  u32 off[256];                 // running digit offsets (chunked runs)
+  u32 hist[kLocalMaxPass][256]; // digit counts of every pass (chunked runs)
   u32 tmp[kLocalNT / 64 + 1];
   u32 range[2];
 };
 constexpr size_t kLocalHeadBytes = (sizeof(LocalSortHead) + 15) & ~size_t(15);
 
+template <typename K, typename V, int PAY>
+constexpr size_t local_sort_lds() {
+  return kLocalHeadBytes + (size_t)kLocalCap * sizeof(K) +
+         (PAY == kPayNone ? 0 : (size_t)kLocalCap * sizeof(V));
+}
+
+// Stable ranks of the kLocalIPT wave-striped items of each thread among the
+// items of its wave with the same digit; per-wave digit counts go to
+// h.wc[wave] (cleared by the caller).
+template <typename K>
+__device__ __forceinline__ void local_rank(const K (&key)[kLocalIPT], u32 nvalid_base, u32 n,
+                                           u32 shift, LocalSortHead& h, u32 (&rank)[kLocalIPT]) {
+  const u32 w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+#pragma unroll
+  for (int k = 0; k < kLocalIPT; ++k) {
+    const u32 li = nvalid_base + w * 64u * kLocalIPT + (u32)k * 64u + lane;
+    const bool valid = li < n;
+    const u32 d = digit_of<K, 8>(key[k], shift);
+    const u64 m = match_digit<8>(d, wave_ballot(valid));
+    const u32 below = rank_below(m);
+    const u32 cnt = (u32)__popcll(m);
+    const u32 base = valid ? h.wc[w][d] : 0u;
+    rank[k] = base + below;
+    if (valid && below == cnt - 1) h.wc[w][d] = base + cnt;
+  }
+}
+
+// Turns h.wc into exclusive prefixes across waves (per digit) and returns,
+// in thread d < 256, the digit's total.  All threads call.
+__device__ __forceinline__ u32 local_wave_prefix(LocalSortHead& h) {
+  constexpr int WAVES = kLocalNT / 64;
+  const u32 tid = threadIdx.x;
+  u32 tot = 0;
+  if (tid < 256u) {
+#pragma unroll
+    for (int ww = 0; ww < WAVES; ++ww) {
+      const u32 c = h.wc[ww][tid];
+      h.wc[ww][tid] = tot;
+      tot += c;
+    }
+  }
+  return tot;
+}
+
+// Sorts the cnt (<= kLocalCap) wave-striped items held in registers on digits
+// 0..npass-1, leaving them sorted and wave-striped in registers; s_k / s_v
+// are the LDS staging arrays.  All threads call.
+template <typename K, typename V, int PAY>
+__device__ void local_lds_passes(K (&key)[kLocalIPT], V (&pay)[kLocalIPT], u32 cnt, u32 npass,
+                                 LocalSortHead& h, K* s_k, V* s_v) {
+  constexpr int IPT = kLocalIPT;
+  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  u32 rank[IPT];
+  for (u32 p = 0; p < npass; ++p) {
+    const u32 shift = p * 8u;
+    for (u32 i = tid; i < (kLocalNT / 64) * 256u; i += kLocalNT) (&h.wc[0][0])[i] = 0;
+    __syncthreads();
+    local_rank<K>(key, 0u, cnt, shift, h, rank);
+    __syncthreads();
+    const u32 tot = local_wave_prefix(h);
+    u32 dummy;
+    const u32 ds = block_exclusive_scan<kLocalNT>(tid < 256u ? tot : 0u, h.tmp, &dummy);
+    if (tid < 256u) h.dstart[tid] = ds;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+      if (li < cnt) {
+        const u32 d = digit_of<K, 8>(key[k], shift);
+        const u32 pos = h.dstart[d] + h.wc[w][d] + rank[k];
+        s_k[pos] = key[k];
+        if (PAY != kPayNone) s_v[pos] = pay[k];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+      if (li < cnt) {
+        key[k] = s_k[li];
+        if (PAY != kPayNone) pay[k] = s_v[li];
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Stable rank of the flagged wave-striped items of a chunk among the flagged
+// items (input order); returns the chunk's flagged count.  All threads call.
+__device__ __forceinline__ u32 local_class_rank(const bool (&is)[kLocalIPT],
+                                                u32 (&rank)[kLocalIPT], LocalSortHead& h) {
+  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  u32 run = 0;
+#pragma unroll
+  for (int k = 0; k < kLocalIPT; ++k) {
+    const u64 m = wave_ballot(is[k]);
+    rank[k] = run + rank_below(m);
+    run += (u32)__popcll(m);
+  }
+  if (lane == 0) h.wc[0][w] = run;
+  __syncthreads();
+  u32 pre = 0, total = 0;
+  for (u32 ww = 0; ww < kLocalNT / 64; ++ww) {
+    const u32 c = h.wc[0][ww];
+    if (ww < w) pre += c;
+    total += c;
+  }
+#pragma unroll
+  for (int k = 0; k < kLocalIPT; ++k) rank[k] += pre;
+  __syncthreads();
+  return total;
+}
+
+template <typename K, typename V, int PAY>
+__global__ __launch_bounds__(kLocalNT) void k_local_sort(K* __restrict__ ka, V* __restrict__ va,
+                                                         K* __restrict__ kb, V* __restrict__ vb,
+                                                         const u32* __restrict__ top_count,
+                                                         u32 npass, u32 n, u32* __restrict__ err) {
+  extern __shared__ unsigned char lsm[];
+  LocalSortHead& h = *reinterpret_cast<LocalSortHead*>(lsm);
+  K* s_k = reinterpret_cast<K*>(lsm + kLocalHeadBytes);
+  V* s_v = reinterpret_cast<V*>(lsm + kLocalHeadBytes + (size_t)kLocalCap * sizeof(K));
+  constexpr int IPT = kLocalIPT;
+  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  // this run: the blockIdx.x-th run of the most significant digit
+  {
+    const u32 c = tid < 256u ? top_count[tid] : 0u;
+    u32 total;
+    const u32 ex = block_exclusive_scan<kLocalNT>(c, h.tmp, &total);
+    if (tid == blockIdx.x) {
+      h.range[0] = ex;
+      h.range[1] = c;
+    }
+    __syncthreads();
+  }
+  const u32 start = h.range[0], cnt = h.range[1];
+  if (cnt == 0 || npass > (u32)kLocalMaxPass) return;
+  if ((u64)start + cnt > n) {   // histogram inconsistent with the keys: never expected
+    if (tid == 0) atomicOr(err, 2u);
+    return;
+  }
+  K key[IPT];
+  V pay[IPT];
+  u32 rank[IPT];
+  if (cnt <= kLocalCap) {
+    // the run lives in registers and LDS for all passes
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+      if (li < cnt) {
+        key[k] = ka[start + li];
+        if (PAY != kPayNone) pay[k] = va[start + li];
+      } else {
+        key[k] = K(0);
+      }
+    }
+    local_lds_passes<K, V, PAY>(key, pay, cnt, npass, h, s_k, s_v);
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+      if (li < cnt) {
+        kb[start + li] = key[k];
+        if (PAY != kPayNone) vb[start + li] = pay[k];
+      }
+    }
+    return;
+  }
+  // A long run is usually one repeated key (skewed batches).  With X the key
+  // in the middle of the run: the items other than X are gathered in order
+  // into LDS; if they fit, they are sorted there and written around the
+  // block of X items, which keep their input order (stable).
+  {
+    const K X = ka[start + cnt / 2];
+    u32 nrest = 0;
+    bool fits = true;
+    for (u32 base = 0; base < cnt; base += kLocalCap) {
+      bool rest[IPT];
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base + w * 64u * IPT + (u32)k * 64u + lane;
+        const bool valid = li < cnt;
+        key[k] = valid ? ka[start + li] : X;
+        if (PAY != kPayNone && valid) pay[k] = va[start + li];
+        rest[k] = valid && key[k] != X;
+      }
+      const u32 tot = local_class_rank(rest, rank, h);
+      if (nrest + tot > kLocalCap) {   // uniform: tot and nrest are workgroup-wide
+        fits = false;
+        break;
+      }
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        if (rest[k]) {
+          s_k[nrest + rank[k]] = key[k];
+          if (PAY != kPayNone) s_v[nrest + rank[k]] = pay[k];
+        }
+      }
+      nrest += tot;
+    }
+    if (fits) {
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < nrest) {
+          key[k] = s_k[li];
+          if (PAY != kPayNone) pay[k] = s_v[li];
+        }
+      }
+      __syncthreads();
+      local_lds_passes<K, V, PAY>(key, pay, nrest, npass, h, s_k, s_v);
+      // items below X come first, then the X block, then the rest
+      u32 mine = 0;
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < nrest && key[k] < X) ++mine;
+      }
+      u32 nlt;
+      (void)block_exclusive_scan<kLocalNT>(mine, h.tmp, &nlt);
+      const u32 neq = cnt - nrest;
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < nrest) {
+          const u32 o = li < nlt ? li : li + neq;
+          kb[start + o] = key[k];
+          if (PAY != kPayNone) vb[start + o] = pay[k];
+        }
+      }
+      // the X items in input order
+      u32 xbase = 0;
+      for (u32 base = 0; base < cnt; base += kLocalCap) {
+        bool isx[IPT];
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 li = base + w * 64u * IPT + (u32)k * 64u + lane;
+          const bool valid = li < cnt;
+          isx[k] = false;
+          if (valid) {
+            isx[k] = ka[start + li] == X;
+            if (PAY != kPayNone) pay[k] = va[start + li];
+          }
+        }
+        const u32 tot = local_class_rank(isx, rank, h);
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          if (isx[k]) {
+            kb[start + nlt + xbase + rank[k]] = X;
+            if (PAY != kPayNone) vb[start + nlt + xbase + rank[k]] = pay[k];
+          }
+        }
+        xbase += tot;
+      }
+      return;
+    }
+    __syncthreads();
+  }
+  // A long run: each pass reads one buffer of the run and writes the other
+  // (npass is odd, so the last pass writes the second buffer), chunk by
+  // chunk in order.  The digit counts of every pass come from one sweep over
+  // the run first (a pass only permutes the run).
+  for (u32 i = tid; i < npass * 256u; i += kLocalNT) (&h.hist[0][0])[i] = 0;
+  __syncthreads();
+  for (u32 base = 0; base < cnt; base += kLocalCap) {
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = base + (u32)k * kLocalNT + tid;
+      key[k] = li < cnt ? ka[start + li] : K(0);
+    }
+    // Skewed runs repeat a few keys: the wave's most common case, the first
+    // valid lane's digit, is added once with its lane count, the other lanes
+    // add one each (LDS atomics on one address would serialise the wave).
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const bool valid = base + (u32)k * kLocalNT + tid < cnt;
+      const u64 vm = wave_ballot(valid);
+      if (vm == 0) continue;   // uniform across the wave
+      const int src = __ffsll((unsigned long long)vm) - 1;
+      for (u32 p = 0; p < npass; ++p) {
+        const u32 d = digit_of<K, 8>(key[k], p * 8u);
+        const u32 d0 = (u32)__shfl((int)d, src, 64);
+        const u64 same = wave_ballot(valid && d == d0);
+        if ((int)lane == src) atomicAdd(&h.hist[p][d0], (u32)__popcll(same));
+        if (valid && d != d0) atomicAdd(&h.hist[p][d], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (u32 p = 0; p < npass; ++p) {
+    const u32 shift = p * 8u;
+    K* ik = (p & 1u) ? kb + start : ka + start;
+    V* iv = (p & 1u) ? vb + start : va + start;
+    K* ok = (p & 1u) ? ka + start : kb + start;
+    V* ov = (p & 1u) ? va + start : vb + start;
+    {
+      const u32 c = tid < 256u ? h.hist[p][tid] : 0u;
+      u32 dummy;
+      const u32 ex = block_exclusive_scan<kLocalNT>(c, h.tmp, &dummy);
+      if (tid < 256u) h.off[tid] = ex;
+      __syncthreads();
+    }
+    for (u32 base = 0; base < cnt; base += kLocalCap) {
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base + w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < cnt) {
+          key[k] = ik[li];
+          if (PAY != kPayNone) pay[k] = iv[li];
+        } else {
+          key[k] = K(0);
+        }
+      }
+      for (u32 i = tid; i < (kLocalNT / 64) * 256u; i += kLocalNT) (&h.wc[0][0])[i] = 0;
+      __syncthreads();
+      local_rank<K>(key, base, cnt, shift, h, rank);
+      __syncthreads();
+      const u32 tot = local_wave_prefix(h);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base + w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < cnt) {
+          const u32 d = digit_of<K, 8>(key[k], shift);
+          const u32 pos = h.off[d] + h.wc[w][d] + rank[k];
+          ok[pos] = key[k];
+          if (PAY != kPayNone) ov[pos] = pay[k];
+        }
+      }
+      __syncthreads();
+      if (tid < 256u) h.off[tid] += tot;
+      __syncthreads();
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Batches of at most kSplitMaxItems items with 8-bit digits: two launches and
+// no device-wide look-back chain.
+//   k_tile_split: every tile of kSplitTile items is split stably on the most
+//     significant digit in LDS and written back in place, digit by digit,
+//     with the start of every digit inside the tile (one 256-entry row per
+//     tile);
+//   k_run_sort: one workgroup per top digit.  It reads its column of the row
+//     table (where its digit's segment lies in every tile), publishes the
+//     run's length, gathers the segments in tile order (a stable
+//     concatenation), sorts the run on the digits that vary inside it
+//     (LDS passes when it fits, else the dominant-key or chunked global
+//     forms), and writes it at the sum of the lengths published by the lower
+//     digits.
+// A workgroup only waits on lower digits, whose workgroups were dispatched
+// before it and publish before they wait on anything.
 constexpr int kSplitNT = 512;
 constexpr int kSplitIPT = 4;
 constexpr u32 kSplitTile = kSplitNT * kSplitIPT;
 constexpr u32 kSplitMaxTiles = 1024;
-// Runs average n / 256 items and must stay below kLocalCap: 7168 is twelve
-// standard deviations of a uniform batch away.
-constexpr u32 kSplitMaxItems = 7168 * 256;
-static_assert(kSplitMaxItems <= kSplitMaxTiles * kSplitTile, "row table");
-constexpr u32 kSpanParts = 256;
+constexpr u32 kSplitMaxItems = kSplitMaxTiles * kSplitTile;   // 2^21
 static_assert(kSplitMaxTiles <= (u32)kLocalNT, "one tile per thread of a run workgroup");
 static_assert(kSplitTile <= 65536u, "segment starts are 16-bit");
-
-// Smallest and largest of the workgroup's keys (lo and hi per thread, KEY_MAX
-// and 0 in threads without any), to every thread.  red: 2 * NT / 64 words.  All
-// threads call.
-template <typename K, int NT>
-__device__ __forceinline__ void block_span(K& lo, K& hi, u64* red) {
-  constexpr u32 NW = NT / 64;
-  const u32 tid = threadIdx.x;
-  u64 a = (u64)lo, b = (u64)hi;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const u64 x = __shfl_xor((unsigned long long)a, off, 64);
-    const u64 y = __shfl_xor((unsigned long long)b, off, 64);
-    a = a < x ? a : x;
-    b = b > y ? b : y;
-  }
-  __syncthreads();
-  if ((tid & 63u) == 0) {
-    red[tid >> 6] = a;
-    red[NW + (tid >> 6)] = b;
-  }
-  __syncthreads();
-  a = red[tid & (NW - 1)];
-  b = red[NW + (tid & (NW - 1))];
-#pragma unroll
-  for (int off = NW / 2; off >= 1; off >>= 1) {
-    const u64 x = __shfl_xor((unsigned long long)a, off, 64);
-    const u64 y = __shfl_xor((unsigned long long)b, off, 64);
-    a = a < x ? a : x;
-    b = b > y ? b : y;
-  }
-  lo = (K)a;
-  hi = (K)b;
-}
-
-// Counters of spill_sort; k_key_span clears them.
-struct SpillCtl {
-  u32 hist[8 * 256];
-  u32 ticket[16];        // [0]: work handed out
-  // finished parts of the reading and of every pass: counted in 16 groups, then
-  // the full groups, counters of one line each (a pass over 300000 items 17 us;
-  // with one counter for all 23)
-  u32 done[9][17][16];
-};
-
-// Digits are taken from the span of the batch, not from the key width: keys
-// below 2^56, say consecutive numbers, would share their top byte (2^20 such
-// u64 keys: one run, sorted by one workgroup in 9 ms; 51 us so).  parts: [256]
-// smallest, [256] largest.
-template <typename K>
-__global__ __launch_bounds__(256) void k_key_span(const K* __restrict__ keys, u32 n,
-                                                  u64* __restrict__ parts, SpillCtl* sc, Ctl* ctl) {
-  __shared__ u64 red[8];
-  if (blockIdx.x == gridDim.x - 1)
-    for (u32 i = threadIdx.x; i < sizeof(SpillCtl) / 4; i += 256) reinterpret_cast<u32*>(sc)[i] = 0;
-  // the counters of the update call this sort begins (ctl may be null)
-  if (ctl && blockIdx.x == 0) {
-    if (threadIdx.x == 0) {
-      ctl->need = 0;
-      ctl->call_err = 0;
-      ctl->call_abort = 0;
-    }
-    reset_work_regions(ctl, threadIdx.x);
-  }
-  constexpr u32 U = 8;
-  K lo = key_max<K>(), hi = K(0);
-  for (u64 base = (u64)blockIdx.x * 256 * U; base < n; base += (u64)gridDim.x * 256 * U) {
-    K k[U];
-#pragma unroll
-    for (u32 u = 0; u < U; ++u) {
-      const u64 i = base + u * 256 + threadIdx.x;
-      k[u] = keys[i < n ? i : base];
-    }
-#pragma unroll
-    for (u32 u = 0; u < U; ++u) {
-      lo = k[u] < lo ? k[u] : lo;
-      hi = k[u] > hi ? k[u] : hi;
-    }
-  }
-  block_span<K, 256>(lo, hi, red);
-  if (threadIdx.x == 0) {
-    parts[blockIdx.x] = (u64)lo;
-    parts[kSpanParts + blockIdx.x] = (u64)hi;
-  }
-}
-
-// Which 256th of the span [kmin, kmax] a key lies in (of its top 16 bits, scaled,
-// so that all 256 are used whatever the span).
-template <typename K>
-struct SpanDigit {
-  K kmin;
-  u32 shift, scale;
-  __device__ __forceinline__ SpanDigit(K lo, K hi) : kmin(lo) {
-    const u64 span = (u64)(K)(hi - lo);
-    const u32 width = span ? 64u - (u32)__builtin_clzll(span) : 0u;
-    shift = width > 16 ? width - 16 : 0u;
-    scale = (1u << 24) / ((u32)(span >> shift) + 1u);
-  }
-  __device__ __forceinline__ u32 operator()(K k) const {
-    return (((u32)((K)(k - kmin) >> shift) & 0xFFFFu) * scale) >> 16;
-  }
-};
 
 template <typename K, typename V, int PAY>
 struct SplitSmem {
@@ -663,7 +893,6 @@ struct SplitSmem {
   u32 wc[kSplitNT / 64][256];
   u32 lstart[256];
   u32 tmp[kSplitNT / 64 + 1];
-  u64 red[2 * kSplitNT / 64];
 };
 
 template <typename K, typename V, int PAY>
@@ -671,8 +900,7 @@ __global__ __launch_bounds__(kSplitNT) void k_tile_split(const K* __restrict__ k
                                                          const V* __restrict__ vin,
                                                          K* __restrict__ ks, V* __restrict__ vs,
                                                          u32* __restrict__ toff, u32 n,
-                                                         const u64* __restrict__ parts,
-                                                         u32 nparts) {
+                                                         u32 shift) {
   __shared__ SplitSmem<K, V, PAY> sm;
   constexpr int IPT = kSplitIPT;
   constexpr int NT = kSplitNT;
@@ -693,21 +921,14 @@ __global__ __launch_bounds__(kSplitNT) void k_tile_split(const K* __restrict__ k
       if (PAY == kPayValue) pay[k] = vin[idx];
     }
   }
-  // the batch's span, from its parts
-  K kmin = key_max<K>(), kmax = K(0);
-  if (tid < nparts) {
-    kmin = (K)parts[tid];
-    kmax = (K)parts[kSpanParts + tid];
-  }
-  block_span<K, NT>(kmin, kmax, sm.red);
-  const SpanDigit<K> dig(kmin, kmax);
+  __syncthreads();
   // stable rank among the same-digit items of the wave (wave-striped order)
   u32 rank[IPT];
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
     const u32 idx = tile0 + w * 64u * IPT + (u32)k * 64u + lane;
     const bool valid = idx < n;
-    const u32 d = dig(key[k]);
+    const u32 d = digit_of<K, 8>(key[k], shift);
     const u64 m = match_digit<8>(d, wave_ballot(valid));
     const u32 below = rank_below(m);
     const u32 cnt = (u32)__popcll(m);
@@ -738,7 +959,7 @@ __global__ __launch_bounds__(kSplitNT) void k_tile_split(const K* __restrict__ k
   for (int k = 0; k < IPT; ++k) {
     const u32 idx = tile0 + w * 64u * IPT + (u32)k * 64u + lane;
     if (idx < n) {
-      const u32 d = dig(key[k]);
+      const u32 d = digit_of<K, 8>(key[k], shift);
       const u32 pos = sm.lstart[d] + sm.wc[w][d] + rank[k];
       sm.k[pos] = key[k];
       if (PAY != kPayNone) sm.v[pos] = pay[k];
@@ -756,12 +977,12 @@ __global__ __launch_bounds__(kSplitNT) void k_tile_split(const K* __restrict__ k
   }
 }
 
-// Where one digit's run lies in the split tiles: segment t starts at
+// Where one top digit's run lies in the split tiles: segment t starts at
 // a[t] inside tile t and holds run positions [p[t], p[t+1]).
 struct RunMap {
   u32 p[kSplitMaxTiles + 1];
   unsigned short a[kSplitMaxTiles];
-  u64 red[2 * kLocalNT / 64];
+  u32 red[4];
 };
 constexpr size_t kRunMapBytes = (sizeof(RunMap) + 15) & ~size_t(15);
 
@@ -782,11 +1003,214 @@ __device__ __forceinline__ u32 run_src(const RunMap& m, u32 ntiles, u32 i) {
   return lo * kSplitTile + m.a[lo] + (i - m.p[lo]);
 }
 
-// The map of digit d's run; returns its length.  All threads call.
-__device__ __forceinline__ u32 load_run_map(const u32* __restrict__ toff, u32 d, u32 n, RunMap& m,
-                                            u32* tmp, u32* err) {
+// Bit p of the result is set when digit p (below the top one) differs
+// between some two of the thread's valid items' keys across the workgroup.
+template <typename K>
+__device__ __forceinline__ u32 varying_digits(K kand, K kor, u32 npass, u32* red) {
   const u32 tid = threadIdx.x;
+  if (tid < 4u) red[tid] = tid < 2u ? 0xFFFFFFFFu : 0u;
+  __syncthreads();
+  const u64 a = (u64)kand, o = (u64)kor;
+  u32 a0 = (u32)a, a1 = (u32)(a >> 32), o0 = (u32)o, o1 = (u32)(o >> 32);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    a0 &= (u32)__shfl_xor((int)a0, off, 64);
+    a1 &= (u32)__shfl_xor((int)a1, off, 64);
+    o0 |= (u32)__shfl_xor((int)o0, off, 64);
+    o1 |= (u32)__shfl_xor((int)o1, off, 64);
+  }
+  if ((tid & 63u) == 0) {
+    atomicAnd(&red[0], a0);
+    atomicAnd(&red[1], a1);
+    atomicOr(&red[2], o0);
+    atomicOr(&red[3], o1);
+  }
+  __syncthreads();
+  const u64 diff = (((u64)red[1] << 32) | red[0]) ^ (((u64)red[3] << 32) | red[2]);
+  __syncthreads();
+  u32 mask = 0;
+  for (u32 p = 0; p < npass; ++p)
+    if ((diff >> (8u * p)) & 0xFFull) mask |= 1u << p;
+  return mask;
+}
+
+// LDS passes over the digits set in `passes` for cnt items held wave-striped
+// with ipt items per lane (position w*64*ipt + k*64 + lane); leaves them
+// sorted in the same layout.  All threads call.
+template <typename K, typename V, int PAY>
+__device__ void run_lds_passes(K (&key)[kLocalIPT], V (&pay)[kLocalIPT], u32 cnt, u32 ipt,
+                               u32 passes, LocalSortHead& h, K* s_k, V* s_v) {
+  constexpr int IPT = kLocalIPT;
+  constexpr int WAVES = kLocalNT / 64;
+  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  u32 rank[IPT];
+  for (u32 p = 0; p < (u32)kLocalMaxPass; ++p) {
+    if (!((passes >> p) & 1u)) continue;
+    const u32 shift = p * 8u;
+    for (u32 i = tid; i < (u32)WAVES * 256u; i += kLocalNT) (&h.wc[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      rank[k] = 0;
+      if ((u32)k < ipt) {   // uniform across the workgroup
+        const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+        const bool valid = li < cnt;
+        const u32 d = digit_of<K, 8>(key[k], shift);
+        const u64 vm = wave_ballot(valid);
+        if (vm) {
+          const u64 m = match_digit<8>(d, vm);
+          const u32 below = rank_below(m);
+          const u32 c = (u32)__popcll(m);
+          const u32 base = valid ? h.wc[w][d] : 0u;
+          rank[k] = base + below;
+          if (valid && below == c - 1) h.wc[w][d] = base + c;
+        }
+      }
+    }
+    __syncthreads();
+    u32 tot = 0;
+    if (tid < 256u) {
+      u32 c[WAVES];
+#pragma unroll
+      for (int ww = 0; ww < WAVES; ++ww) c[ww] = h.wc[ww][tid];
+#pragma unroll
+      for (int ww = 0; ww < WAVES; ++ww) {
+        h.wc[ww][tid] = tot;
+        tot += c[ww];
+      }
+    }
+    u32 dummy;
+    const u32 ds = block_exclusive_scan<kLocalNT>(tid < 256u ? tot : 0u, h.tmp, &dummy);
+    if (tid < 256u) h.dstart[tid] = ds;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+      if ((u32)k < ipt && li < cnt) {
+        const u32 d = digit_of<K, 8>(key[k], shift);
+        const u32 pos = h.dstart[d] + h.wc[w][d] + rank[k];
+        s_k[pos] = key[k];
+        if (PAY != kPayNone) s_v[pos] = pay[k];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+      if ((u32)k < ipt && li < cnt) {
+        key[k] = s_k[li];
+        if (PAY != kPayNone) pay[k] = s_v[li];
+      }
+    }
+  }
+}
+
+// Sum of the run lengths published by the digits below d (all threads call;
+// the result is workgroup-uniform).
+__device__ __forceinline__ u32 lower_runs_total(const u64* status, u32 d, u32 epoch, u32* err,
+                                                u32* tmp) {
+  const u32 tid = threadIdx.x;
+  u32 v = 0;
+  if (tid < d) {
+    u32 polls = 0;
+    while (true) {
+      const u64 s = ld_agent(&status[tid]);
+      if ((u32)(s >> 34) == epoch && ((s >> 32) & 3u) != 0u) {
+        v = (u32)s;
+        break;
+      }
+      // bounded wait: a lower digit that never publishes is a bug, and the
+      // kernel must still end; the error word reports it
+      if (++polls > (1u << 22)) {
+        atomicOr(err, 1u);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  u32 total;
+  (void)block_exclusive_scan<kLocalNT>(v, tmp, &total);
+  return total;
+}
+
+// Merge-path cuts of the read kernel's shares, written by the run sort: the
+// merge of the sorted batch with the directory maxima (MKBA) is, top digit
+// by top digit, the merge of one run with the MKBA entries of that digit, so
+// the workgroup of digit d finds every cut whose diagonal falls in its block
+// [base + mktop[d], base + cnt + mktop[d + 1]) by a binary search over its
+// own run and MKBA slice (ties to the keys: a key equal to MKBA[i] belongs
+// to bucket i).  This replaces a device-wide search launch per read call.
+template <typename K>
+struct RunCuts {
+  const K* mk;          // MKBA (nb entries); null: no cuts wanted
+  const u32* mktop;     // [257] first MKBA entry of every top digit
+  u32 nb;
+  u32 share;            // merged items per share
+  u32 ncuts;            // shares + 1 (the last diagonal is the merge's end)
+  u32* cuts;
+};
+
+// Cuts of block d (all threads call; run: the sorted run (cnt keys), mks:
+// the digit's MKBA entries (nmk), both in LDS or global memory).
+template <typename K>
+__device__ void write_block_cuts(const RunCuts<K>& rc, u32 d, u32 base, u32 cnt, const K* run,
+                                 const K* mks, u32 nmk, u64 total) {
+  const u64 b0 = (u64)base + rc.mktop[d];
+  const u64 b1 = b0 + cnt + nmk;
+  const u32 c0 = (u32)((b0 + rc.share - 1) / rc.share);
+  const u32 c1 = d == 255u ? rc.ncuts : (u32)((b1 + rc.share - 1) / rc.share);
+  for (u32 c = c0 + threadIdx.x; c < c1; c += kLocalNT) {
+    u64 dd = (u64)c * rc.share;
+    if (dd > total) dd = total;
+    const u32 l = (u32)(dd - b0);   // local diagonal, at most cnt + nmk
+    // the run items among the first l items of merge(run, mks): the
+    // predicate run[p] <= mks[l - p - 1] holds exactly for p below the cut
+    u32 lo = l > nmk ? l - nmk : 0u;
+    u32 hi = l < cnt ? l : cnt;
+    while (lo < hi) {
+      const u32 mid = (lo + hi) >> 1;
+      if (run[mid] <= mks[l - mid - 1]) lo = mid + 1; else hi = mid;
+    }
+    rc.cuts[c] = base + lo;
+  }
+}
+
+template <typename K, typename V, int PAY>
+__global__ __launch_bounds__(kLocalNT) void k_run_sort(const K* __restrict__ ks,
+                                                       const V* __restrict__ vs,
+                                                       K* __restrict__ ko, V* __restrict__ vo,
+                                                       K* __restrict__ kx, V* __restrict__ vx,
+                                                       const u32* __restrict__ toff,
+                                                       u64* __restrict__ status, u32 epoch,
+                                                       u32 npass, u32 n, u32* __restrict__ err,
+                                                       RunCuts<K> rcut) {
+  extern __shared__ unsigned char lsm[];
+  LocalSortHead& h = *reinterpret_cast<LocalSortHead*>(lsm);
+  RunMap& m = *reinterpret_cast<RunMap*>(lsm + kLocalHeadBytes);
+  K* s_k = reinterpret_cast<K*>(lsm + kLocalHeadBytes + kRunMapBytes);
+  V* s_v = reinterpret_cast<V*>(lsm + kLocalHeadBytes + kRunMapBytes +
+                                (size_t)kLocalCap * sizeof(K));
+  constexpr int IPT = kLocalIPT;
+  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  const u32 d = blockIdx.x;
   const u32 ntiles = (n + kSplitTile - 1) / kSplitTile;   // <= kSplitMaxTiles = blockDim
+  // the read kernel's cuts of this digit's block, once the run is in place
+  // (run: its sorted keys in LDS or in the output); the MKBA slice is staged
+  // in the payload area of LDS when it fits (the payloads are written out)
+  auto block_cuts = [&](u32 base, u32 cnt, const K* run) {
+    if (rcut.mk == nullptr) return;
+    const u32 m0 = rcut.mktop[d];
+    const u32 nmk = rcut.mktop[d + 1] - m0;
+    const K* mks = rcut.mk + m0;
+    if (PAY != kPayNone && (size_t)nmk * sizeof(K) <= (size_t)kLocalCap * sizeof(V)) {
+      K* st = reinterpret_cast<K*>(s_v);
+      for (u32 i = threadIdx.x; i < nmk; i += kLocalNT) st[i] = mks[i];
+      mks = st;
+    }
+    __syncthreads();
+    write_block_cuts<K>(rcut, d, base, cnt, run, mks, nmk, (u64)n + rcut.nb);
+  };
+  // this digit's segment in every tile
   u32 c = 0;
   if (tid < ntiles) {
     const u32 tn = (n - tid * kSplitTile) < kSplitTile ? (n - tid * kSplitTile) : kSplitTile;
@@ -800,419 +1224,403 @@ __device__ __forceinline__ u32 load_run_map(const u32* __restrict__ toff, u32 d,
     m.a[tid] = (unsigned short)a;
   }
   u32 cnt;
-  const u32 pre = block_exclusive_scan<kLocalNT>(c, tmp, &cnt);
+  const u32 pre = block_exclusive_scan<kLocalNT>(c, h.tmp, &cnt);
   if (tid < ntiles) m.p[tid] = pre;
-  if (tid == 0) m.p[ntiles] = cnt;
-  return cnt;
-}
-
-// Moves item k of every lane (wave-striped, ipt items per lane: position
-// w*64*ipt + k*64 + lane) to position to[k]; the items are then held in the
-// same layout and lie in s_k / s_v.  All threads call.
-template <typename K, typename V, int PAY>
-__device__ __forceinline__ void run_exchange(K (&key)[kLocalIPT], V (&pay)[kLocalIPT],
-                                             const u32 (&to)[kLocalIPT], u32 cnt, u32 ipt, K* s_k,
-                                             V* s_v) {
-  const u32 w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-#pragma unroll
-  for (int k = 0; k < kLocalIPT; ++k) {
-    if ((u32)k < ipt && w * 64u * ipt + (u32)k * 64u + lane < cnt) {
-      s_k[to[k]] = key[k];
-      if (PAY != kPayNone) s_v[to[k]] = pay[k];
-    }
+  if (tid == 0) {
+    m.p[ntiles] = cnt;
+    st_agent(&status[d], pack_status(epoch, kFlagAgg, cnt));
   }
   __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kLocalIPT; ++k) {
-    const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-    if ((u32)k < ipt && li < cnt) {
-      key[k] = s_k[li];
-      if (PAY != kPayNone) pay[k] = s_v[li];
-    }
+  if (cnt == 0) {
+    if (rcut.mk != nullptr) block_cuts(lower_runs_total(status, d, epoch, err, h.tmp), 0u, s_k);
+    return;
   }
-}
-
-// One stable counting pass on the 8-bit digit of (key - kmin) >> shift over
-// cnt items held wave-striped.  All threads call.
-template <typename K, typename V, int PAY>
-__device__ __forceinline__ void run_digit_pass(K (&key)[kLocalIPT], V (&pay)[kLocalIPT], u32 cnt,
-                                               u32 ipt, K kmin, u32 shift, LocalSortHead& h,
-                                               K* s_k, V* s_v) {
-  constexpr int IPT = kLocalIPT;
-  constexpr int WAVES = kLocalNT / 64;
-  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
-  u32 rank[IPT];
-  for (u32 i = tid; i < (u32)WAVES * 256u; i += kLocalNT) (&h.wc[0][0])[i] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    rank[k] = 0;
-    if ((u32)k < ipt) {   // uniform across the workgroup
-      const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-      const bool valid = li < cnt;
-      const u32 d = digit_of<K, 8>((K)(key[k] - kmin), shift);
-      const u64 vm = wave_ballot(valid);
-      if (vm) {
-        const u64 m = match_digit<8>(d, vm);
-        const u32 below = rank_below(m);
-        const u32 c = (u32)__popcll(m);
-        const u32 base = valid ? h.wc[w][d] : 0u;
-        rank[k] = base + below;
-        if (valid && below == c - 1) h.wc[w][d] = base + c;
-      }
-    }
-  }
-  __syncthreads();
-  u32 tot = 0;
-  if (tid < 256u) {
-    u32 c[WAVES];
-#pragma unroll
-    for (int ww = 0; ww < WAVES; ++ww) c[ww] = h.wc[ww][tid];
-#pragma unroll
-    for (int ww = 0; ww < WAVES; ++ww) {
-      h.wc[ww][tid] = tot;
-      tot += c[ww];
-    }
-  }
-  u32 dummy;
-  const u32 ds = block_exclusive_scan<kLocalNT>(tid < 256u ? tot : 0u, h.tmp, &dummy);
-  if (tid < 256u) h.dstart[tid] = ds;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-    if ((u32)k < ipt && li < cnt) {
-      const u32 d = digit_of<K, 8>((K)(key[k] - kmin), shift);
-      rank[k] += h.dstart[d] + h.wc[w][d];
-    }
-  }
-  run_exchange<K, V, PAY>(key, pay, rank, cnt, ipt, s_k, s_v);
-}
-
-// Sorts cnt items held wave-striped whose keys lie in [kmin, kmax].  The top 16
-// bits of the span come first, in two passes; few keys of a run agree in them,
-// and those are put in order by comparing neighbours in LDS.  Where more than
-// kTieMax agree, the whole span is sorted digit by digit.  (Every digit that
-// varied, seven of a u64 run: 46 us for the run sort of 2^20 keys, 35 so.)
-// Leaves the keys in s_k too.  All threads call.
-constexpr u32 kTieMax = 16;
-
-template <typename K, typename V, int PAY>
-__device__ __forceinline__ void run_span_sort(K (&key)[kLocalIPT], V (&pay)[kLocalIPT], u32 cnt,
-                                              u32 ipt, K kmin, K kmax, LocalSortHead& h, K* s_k,
-                                              V* s_v) {
-  constexpr int IPT = kLocalIPT;
-  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
-  const u64 span = (u64)(K)(kmax - kmin);
-  const u32 width = span ? 64u - (u32)__builtin_clzll(span) : 1u;
-  const u32 sh = width > 16 ? width - 16 : 0u;
-  u32 s = sh;
-  bool whole = false;   // the digits from the lowest on
-  while (true) {
-    __syncthreads();
-    run_digit_pass<K, V, PAY>(key, pay, cnt, ipt, kmin, s, h, s_k, s_v);
-    s += 8;
-    if (s < width) continue;
-    if (sh == 0 || whole) return;
-    // every item looks for its neighbours with the same 16 bits
-    if (tid == 0) {
-      h.range[0] = 0;
-      h.range[1] = 0;
-    }
-    __syncthreads();
-    u32 to[IPT];
-    bool tied = false, many = false;
+  K key[IPT];
+  V pay[IPT];
+  if (cnt <= kLocalCap) {
+    // the run lives in registers and LDS for all of its passes
+    const u32 ipt = (cnt + kLocalNT - 1) / kLocalNT;
+    K kand = ~K(0), kor = K(0);
 #pragma unroll
     for (int k = 0; k < IPT; ++k) {
       const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-      to[k] = li;
+      key[k] = K(0);
       if ((u32)k < ipt && li < cnt) {
-        const K p = (K)(key[k] - kmin) >> sh;
-        u32 before = 0;   // items of the group that belong before this one
-        u32 a = li;
-        while (a > 0) {
-          const K o = s_k[a - 1];
-          if (((K)(o - kmin) >> sh) != p) break;
-          --a;
-          tied = true;
-          if (li - a >= kTieMax) { many = true; break; }
-          before += o <= key[k] ? 1u : 0u;   // (equal keys keep their order)
-        }
-        u32 b = li + 1;
-        while (b < cnt && !many) {
-          const K o = s_k[b];
-          if (((K)(o - kmin) >> sh) != p) break;
-          ++b;
-          tied = true;
-          if (b - li > kTieMax) { many = true; break; }
-          before += o < key[k] ? 1u : 0u;
-        }
-        to[k] = a + before;
+        const u32 src = run_src(m, ntiles, li);
+        key[k] = ks[src];
+        if (PAY != kPayNone) pay[k] = vs[src];
+        kand &= key[k];
+        kor |= key[k];
       }
     }
-    if (wave_ballot(tied) && lane == 0) h.range[0] = 1;
-    if (wave_ballot(many) && lane == 0) h.range[1] = 1;
-    __syncthreads();
-    const bool any_tied = h.range[0] != 0, any_many = h.range[1] != 0;
-    if (any_many) {
-      whole = true;
-      s = 0;
-      continue;
+    const u32 passes = varying_digits<K>(kand, kor, npass, m.red);
+    run_lds_passes<K, V, PAY>(key, pay, cnt, ipt, passes, h, s_k, s_v);
+    const u32 base = lower_runs_total(status, d, epoch, err, h.tmp);
+    if (base + cnt > n) {   // published lengths inconsistent: never expected
+      if (tid == 0) atomicOr(err, 2u);
+      return;
     }
-    if (any_tied) run_exchange<K, V, PAY>(key, pay, to, cnt, ipt, s_k, s_v);
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+      if ((u32)k < ipt && li < cnt) {
+        ko[base + li] = key[k];
+        if (PAY != kPayNone) vo[base + li] = pay[k];
+      }
+    }
+    if (rcut.mk != nullptr) {
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+        if ((u32)k < ipt && li < cnt) s_k[li] = key[k];
+      }
+      block_cuts(base, cnt, s_k);
+    }
     return;
   }
-}
-
-// Length published for digit i (0 if it never is: a bug, and the kernel must
-// still end; the error word reports it).
-__device__ __forceinline__ u32 wait_run_length(const u64* status, u32 i, u32 epoch, u32* err) {
-  u32 polls = 0;
-  while (true) {
-    const u64 s = ld_agent(&status[i]);
-    if ((u32)(s >> 34) == epoch && ((s >> 32) & 3u) != 0u) return (u32)s;
-    if (++polls > (1u << 22)) {
-      atomicOr(err, 1u);
-      return 0;
-    }
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-
-// A batch with a run longer than kLocalCap items (keys in a few dense stretches,
-// or many equal ones) is sorted digit by digit instead, from the split tiles, by
-// the further workgroups of the launch: one reading counts every digit, then a
-// onesweep pass per digit that varies.  The work is handed out by a counter in
-// the order of the passes, so a workgroup waits only on work that a running one
-// holds; a pass begins when the one before has ended (its tiles are counted) and
-// its data are at agent scope.  Its cost does not depend on the keys: 2^20 u64
-// pairs in 64 dense stretches 333 us, 70% one key 320, seven keys 91 (each long
-// run by one workgroup: 381, 1133, 4861).  A pass is 36 us there, 17 us of it the
-// chain of hand-outs and look-backs, the rest the traffic past the L2: with plain
-// stores and a release fence per tile a pass took 48, with fences in every wave 150.
-constexpr int kSpillIPT = 4;
-constexpr u32 kSpillTile = kLocalNT * kSpillIPT;
-constexpr u32 kSpillHistParts = 64;
-
-template <typename K, typename V, int PAY>
-using SpillTile = OnesweepSmem<K, V, 8, kLocalNT, kSpillIPT, PAY>;
-
-struct SpillSmem {   // in front of the pass's tile
-  u32 hist[8 * 256];
-  u32 active[8];   // digits that vary, lowest first
-  u32 nactive;
-  u32 ticket;
-  u32 stop;
-};
-
-// Waits until all `parts` are; false when they never are (a bug: the error word
-// reports it).  All threads call.
-__device__ __forceinline__ bool wait_done(const u32 (*c)[16], u32 parts, SpillSmem& sm, u32* err) {
-  if (threadIdx.x == 0) {
-    const u32 want = parts < 16u ? parts : 16u;
-    u32 polls = 0;
-    sm.stop = 0;
-    while (ld_agent32(&c[0][0]) < want) {
-      if (++polls > (1u << 22)) {
-        atomicOr(err, 1u);
-        sm.stop = 1;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  __syncthreads();
-  return sm.stop == 0;
-}
-
-// Counts part i of `parts` as finished once the workgroup's writes are done.  All
-// threads call.
-__device__ __forceinline__ void count_done(u32 (*c)[16], u32 i, u32 parts) {
-  __builtin_amdgcn_s_waitcnt(0);   // this wave's writes, all at agent scope, are done
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const u32 g = i & 15u, members = (parts - g + 15u) / 16u;
-    if (atomicAdd(&c[1 + g][0], 1u) + 1u == members) atomicAdd(&c[0][0], 1u);
-  }
-}
-
-// ks / vs: the split tiles, free to overwrite once status[256 + d] of every digit
-// is published; xk / xv: as many items; ko / vo: the result.  ps: look-back words
-// of the passes, epochs epoch + 1 to epoch + 8.
-template <typename K, typename V, int PAY>
-__device__ __noinline__ void spill_sort(K* ks, V* vs, K* ko, V* vo, K* xk, V* xv, u64* status,
-                                        u64* ps, u64* ps_cl, SpillCtl* sc, u32 epoch, u32 n,
-                                        u32* err, unsigned char* lds) {
-  constexpr u32 P = (u32)sizeof(K);
-  SpillSmem& sm = *reinterpret_cast<SpillSmem*>(lds);
-  SpillTile<K, V, PAY>& tm =
-      *reinterpret_cast<SpillTile<K, V, PAY>*>(lds + ((sizeof(SpillSmem) + 15) & ~size_t(15)));
-  static_assert(sizeof(SpillSmem) + 16 + sizeof(SpillTile<K, V, PAY>) <= run_sort_lds<K, V, PAY>(),
-                "the run sort's LDS holds it");
-  const u32 tid = threadIdx.x, lane = tid & 63u;
-  const u32 tiles = (n + kSpillTile - 1) / kSpillTile;
-  const u32 nh = tiles < kSpillHistParts ? tiles : kSpillHistParts;
-  bool counted = false, free_ks = false;
-  u32 passes = P, next = 0;
-  if (tid == 0) next = atomicAdd(&sc->ticket[0], 1u);
-  while (true) {
-    __syncthreads();
-    if (tid == 0) {
-      sm.ticket = next;
-      next = atomicAdd(&sc->ticket[0], 1u);   // here by the time it is wanted
-    }
-    __syncthreads();
-    const u32 t = sm.ticket;
-    if (t < nh) {   // a part of the reading
-      for (u32 i = tid; i < P * 256u; i += kLocalNT) sm.hist[i] = 0;
-      __syncthreads();
-      for (u32 c0 = t * kSpillTile; c0 < n; c0 += nh * kSpillTile) {
-        K key[kSpillIPT];
-#pragma unroll
-        for (int k = 0; k < kSpillIPT; ++k) {
-          const u32 i = c0 + (u32)k * kLocalNT + tid;
-          key[k] = i < n ? ks[i] : K(0);
-        }
-#pragma unroll
-        for (int k = 0; k < kSpillIPT; ++k) {
-          const bool valid = c0 + (u32)k * kLocalNT + tid < n;
-          const u64 vm = wave_ballot(valid);
-          if (vm == 0) continue;   // uniform over the wave
-#pragma unroll
-          for (u32 p = 0; p < P; ++p) {
-            // a wave's items often share a digit: that of its first lane is
-            // counted once
-            const u32 d = digit_of<K, 8>(key[k], p * 8);
-            const u32 d0 = (u32)__builtin_amdgcn_readfirstlane((int)d);
-            const u64 same = wave_ballot(valid && d == d0);
-            if (lane == 0) atomicAdd(&sm.hist[p * 256 + d0], (u32)__popcll(same));
-            if (valid && d != d0) atomicAdd(&sm.hist[p * 256 + d], 1u);
-          }
-        }
-      }
-      __syncthreads();
-      for (u32 i = tid; i < P * 256u; i += kLocalNT)
-        if (sm.hist[i]) atomicAdd(&sc->hist[i], sm.hist[i]);
-      count_done(sc->done[0], t, nh);
-      continue;
-    }
-    if (!counted) {
-      if (!wait_done(sc->done[0], nh, sm, err)) return;
-      if (tid < P) sm.active[tid] = 1;
-      __syncthreads();
-      for (u32 i = tid; i < P * 256u; i += kLocalNT)
-        if (ld_agent32(&sc->hist[i]) == n) sm.active[i >> 8] = 0;
-      __syncthreads();
-      if (tid == 0) {
-        u32 a = 0;
-        for (u32 p = 0; p < P; ++p)
-          if (sm.active[p]) sm.active[a++] = p;
-        if (a == 0) sm.active[a++] = 0;   // all keys equal: one pass copies them
-        sm.nactive = a;
-      }
-      __syncthreads();
-      passes = sm.nactive;
-      counted = true;
-    }
-    const u32 a = (t - nh) / tiles, tile = (t - nh) % tiles;
-    if (a >= passes) return;
-    if (a > 0 && !wait_done(sc->done[a], tiles, sm, err)) return;
-    if (a > 0 && !free_ks) {
-      // the run workgroups have read their items out of ks
-      if (tid < 256u) (void)wait_run_length(status, 256u + tid, epoch, err);
-      free_ks = true;
-    }
-    const u32 p = sm.active[a];
-    const bool last = a + 1 == passes;
-    PassArgs<K, V> pa;
-    pa.kin = a & 1u ? xk : ks;
-    pa.vin = a & 1u ? xv : vs;
-    pa.kout = last ? ko : a & 1u ? ks : xk;
-    pa.vout = last ? vo : a & 1u ? vs : xv;
-    pa.n = n;
-    pa.shift = p * 8;
-    pa.hist_p = sc->hist + p * 256;
-    pa.status = ps;
-    pa.status_cl = ps_cl;
-    pa.epoch = epoch + 1 + a;
-    pa.err = err;
-    __syncthreads();
-    onesweep_tile<K, V, 8, kLocalNT, kSpillIPT, PAY, true>(pa, tile, tm);
-    if (!last) count_done(sc->done[a + 1], tile, tiles);
-  }
-}
-
-template <typename K, typename V, int PAY>
-__global__ __launch_bounds__(kLocalNT) void k_run_sort(K* ks, V* vs, K* ko, V* vo, K* xk, V* xv,
-                                                       const u32* __restrict__ toff, u64* status,
-                                                       u64* ps_cl, SpillCtl* sc, u32 epoch, u32 n,
-                                                       u32* err) {
-  extern __shared__ __align__(16) unsigned char lsm[];
-  LocalSortHead& h = *reinterpret_cast<LocalSortHead*>(lsm);
-  RunMap& m = *reinterpret_cast<RunMap*>(lsm + kLocalHeadBytes);
-  K* s_k = reinterpret_cast<K*>(lsm + kLocalHeadBytes + kRunMapBytes);
-  V* s_v = reinterpret_cast<V*>(lsm + kLocalHeadBytes + kRunMapBytes +
-                                (size_t)kLocalCap * sizeof(K));
-  constexpr int IPT = kLocalIPT;
-  const u32 tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
-  const u32 ntiles = (n + kSplitTile - 1) / kSplitTile;
-  if (blockIdx.x >= 256u) {
-    const u32 len = tid < 256u ? wait_run_length(status, tid, epoch, err) : 0u;
-    u32 nlong;
-    (void)block_exclusive_scan<kLocalNT>(len > kLocalCap ? 1u : 0u, h.tmp, &nlong);
-    if (nlong == 0) return;
-    __syncthreads();
-    spill_sort<K, V, PAY>(ks, vs, ko, vo, xk, xv, status, status + 512, ps_cl, sc, epoch, n, err,
-                          lsm);
-    return;
-  }
-  const u32 d = blockIdx.x;
-  const u32 cnt = load_run_map(toff, d, n, m, h.tmp, err);
-  if (tid == 0) st_agent(&status[d], pack_status(epoch, kFlagAgg, cnt));
-  __syncthreads();
-  if (cnt == 0 || cnt > kLocalCap) {   // (a long run: the whole batch is sorted above)
-    if (tid == 0) st_agent(&status[256u + d], pack_status(epoch, kFlagAgg, 1u));
-    return;
-  }
-  // the run lives in registers and LDS for all of its passes
-  K key[IPT], lo = key_max<K>(), hi = K(0);
-  V pay[IPT];
-  const u32 ipt = (cnt + kLocalNT - 1) / kLocalNT;
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-    key[k] = K(0);
-    if ((u32)k < ipt && li < cnt) {
-      const u32 src = run_src(m, ntiles, li);
-      key[k] = ks[src];
-      if (PAY != kPayNone) pay[k] = vs[src];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    if ((u32)k < ipt && w * 64u * ipt + (u32)k * 64u + lane < cnt) {
-      lo = key[k] < lo ? key[k] : lo;
-      hi = key[k] > hi ? key[k] : hi;
-    }
-  }
-  block_span<K, kLocalNT>(lo, hi, m.red);
-  if (tid == 0) st_agent(&status[256u + d], pack_status(epoch, kFlagAgg, 1u));   // all read
-  run_span_sort<K, V, PAY>(key, pay, cnt, ipt, lo, hi, h, s_k, s_v);
-  // the sum of the lengths published by the lower digits
-  u32 base;
-  (void)block_exclusive_scan<kLocalNT>(tid < d ? wait_run_length(status, tid, epoch, err) : 0u,
-                                       h.tmp, &base);
-  if (base + cnt > n) {   // published lengths inconsistent: never expected
+  const u32 base = lower_runs_total(status, d, epoch, err, h.tmp);
+  if (base + cnt > n) {
     if (tid == 0) atomicOr(err, 2u);
     return;
   }
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
-    if ((u32)k < ipt && li < cnt) {
-      ko[base + li] = key[k];
-      if (PAY != kPayNone) vo[base + li] = pay[k];
+  K* const okr = ko + base;
+  V* const ovr = vo + base;
+  u32 rank[IPT];
+  // A long run is usually one repeated key (skewed batches).  With X the key
+  // in the middle of the run: the items other than X are gathered in order
+  // into LDS; if they fit, they are sorted there and written around the
+  // block of X items, which keep their input order (stable).
+  {
+    const K X = ks[run_src(m, ntiles, cnt / 2)];
+    // the form only pays when X holds a good share of the run (a skewed
+    // batch); 64 evenly spaced samples decide, so a run of many distinct
+    // keys (a clustered batch) goes straight to the split below
+    if (tid < 64u) {
+      const u32 li = (u32)(((u64)cnt * tid) / 64u);
+      const u64 bm = wave_ballot(ks[run_src(m, ntiles, li)] == X);
+      if (tid == 0) m.red[1] = (u32)__popcll(bm);
     }
+    __syncthreads();
+    // (and only when the samples leave the other items room in LDS: a run
+    // of two or three hot keys goes to the split below at once)
+    const u32 same = m.red[1];
+    const bool try_dominant =
+        same >= 16u && (u64)cnt * (64u - same) <= (u64)kLocalCap * 58u;
+    // the X items' payloads go to the run's region of the extra buffer in
+    // input order as they are met, and are copied behind the smaller keys
+    // once their number is known
+    V* const xvr0 = vx + base;
+    u32 nrest = 0, xbase = 0;
+    bool fits = try_dominant;
+    K kand = ~K(0), kor = K(0);
+    for (u32 base0 = 0; fits && base0 < cnt; base0 += kLocalCap) {
+      bool rest[IPT], isx[IPT];
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base0 + w * 64u * IPT + (u32)k * 64u + lane;
+        const bool valid = li < cnt;
+        key[k] = X;
+        if (valid) {
+          const u32 src = run_src(m, ntiles, li);
+          key[k] = ks[src];
+          if (PAY != kPayNone) pay[k] = vs[src];
+        }
+        rest[k] = valid && key[k] != X;
+        isx[k] = valid && key[k] == X;
+        if (rest[k]) {
+          kand &= key[k];
+          kor |= key[k];
+        }
+      }
+      const u32 tot = local_class_rank(rest, rank, h);
+      if (nrest + tot > kLocalCap) {   // uniform: tot and nrest are workgroup-wide
+        fits = false;
+        break;
+      }
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        if (rest[k]) {
+          s_k[nrest + rank[k]] = key[k];
+          if (PAY != kPayNone) s_v[nrest + rank[k]] = pay[k];
+        }
+      }
+      nrest += tot;
+      // every valid item is X or not, and valid items are a prefix of the
+      // chunk, so an X item's rank among the chunk's X items is its position
+      // less the non-X items before it
+      if (PAY != kPayNone) {
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 pos = w * 64u * IPT + (u32)k * 64u + lane;
+          if (isx[k]) xvr0[xbase + pos - rank[k]] = pay[k];
+        }
+      }
+      const u32 valid_n = cnt - base0 < kLocalCap ? cnt - base0 : kLocalCap;
+      xbase += valid_n - tot;
+    }
+    if (fits) {
+      __syncthreads();
+      const u32 ipt = (nrest + kLocalNT - 1) / kLocalNT;
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+        if ((u32)k < ipt && li < nrest) {
+          key[k] = s_k[li];
+          if (PAY != kPayNone) pay[k] = s_v[li];
+        }
+      }
+      const u32 passes = varying_digits<K>(kand, kor, npass, m.red) & (nrest ? ~0u : 0u);
+      run_lds_passes<K, V, PAY>(key, pay, nrest, ipt, passes, h, s_k, s_v);
+      // items below X come first, then the X block, then the rest
+      u32 mine = 0;
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+        if ((u32)k < ipt && li < nrest && key[k] < X) ++mine;
+      }
+      u32 nlt;
+      (void)block_exclusive_scan<kLocalNT>(mine, h.tmp, &nlt);
+      const u32 neq = cnt - nrest;
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+        if ((u32)k < ipt && li < nrest) {
+          const u32 o = li < nlt ? li : li + neq;
+          okr[o] = key[k];
+          if (PAY != kPayNone) ovr[o] = pay[k];
+        }
+      }
+      // the X block (the payload copies were written by other threads before
+      // the barriers above); IPT loads in flight per thread before the stores
+      for (u32 i0 = 0; i0 < neq; i0 += kLocalNT * IPT) {
+        V xv[IPT];
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 i = i0 + (u32)k * kLocalNT + tid;
+          if (PAY != kPayNone && i < neq) xv[k] = xvr0[i];
+        }
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 i = i0 + (u32)k * kLocalNT + tid;
+          if (i < neq) {
+            okr[nlt + i] = X;
+            if (PAY != kPayNone) ovr[nlt + i] = xv[k];
+          }
+        }
+      }
+      if (rcut.mk != nullptr) {
+        __syncthreads();   // the run is in the output: search it there
+        block_cuts(base, cnt, okr);
+      }
+      return;
+    }
+    __syncthreads();
+  }
+  // A long run of many keys.  An AND/OR sweep finds the digits that vary
+  // inside it; the run is split stably on the highest of them into the extra
+  // buffer (one histogram sweep, one pass), which leaves 256 sub-runs in
+  // order.  Consecutive sub-runs are then taken in groups of up to kLocalCap
+  // items and sorted in registers and LDS on the digits that vary inside the
+  // group (the digits above the split one are constant in the run, so each
+  // group only needs its own order); a sub-run longer than kLocalCap is
+  // sorted by chunked global passes over its varying digits.  Everything is
+  // written at the group's or sub-run's place in the output.
+  K* const xkr = kx + base;
+  V* const xvr = vx + base;
+  // key of item i: from the split tiles (mapped) or a contiguous region
+  auto load_key = [&](bool mapped, const K* ik, u32 i) -> K {
+    return mapped ? ks[run_src(m, ntiles, i)] : ik[i];
+  };
+  // digits (below `below`) that vary among n items
+  auto sweep_vary = [&](bool mapped, const K* ik, u32 n, u32 below) -> u32 {
+    K kand = ~K(0), kor = K(0);
+    for (u32 base0 = 0; base0 < n; base0 += kLocalCap) {
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base0 + (u32)k * kLocalNT + tid;
+        if (li < n) {
+          const K kk = load_key(mapped, ik, li);
+          kand &= kk;
+          kor |= kk;
+        }
+      }
+    }
+    return varying_digits<K>(kand, kor, npass, m.red) & ((1u << below) - 1u);
+  };
+  // digit histograms (digits in `mask`) of n items into h.hist
+  auto sweep_hist = [&](bool mapped, const K* ik, u32 n, u32 mask) {
+    for (u32 i = tid; i < npass * 256u; i += kLocalNT)
+      if ((mask >> (i / 256u)) & 1u) (&h.hist[0][0])[i] = 0;
+    __syncthreads();
+    for (u32 base0 = 0; base0 < n; base0 += kLocalCap) {
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base0 + (u32)k * kLocalNT + tid;
+        key[k] = li < n ? load_key(mapped, ik, li) : K(0);
+      }
+      // Skewed runs repeat a few keys: the wave's most common case, the first
+      // valid lane's digit, is added once with its lane count, the other lanes
+      // add one each (LDS atomics on one address would serialise the wave).
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const bool valid = base0 + (u32)k * kLocalNT + tid < n;
+        const u64 vm = wave_ballot(valid);
+        if (vm == 0) continue;   // uniform across the wave
+        const int src = __ffsll((unsigned long long)vm) - 1;
+        for (u32 p = 0; p < npass; ++p) {
+          if (!((mask >> p) & 1u)) continue;   // uniform across the workgroup
+          const u32 dg = digit_of<K, 8>(key[k], p * 8u);
+          const u32 d0 = (u32)__shfl((int)dg, src, 64);
+          const u64 same = wave_ballot(valid && dg == d0);
+          if ((int)lane == src) atomicAdd(&h.hist[p][d0], (u32)__popcll(same));
+          if (valid && dg != d0) atomicAdd(&h.hist[p][dg], 1u);
+        }
+      }
+    }
+    __syncthreads();
+  };
+  // h.off = exclusive prefix of the histogram of digit p
+  auto digit_starts = [&](u32 p) {
+    const u32 cc = tid < 256u ? h.hist[p][tid] : 0u;
+    u32 dummy;
+    const u32 ex = block_exclusive_scan<kLocalNT>(cc, h.tmp, &dummy);
+    if (tid < 256u) h.off[tid] = ex;
+    __syncthreads();
+  };
+  // one stable counting pass on digit p over n items, chunk by chunk in
+  // order, from the tiles or (ik, iv) to (ok, ov); h.off holds the starts
+  auto chunk_pass = [&](bool mapped, const K* ik, const V* iv, u32 n, u32 p, K* ok, V* ov) {
+    const u32 shift = p * 8u;
+    for (u32 base0 = 0; base0 < n; base0 += kLocalCap) {
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base0 + w * 64u * IPT + (u32)k * 64u + lane;
+        key[k] = K(0);
+        if (li < n) {
+          const u32 src = mapped ? run_src(m, ntiles, li) : li;
+          key[k] = mapped ? ks[src] : ik[src];
+          if (PAY != kPayNone) pay[k] = mapped ? vs[src] : iv[src];
+        }
+      }
+      for (u32 i = tid; i < (kLocalNT / 64) * 256u; i += kLocalNT) (&h.wc[0][0])[i] = 0;
+      __syncthreads();
+      local_rank<K>(key, base0, n, shift, h, rank);
+      __syncthreads();
+      const u32 tot = local_wave_prefix(h);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < IPT; ++k) {
+        const u32 li = base0 + w * 64u * IPT + (u32)k * 64u + lane;
+        if (li < n) {
+          const u32 dg = digit_of<K, 8>(key[k], shift);
+          const u32 pos = h.off[dg] + h.wc[w][dg] + rank[k];
+          ok[pos] = key[k];
+          if (PAY != kPayNone) ov[pos] = pay[k];
+        }
+      }
+      __syncthreads();
+      if (tid < 256u) h.off[tid] += tot;
+      __syncthreads();
+    }
+  };
+  // n contiguous items copied in order
+  auto copy_items = [&](bool mapped, const K* ik, const V* iv, u32 n, K* ok, V* ov) {
+    for (u32 li = tid; li < n; li += kLocalNT) {
+      const u32 src = mapped ? run_src(m, ntiles, li) : li;
+      ok[li] = mapped ? ks[src] : ik[src];
+      if (PAY != kPayNone) ov[li] = mapped ? vs[src] : iv[src];
+    }
+  };
+
+  const u32 vary = sweep_vary(true, nullptr, cnt, npass);
+  if (vary == 0) {   // every key of the run is equal: copy it in order
+    copy_items(true, nullptr, nullptr, cnt, okr, ovr);
+    if (rcut.mk != nullptr) {
+      __syncthreads();
+      block_cuts(base, cnt, okr);
+    }
+    return;
+  }
+  const u32 ph = 31u - (u32)__clz(vary);   // highest varying digit
+  // 1. split on digit ph into the extra buffer; h.hist[ph] becomes the
+  //    sub-run starts (no later step writes that row)
+  sweep_hist(true, nullptr, cnt, 1u << ph);
+  digit_starts(ph);
+  if (tid < 256u) h.hist[ph][tid] = h.off[tid];
+  __syncthreads();
+  chunk_pass(true, nullptr, nullptr, cnt, ph, xkr, xvr);
+  // 2. the sub-runs in order
+  u32 v = 0;
+  while (v < 256u) {   // uniform: every thread reads the same LDS row
+    const u32 s0 = h.hist[ph][v];
+    u32 v2 = v;
+    while (v2 < 256u) {
+      const u32 e2 = v2 < 255u ? h.hist[ph][v2 + 1] : cnt;
+      if (e2 - s0 > kLocalCap) break;
+      ++v2;
+    }
+    if (v2 > v) {
+      // sub-runs v .. v2-1 fit LDS together: sort them there
+      const u32 n = (v2 < 256u ? h.hist[ph][v2] : cnt) - s0;
+      if (n > 0) {
+        const u32 ipt = (n + kLocalNT - 1) / kLocalNT;
+        K kand = ~K(0), kor = K(0);
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+          key[k] = K(0);
+          if ((u32)k < ipt && li < n) {
+            key[k] = xkr[s0 + li];
+            if (PAY != kPayNone) pay[k] = xvr[s0 + li];
+            kand &= key[k];
+            kor |= key[k];
+          }
+        }
+        const u32 passes = varying_digits<K>(kand, kor, npass, m.red) & ((2u << ph) - 1u);
+        run_lds_passes<K, V, PAY>(key, pay, n, ipt, passes, h, s_k, s_v);
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+          const u32 li = w * 64u * ipt + (u32)k * 64u + lane;
+          if ((u32)k < ipt && li < n) {
+            okr[s0 + li] = key[k];
+            if (PAY != kPayNone) ovr[s0 + li] = pay[k];
+          }
+        }
+        __syncthreads();
+      }
+      v = v2;
+      continue;
+    }
+    // sub-run v alone is longer than kLocalCap: chunked passes over the
+    // digits (below ph) that vary inside it, from the extra buffer,
+    // alternating with the output region, the last one into the output
+    const u32 n = (v < 255u ? h.hist[ph][v + 1] : cnt) - s0;
+    K* const sxk = xkr + s0;
+    V* const sxv = xvr + s0;
+    K* const sok = okr + s0;
+    V* const sov = ovr + s0;
+    const u32 vary2 = sweep_vary(false, sxk, n, ph);
+    const u32 np2 = (u32)__popc(vary2);
+    if (np2 > 0) sweep_hist(false, sxk, n, vary2);
+    u32 done = 0;
+    for (u32 p = 0; p < ph; ++p) {
+      if (!((vary2 >> p) & 1u)) continue;
+      digit_starts(p);
+      const bool to_out = (done & 1u) == 0u;   // the input is in the extra buffer
+      chunk_pass(false, to_out ? sxk : sok, to_out ? sxv : sov, n, p, to_out ? sok : sxk,
+                 to_out ? sov : sxv);
+      ++done;
+    }
+    if ((done & 1u) == 0u) {   // an even number of passes left it in the extra buffer
+      copy_items(false, sxk, sxv, n, sok, sov);
+      __syncthreads();
+    }
+    ++v;
+  }
+  if (rcut.mk != nullptr) {
+    __syncthreads();   // the run is in the output: search it there
+    block_cuts(base, cnt, okr);
   }
 }
 
@@ -1228,9 +1636,7 @@ struct SortScratch {
   u32 parity = 0;           // histogram slot of the next call
   u64 max_items = 0;        // capacity of the status array, in items
   u32* toff = nullptr;      // [kSplitMaxTiles][256] digit starts of the split tiles
-  u64* span = nullptr;      // [2 * kSpanParts] smallest and largest keys
-  SpillCtl* spill = nullptr;
-  void* xk = nullptr;       // [x_items] keys between passes of spill_sort (8-byte slots)
+  void* xk = nullptr;       // [x_items] keys of long runs between passes (8-byte slots)
   void* xv = nullptr;       // [x_items] their payloads (8-byte slots)
   u64 x_items = 0;
   // optional per-kernel timing hooks (family 0: histogram, 1: one pass or
@@ -1284,12 +1690,12 @@ inline u64 sort_cluster_words(u64 max_items) {
 
 // Host driver: sorts n pairs from (kin, vin) using ping-pong buffers
 // (k0, v0) / (k1, v1).  Returns which buffer holds the result (0 or 1).
-// ctl: control block whose update counters the sort may clear on its way;
-// *ctl_reset tells whether it did.
+// `reset_status` is called when the epoch counter wraps.
 template <typename K, typename V, int RB, int PAY>
 hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u32 n,
-                      SortScratch& s, hipStream_t st, int* result_buf, Ctl* ctl = nullptr,
-                      bool* ctl_reset = nullptr) {
+                      SortScratch& s, hipStream_t st, int* result_buf,
+                      const RunCuts<K>* cuts = nullptr, bool* cuts_done = nullptr) {
+  if (cuts_done) *cuts_done = false;
   constexpr int R = RadixShape<K, RB>::R;
   constexpr int P = RadixShape<K, RB>::P;
   if (n == 0) {
@@ -1298,35 +1704,24 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
   }
   if ((u64)n > s.max_items) return hipErrorInvalidValue;
   const u32 ntiles = (n + kSortTile - 1) / kSortTile;
-  if (RB == 8 && n <= kSplitMaxItems && s.toff && s.span && s.spill && n <= s.x_items) {
-    // three launches: key span, tile split, run sort
-    if (s.epoch >= (1u << 30) - 10u) {
+  if (RB == 8 && n <= kSplitMaxItems && s.toff && s.xk && s.xv && n <= s.x_items) {
+    // two launches: tile split on the top digit, then one workgroup per run
+    if (s.epoch >= (1u << 30) - 1u) {
       hipError_t e = hipMemsetAsync(s.status, 0, sort_status_words(s.max_items, RB) * sizeof(u64), st);
       if (e != hipSuccess) return e;
       e = hipMemsetAsync(s.status_cl, 0, sort_cluster_words(s.max_items) * sizeof(u64), st);
       if (e != hipSuccess) return e;
       s.epoch = 0;
     }
-    const u32 epoch = s.epoch + 1;
-    s.epoch += 9;   // the run lengths and up to eight passes
+    const u32 epoch = ++s.epoch;
     const u32 nsplit = (n + kSplitTile - 1) / kSplitTile;
-    const u32 nparts = (n + 2047) / 2048 < kSpanParts ? (n + 2047) / 2048 : kSpanParts;
-    {
-      SortTimer t(s, 0);
-      launch_timed(t.e0, t.e1, k_key_span<K>, dim3(nparts), dim3(256), 0, st, kin, n, s.span, s.spill,
-                   ctl);
-      if (ctl_reset) *ctl_reset = ctl != nullptr;
-      t.end();
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     {
       SortTimer t(s, 1);
       launch_timed(t.e0, t.e1, k_tile_split<K, V, PAY>, dim3(nsplit), dim3(kSplitNT), 0, st, kin,
-                   vin, k0, v0, s.toff, n, (const u64*)s.span, nparts);
+                   vin, k0, v0, s.toff, n, (u32)((P - 1) * RB));
       t.end();
     }
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr size_t lds = run_sort_lds<K, V, PAY>();
     static bool lds_set = false;
@@ -1338,16 +1733,17 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
     }
     {
       SortTimer t(s, 2);
-      // a workgroup per digit and, where a run can be long, as many for
-      // spill_sort (one per CU)
-      launch_timed(t.e0, t.e1, k_run_sort<K, V, PAY>, dim3(n > kLocalCap ? 512u : 256u),
-                   dim3(kLocalNT), (uint32_t)lds, st, k0, v0, k1, v1, (K*)s.xk, (V*)s.xv,
-                   (const u32*)s.toff, s.status, s.status_cl, s.spill, epoch, n, s.err);
+      RunCuts<K> rc{};
+      if (cuts) rc = *cuts;
+      launch_timed(t.e0, t.e1, k_run_sort<K, V, PAY>, dim3(R), dim3(kLocalNT), (uint32_t)lds, st,
+                   (const K*)k0, (const V*)v0, k1, v1, (K*)s.xk, (V*)s.xv, (const u32*)s.toff,
+                   s.status, epoch, (u32)(P - 1), n, s.err, rc);
       t.end();
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     *result_buf = 1;
+    if (cuts_done && cuts && cuts->mk) *cuts_done = true;
     return hipSuccess;
   }
   u32* hist = s.hist + (size_t)s.parity * (P * R);
@@ -1363,7 +1759,10 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  for (int p = 0; p < P; ++p) {
+  // Small batches with 8-bit digits: one onesweep pass on the top digit, then
+  // the runs are sorted on the other digits by k_local_sort (result in k1).
+  const bool local = RB == 8 && n <= kLocalMaxItems && ((P - 1) & 1) == 1;
+  for (int p = local ? P - 1 : 0; p < P; ++p) {
     if (s.epoch >= (1u << 30) - 1u) {
       e = hipMemsetAsync(s.status, 0, sort_status_words(s.max_items, RB) * sizeof(u64), st);
       if (e != hipSuccess) return e;
@@ -1372,10 +1771,11 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
       s.epoch = 0;
     }
     const u32 epoch = ++s.epoch;
-    const K* ki = p == 0 ? kin : ((p & 1) ? k0 : k1);
-    const V* vi = p == 0 ? vin : ((p & 1) ? v0 : v1);
-    K* ko = (p & 1) ? k1 : k0;
-    V* vo = (p & 1) ? v1 : v0;
+    const bool first = local || p == 0;
+    const K* ki = first ? kin : ((p & 1) ? k0 : k1);
+    const V* vi = first ? vin : ((p & 1) ? v0 : v1);
+    K* ko = (local || !(p & 1)) ? k0 : k1;
+    V* vo = (local || !(p & 1)) ? v0 : v1;
     PassArgs<K, V> pa;
     pa.kin = ki;
     pa.vin = vi;
@@ -1390,24 +1790,46 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
     pa.err = s.err;
     SortTimer t(s, 1);
     if constexpr (RB == 8) {
-      constexpr size_t lds = sizeof(BigPassSmem<K, V, PAY>);
-      static bool lds_set = false;
-      if (!lds_set && lds > 65536) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_onesweep_big<K, V, PAY>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (!local) {
+        constexpr size_t lds = sizeof(BigPassSmem<K, V, PAY>);
+        static bool lds_set = false;
+        if (!lds_set && lds > 65536) {
+          e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_onesweep_big<K, V, PAY>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+          if (e != hipSuccess) return e;
+          lds_set = true;
+        }
+        launch_timed(t.e0, t.e1, k_onesweep_big<K, V, PAY>,
+                     dim3((n + BigTile<K, PAY>::N - 1) / BigTile<K, PAY>::N), dim3(kBigNT), (uint32_t)lds, st, pa);
+        t.end();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
-        lds_set = true;
+        continue;
       }
-      launch_timed(t.e0, t.e1, k_onesweep_big<K, V, PAY>,
-                   dim3((n + BigTile<K, PAY>::N - 1) / BigTile<K, PAY>::N), dim3(kBigNT),
-                   (uint32_t)lds, st, pa);
-    } else {
-      launch_timed(t.e0, t.e1, k_onesweep<K, V, RB, kSortNT, kSortIPT, PAY>, dim3(ntiles),
-                   dim3(kSortNT), 0, st, pa);
     }
+    launch_timed(t.e0, t.e1, k_onesweep<K, V, RB, kSortNT, kSortIPT, PAY>, dim3(ntiles),
+                 dim3(kSortNT), 0, st, pa);
     t.end();
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+  }
+  if (local) {
+    constexpr size_t lds = local_sort_lds<K, V, PAY>();
+    static bool lds_set = false;
+    if (!lds_set) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_local_sort<K, V, PAY>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      lds_set = true;
+    }
+    SortTimer t(s, 2);
+    launch_timed(t.e0, t.e1, k_local_sort<K, V, PAY>, dim3(R), dim3(kLocalNT), (uint32_t)lds, st,
+                 k0, v0, k1, v1, (const u32*)(hist + (P - 1) * R), (u32)(P - 1), n, s.err);
+    t.end();
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    *result_buf = 1;
+    return hipSuccess;
   }
   *result_buf = ((P - 1) & 1) ? 1 : 0;
   return hipSuccess;
