@@ -95,12 +95,15 @@ def byte_model(wl, mkba, sizes_cap, kbytes=4, vbytes=4, rb=8, read_path="sorted"
     groups = read_path == "groups"
 
     fam = {}
-    # sorts per step: insert (key + value) and delete (key only), plus the
-    # three read batches (key + input position) on the sorted read path
-    pay = [vbytes, 0] if groups else [4, 4, 4, vbytes, 0]
+    # sorts per step: insert (key + value) and delete (key only), and the three
+    # read batches (key + input position) where they are sorted: 32-bit batches
+    # above 3 * 2^21 on the sorted read path
+    direct = not groups and (kbytes == 8 or m <= 3 << 21)
+    reads = [] if groups or direct else [4, 4, 4]
+    pay = reads + [vbytes, 0]
     # input payload read by the first launch: the read batches' input
     # positions are generated, not read
-    pay_in = [vbytes, 0] if groups else [0, 0, 0, vbytes, 0]
+    pay_in = [0] * len(reads) + [vbytes, 0]
     split = rb == 8 and m <= (1 << 21)
     if split:
         # batches of up to 2^21 keys with 8-bit digits: the tile split reads
@@ -147,6 +150,25 @@ def byte_model(wl, mkba, sizes_cap, kbytes=4, vbytes=4, rb=8, read_path="sorted"
         rng = read_bytes(lo, m * 4 + cnt * (kbytes + vbytes), cnt, hi_bytes=m * kbytes,
                          head_bytes=8)
         fam["group_read"] = look + succ + rng
+    elif direct:
+        # answered in input order: the batch, the directory, the header of each
+        # touched bucket, the distinct 64-byte blocks of node keys that hold a
+        # query's place, values read, outputs
+        start = np.concatenate([[0], np.cumsum(size_of)[:-1]])
+        per_block = 64 // kbytes
+
+        def direct_bytes(keys, extra_out, val_reads):
+            b = np.searchsorted(mkba, keys, side="left")
+            pos = np.searchsorted(build_sorted, keys) - start[b]
+            blk = np.minimum(pos, np.maximum(size_of[b] - 1, 0)) // per_block
+            nblk = np.unique(b.astype(np.int64) * 64 + blk).size
+            return (nb * kbytes + m * kbytes + np.unique(b).size * 16 + nblk * 64
+                    + val_reads * vbytes + extra_out)
+
+        look = direct_bytes(wl["lookup"], m * vbytes, hits)
+        succ = direct_bytes(wl["successor"], m * (kbytes + vbytes), m)
+        rng = direct_bytes(lo, m * (4 + kbytes) + cnt * (kbytes + vbytes), cnt)
+        fam["read_apply"] = look + succ + rng
     else:
         look = read_bytes(wl["lookup"], m * vbytes, hits)
         succ = read_bytes(wl["successor"], m * (kbytes + vbytes), m)
@@ -270,13 +292,19 @@ def grown_store_reads(args, wl, dev, bufs):
         stt = st.stats()
         nb, keys, live = stt["buckets"], stt["keys"], stt["live_nodes"]
         # algorithmic bytes of the bucket kernel per read batch: every
-        # maxBucket entry, the sorted batch, the header of every node of a
-        # touched bucket and its live keys in whole lines, values, outputs
+        # maxBucket entry, the batch, the header of every node of a touched
+        # bucket, values, outputs, and of the node keys the distinct 64-byte
+        # blocks (in input order) or the touched buckets' live keys in whole
+        # lines (sorted or grouped)
         touched = nb * (1.0 - np.exp(-m / nb))
         per_bucket = keys / nb
         chain = live / nb
         lines = np.ceil(per_bucket * 4 / 128.0) * 128.0 + (chain - 1) * 64.0
         base = nb * 4 + m * 8 + touched * (16 * chain + lines)
+        if args.read_path == "sorted" and m <= 3 << 21:
+            blocks = keys / 16
+            base = (nb * 4 + m * 4 + touched * 16 * chain
+                    + blocks * (1.0 - np.exp(-m / blocks)) * 64)
         outb = {"lookup": m * 4 + 0.9 * m * 4, "successor": m * 8 + m * 4,
                 "range16": m * 4 + m * 4 + m * 8}
         rows = {}

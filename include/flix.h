@@ -340,10 +340,10 @@ const char* flix_last_error(void);
  * the dispatch itself stamps (no marker packets between kernels);
  * flix_kernel_time returns the summed milliseconds and launch count since the
  * last reset.  Each family is one kernel: "sort_hist" (digit histograms),
- * "sort_pass" (one onesweep pass), "sort_local" (the per-run sort of batches
- * of up to 2^22 keys after their top-digit pass), "read_apply"
- * (lookup/successor/range bucket kernel), "read_cuts" (merge-path cuts of the
- * read shares), "slices" (update slice discovery and node budget),
+ * "sort_pass" (one onesweep pass or tile split), "sort_local" (the per-run sort
+ * of batches of up to 2^22 keys, or the sort by counting of short updates),
+ * "read_apply" (lookup/successor/range kernel), "read_cuts" (merge-path cuts of
+ * the shares of read batches that are sorted), "slices" (update slice discovery and node budget),
  * "insert_apply", "delete_apply".  flix_set_timing(s, enable) times every
  * family (enable != 0) or none; flix_set_timing_only(s, family) times only
  * the named family, leaving the other launches uninstrumented (FLIX_EINVAL
