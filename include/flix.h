@@ -19,7 +19,10 @@
  *    KEY_MAX are ordinary keys.
  *  - Pointers named d_* are device pointers owned by the caller.  They must
  *    stay valid until the work enqueued on `stream` has completed.  Inputs are
- *    never modified; the library sorts copies in its own scratch memory.
+ *    never modified through their own pointers; an output of a read may overlap
+ *    the keys it answers (a range's d_lo), by any distance: the batch is then
+ *    answered from a copy of its keys.  No other two buffers of a call may
+ *    overlap where one of them is an output.
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All
  *    calls are asynchronous and stream-ordered unless marked "synchronizes".
  *    A store may be used from one host thread at a time; when the caller

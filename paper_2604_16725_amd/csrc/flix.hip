@@ -574,8 +574,16 @@ int read_batch(flix_store* s, int op, const void* keys, u64 n, void* out_k, void
                const void* hi, u32* counts, u32 maxpq, hipStream_t st) {
   if (s->cfg.read_path == FLIX_READ_GROUPS && s->grp_ok && n <= (u64)kGroupTilesMax * kPartTile)
     return read_batch_groups<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
-  if (n <= direct_max<K>(op))
+  if (n <= direct_max<K>(op)) {
+    if (answers_over_keys<K>(op, keys, n, out_k, out_v, counts, maxpq)) {
+      hipLaunchKernelGGL((k_copy_keys<K>), dim3((u32)std::min<u64>((n + 255) / 256, 2048)),
+                         dim3(256), 0, st, (const K*)keys, (u32)n, (K*)s->bk[0], (const K*)nullptr,
+                         0u, (K*)nullptr);
+      HIP_TRY(hipGetLastError());
+      keys = s->bk[0];
+    }
     return read_direct<K>(s, op, (const K*)keys, n, out_k, out_v, hi, counts, maxpq, st);
+  }
   int r;
   int rc = sort_batch<K>(s, keys, nullptr, n, kPayIndex, st, &r);
   if (rc) return rc;
@@ -947,7 +955,7 @@ int epoch_prepare_rb(EpochSlot* es, const flix_epoch* e, hipStream_t st) {
   es->r_direct = e->n_range <= direct_max<K>(kOpRange);
   const u32 cl = es->l_direct ? (u32)e->n_lookup : 0u, cr = es->r_direct ? (u32)e->n_range : 0u;
   if (cl + cr)
-    hipLaunchKernelGGL((k_epoch_copy<K>), dim3(std::min<u32>((cl + cr + 255) / 256, 2048)),
+    hipLaunchKernelGGL((k_copy_keys<K>), dim3(std::min<u32>((cl + cr + 255) / 256, 2048)),
                        dim3(256), 0, st, (const K*)e->d_lookup_keys, cl, (K*)es->lk[0],
                        (const K*)e->d_range_lo, cr, (K*)es->rk[0]);
   if (!es->l_direct)

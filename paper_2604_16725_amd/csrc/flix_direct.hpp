@@ -457,6 +457,37 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
     if (live[q] && bad[q]) atomicCAS(a.err, 0u, kErrInternal);
 }
 
+// Whether some answers of a batch are stored over keys that another wave has
+// still to read: an output overlaps the keys (ranges: lo).  A point read answered
+// in place is safe, its lane has read its key by then; nothing else is, so such a
+// batch is answered from a copy of its keys (the sorted forms always do that).
+template <typename K>
+__host__ __device__ inline bool answers_over_keys(int op, const void* keys, u64 n,
+                                                  const void* out_k, const void* out_v,
+                                                  const void* counts, u32 maxpq) {
+  const u64 k0 = (u64)keys, k1 = k0 + n * sizeof(K);
+  const bool range = op == kOpRange;
+  auto over = [&](const void* p, u64 bytes) {
+    const u64 o = (u64)p;
+    return p && (range || o != k0) && o < k1 && k0 < o + bytes;
+  };
+  const u64 bytes = (range ? n * maxpq : n) * sizeof(K);
+  return over(out_v, bytes) || (op != kOpLookup && over(out_k, bytes)) ||
+         (range && over(counts, n * sizeof(u32)));
+}
+
+// Key lists kept in scratch: both read lists of an epoch until its apply, or the
+// one list of a batch whose answers overlap its keys.
+template <typename K>
+__global__ __launch_bounds__(256) void k_copy_keys(const K* __restrict__ a, u32 na,
+                                                    K* __restrict__ ao, const K* __restrict__ b,
+                                                    u32 nb, K* __restrict__ bo) {
+  for (u32 i = blockIdx.x * 256 + threadIdx.x; i < na + nb; i += gridDim.x * 256) {
+    if (i < na) ao[i] = a[i];
+    else bo[i - na] = b[i - na];
+  }
+}
+
 // The top directory level into LDS.
 template <typename K, int NT>
 __device__ __forceinline__ void load_top(const DirTree<K>& t, K* s_top) {

@@ -323,8 +323,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     if (!is_update) {
+      // answers over keys still to be read: the batch gets a copy of its keys in
+      // the sort's scratch (which no batch since the last barrier uses)
+      const bool copied =
+          answers_over_keys<K>((int)d.op, d.keys, n, d.out_k, d.out_v, d.counts, d.maxpq);
+      if (copied) {
+        for (u32 i = blk * 256 + threadIdx.x; i < n; i += G * 256) a.bk[0][i] = ((const K*)d.keys)[i];
+        if (grid_sync(dc, G)) return;
+      }
       ReadArgs<K> ra;
-      ra.skeys = (const K*)d.keys;
+      ra.skeys = copied ? a.bk[0] : (const K*)d.keys;
       ra.sidx = nullptr;
       ra.m = n;
       ra.mkba = mkba;
@@ -362,6 +370,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       if (any && a.tstamp) {   // the last wave to end leaves its time
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if ((threadIdx.x & 63u) == 0) atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
+      }
+      if (copied) {   // the scratch is free for the next batch
+        if (grid_sync(dc, G)) return;
+        pend = bi + 1;
       }
       continue;
     }

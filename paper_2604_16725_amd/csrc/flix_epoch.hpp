@@ -81,17 +81,6 @@ __global__ __launch_bounds__(kCompactNT) void k_fold_scatter(
   }
 }
 
-// The read lists of an epoch, kept for its apply.
-template <typename K>
-__global__ __launch_bounds__(256) void k_epoch_copy(const K* __restrict__ a, u32 na,
-                                                    K* __restrict__ ao, const K* __restrict__ b,
-                                                    u32 nb, K* __restrict__ bo) {
-  for (u32 i = blockIdx.x * 256 + threadIdx.x; i < na + nb; i += gridDim.x * 256) {
-    if (i < na) ao[i] = a[i];
-    else bo[i - na] = b[i - na];
-  }
-}
-
 // k_fold_count, the scans and k_fold_scatter in one workgroup, for an update
 // list of at most kSmallMax entries: counts[0] upserts, counts[1] deletes.
 template <typename K>
