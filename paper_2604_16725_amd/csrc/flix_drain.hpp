@@ -158,7 +158,7 @@ __device__ __forceinline__ bool grid_sync(DrainCtl* c, u32 nblocks) {
   return s_abort != 0;
 }
 
-template <typename K, int RB, int GL, int KPL>
+template <typename K, int RB>
 struct DrainSmemSize {
   static constexpr size_t hist = sizeof(HistSmem<K, RB>);
   static constexpr size_t pass_val = sizeof(OnesweepSmem<K, K, RB, kDrainSortNT, kDrainSortIPT, kPayValue>);
@@ -234,7 +234,7 @@ __device__ __forceinline__ bool drain_read(const ReadArgs<K>& ra, const DirTree<
   return any;
 }
 
-template <typename K, int RB, int GL, int KPL>
+template <typename K, int RB, int GL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_drain(DrainArgs<K> a) {
   extern __shared__ unsigned char smem[];
   __shared__ UpdShared s_upd;

@@ -1,6 +1,6 @@
 // The persistent drain kernel (flix_drain.hpp) in a translation unit of its
-// own, instantiated for both key widths, both digit widths and every
-// lane-group shape the autotuner sweeps.
+// own, instantiated for both key widths, both digit widths and every lane-group
+// width of its update phases.
 #include <algorithm>
 
 #include "flix_launch.hpp"
@@ -8,12 +8,12 @@
 namespace flix {
 namespace {
 
-template <typename K, int RB, int GL, int KPL>
+template <typename K, int RB, int GL>
 hipError_t drain_t(const DrainLaunch& d, hipStream_t st) {
-  size_t shm = DrainSmemSize<K, RB, GL, KPL>::fixed();
+  size_t shm = DrainSmemSize<K, RB>::fixed();
   const size_t upd = (size_t)(256 / GL) * 2 * d.lds_items * sizeof(K);
   if (upd > shm) shm = upd;
-  auto kfn = k_drain<K, RB, GL, KPL>;
+  auto kfn = k_drain<K, RB, GL>;
   hipError_t e;
   if (*d.grid == 0 || *d.shm != shm) {
     if (shm > 65536 &&
@@ -60,20 +60,10 @@ hipError_t drain_t(const DrainLaunch& d, hipStream_t st) {
 
 template <typename K, int RB>
 hipError_t drain_rb(const DrainLaunch& d, hipStream_t st) {
-  const u32 kpl = std::max<u32>(1u, d.cap / d.gl);
-  switch (d.gl * 100 + kpl) {
-    case 1601: return drain_t<K, RB, 16, 1>(d, st);
-    case 1602: return drain_t<K, RB, 16, 2>(d, st);
-    case 1604: return drain_t<K, RB, 16, 4>(d, st);
-    case 1608: return drain_t<K, RB, 16, 8>(d, st);
-    case 1616: return drain_t<K, RB, 16, 16>(d, st);
-    case 3201: return drain_t<K, RB, 32, 1>(d, st);
-    case 3202: return drain_t<K, RB, 32, 2>(d, st);
-    case 3204: return drain_t<K, RB, 32, 4>(d, st);
-    case 3208: return drain_t<K, RB, 32, 8>(d, st);
-    case 6401: return drain_t<K, RB, 64, 1>(d, st);
-    case 6402: return drain_t<K, RB, 64, 2>(d, st);
-    default: return drain_t<K, RB, 64, 4>(d, st);
+  switch (d.gl) {
+    case 16: return drain_t<K, RB, 16>(d, st);
+    case 32: return drain_t<K, RB, 32>(d, st);
+    default: return drain_t<K, RB, 64>(d, st);
   }
 }
 
