@@ -119,7 +119,13 @@ int flix_create(const flix_config* cfg, void* stream, flix_store** out);
  * key of a group is its maxBucket).  Duplicate keys: last occurrence wins.  n
  * is not limited by max_batch.  A value equal to NOT_FOUND -> FLIX_EINVAL and
  * the previous contents are kept.  Pool too small for a fixed pool_bytes ->
- * FLIX_ENOMEM.  Synchronizes. */
+ * FLIX_ENOMEM, contents kept.  Device memory running out -> FLIX_ENOMEM: a pool
+ * of another size is allocated beside the old one, so the contents are kept
+ * unless the old pool had to be freed to make room; then the store is empty, or,
+ * when it could not get a pool of any size, every call but flix_bulk_load,
+ * flix_status and flix_destroy returns FLIX_ENOMEM until a load succeeds (a
+ * drain graph replayed meanwhile does nothing; flix_status then reports
+ * FLIX_EINTERNAL).  Synchronizes. */
 int flix_bulk_load(flix_store* s, const void* d_keys, const void* d_vals, uint64_t n,
                    void* stream);
 

@@ -7,6 +7,7 @@
 #include <mutex>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/flix.h"
@@ -252,34 +253,87 @@ int alloc_split_scratch(SortScratch& ss, u64 items) {
 int ensure_sort_capacity(flix_store* s, u64 items) {
   if (items <= s->ss.max_items) return FLIX_OK;
   HIP_TRY(hipDeviceSynchronize());
+  // the new words are had before the old ones go, so a failure changes nothing
+  const u64 words = sort_status_words(items, 8);  // sized for the widest digit
+  const u64 cwords = sort_cluster_words(items);
+  u64 *status = nullptr, *status_cl = nullptr;
+  int rc;
+  if ((rc = dev_alloc(&status, words * sizeof(u64))) ||
+      (rc = dev_alloc(&status_cl, cwords * sizeof(u64)))) {
+    dev_free(&status);
+    return rc;
+  }
+  hipError_t e = hipMemset(status, 0, words * sizeof(u64));
+  if (e == hipSuccess) e = hipMemset(status_cl, 0, cwords * sizeof(u64));
+  if (e != hipSuccess) {
+    dev_free(&status);
+    dev_free(&status_cl);
+    return note_hip_error(e, "sort scratch", __LINE__);
+  }
   dev_free(&s->ss.status);
-  u64 words = sort_status_words(items, 8);  // sized for the widest digit
-  int rc = dev_alloc(&s->ss.status, words * sizeof(u64));
-  if (rc) return rc;
-  HIP_TRY(hipMemset(s->ss.status, 0, words * sizeof(u64)));
   dev_free(&s->ss.status_cl);
-  u64 cwords = sort_cluster_words(items);
-  rc = dev_alloc(&s->ss.status_cl, cwords * sizeof(u64));
-  if (rc) return rc;
-  HIP_TRY(hipMemset(s->ss.status_cl, 0, cwords * sizeof(u64)));
+  s->ss.status = status;
+  s->ss.status_cl = status_cl;
   s->ss.epoch = 0;
   s->ss.max_items = items;
   return alloc_split_scratch(s->ss, items);
 }
 
-int alloc_pool(flix_store* s, u32 pool) {
-  dev_free(&s->hdr);
-  dev_free(&s->nkeys);
-  dev_free(&s->nvals);
-  dev_free(&s->free_ids);
-  s->pool = 0;
+// Arrays of a node pool that is not (or no longer) the store's.
+struct PoolMem {
+  NodeHdr* hdr = nullptr;
+  void* nkeys = nullptr;
+  void* nvals = nullptr;
+  u32* free_ids = nullptr;
+  u32 nodes = 0;
+};
+void pool_free(PoolMem* m) {
+  dev_free(&m->hdr);
+  dev_free(&m->nkeys);
+  dev_free(&m->nvals);
+  dev_free(&m->free_ids);
+  m->nodes = 0;
+}
+// All of a pool's arrays or none of them.
+int pool_alloc(const flix_store* s, u32 nodes, PoolMem* m) {
   int rc;
-  if ((rc = dev_alloc(&s->hdr, (u64)pool * sizeof(NodeHdr)))) return rc;
-  if ((rc = dev_alloc(&s->nkeys, (u64)pool * s->cap * s->ksz))) return rc;
-  if ((rc = dev_alloc(&s->nvals, (u64)pool * s->cap * s->ksz))) return rc;
-  if ((rc = dev_alloc(&s->free_ids, (u64)pool * sizeof(u32)))) return rc;
-  s->pool = pool;
+  if ((rc = dev_alloc(&m->hdr, (u64)nodes * sizeof(NodeHdr))) ||
+      (rc = dev_alloc(&m->nkeys, (u64)nodes * s->cap * s->ksz)) ||
+      (rc = dev_alloc(&m->nvals, (u64)nodes * s->cap * s->ksz)) ||
+      (rc = dev_alloc(&m->free_ids, (u64)nodes * sizeof(u32)))) {
+    pool_free(m);
+    return rc;
+  }
+  m->nodes = nodes;
   return FLIX_OK;
+}
+// The store takes *m; *m receives what it held.
+void pool_swap(flix_store* s, PoolMem* m) {
+  std::swap(s->hdr, m->hdr);
+  std::swap(s->nkeys, m->nkeys);
+  std::swap(s->nvals, m->nvals);
+  std::swap(s->free_ids, m->free_ids);
+  std::swap(s->pool, m->nodes);
+}
+// A pool for which there was no room beside the old one: the old one goes first,
+// and the contents with it (s->nb = 0 until a layout is built).  Where the device
+// has no room even then, nothing changes (an allocator hook cannot be asked); when
+// the new pool is refused all the same, the store gets its old size back, or is
+// left without a pool.
+int pool_instead(flix_store* s, u32 nodes) {
+  size_t avail = 0, total = 0;
+  if (!s->pool || (!g_alloc.alloc && hipMemGetInfo(&avail, &total) == hipSuccess &&
+                   (u64)nodes * (node_bytes(s) + 4) > avail + (u64)s->pool * (node_bytes(s) + 4)))
+    return FLIX_ENOMEM;
+  PoolMem old, now;
+  pool_swap(s, &old);
+  const u32 was = old.nodes;
+  s->nb = 0;
+  pool_free(&old);
+  const int rc = pool_alloc(s, nodes, &now);
+  if (rc && pool_alloc(s, was, &now)) return rc;
+  pool_swap(s, &now);
+  return rc;
 }
 
 // Entries of the read-share cut list for batches of up to n keys over nb buckets.
@@ -291,35 +345,50 @@ u64 group_tiles(u64 n) {
   return t < kGroupTilesMax ? t : kGroupTilesMax;
 }
 
-// Directory arrays for nb buckets.  The new arrays are allocated before the
-// old ones are freed, so a failed allocation leaves the directory as it was.
-int alloc_dir(flix_store* s, u32 nb) {
+// Directory arrays for `buckets` buckets that are not (or no longer) the store's.
+struct DirMem {
+  void* mkba = nullptr;
+  void* dir = nullptr;
+  u32* bnodes = nullptr;
+  u64* occ = nullptr;
+  u32* cuts = nullptr;
+  u32 buckets = 0;
+};
+void dir_free(DirMem* d) {
+  dev_free(&d->mkba);
+  dev_free(&d->dir);
+  dev_free(&d->bnodes);
+  dev_free(&d->occ);
+  dev_free(&d->cuts);
+  d->buckets = 0;
+}
+// All of a directory's arrays or none of them; nothing where the store's own
+// arrays hold nb buckets.
+int dir_alloc(const flix_store* s, u32 nb, DirMem* d) {
   if (nb <= s->nb_alloc) return FLIX_OK;
-  void* mk = nullptr;
-  u32* bn = nullptr;
-  u64* oc = nullptr;
-  u32* cu = nullptr;
-  void* dr = nullptr;
   int rc;
-  if ((rc = dev_alloc(&mk, dir_round(nb) * s->ksz)) ||
-      (rc = dev_alloc(&dr, s->kb == 32 ? dir_entries<u32>(nb) * 4 : dir_entries<u64>(nb) * 8)) || (rc = dev_alloc(&bn, (u64)nb * sizeof(u32))) ||
-      (rc = dev_alloc(&oc, occ_words(nb) * sizeof(u64))) ||
-      (rc = dev_alloc(&cu, (cuts_for(s->max_batch, nb) * sizeof(u32))))) {
-    dev_free(&mk); dev_free(&bn); dev_free(&oc); dev_free(&cu); dev_free(&dr);
+  if ((rc = dev_alloc(&d->mkba, dir_round(nb) * s->ksz)) ||
+      (rc = dev_alloc(&d->dir, s->kb == 32 ? dir_entries<u32>(nb) * 4 : dir_entries<u64>(nb) * 8)) ||
+      (rc = dev_alloc(&d->bnodes, (u64)nb * sizeof(u32))) ||
+      (rc = dev_alloc(&d->occ, occ_words(nb) * sizeof(u64))) ||
+      (rc = dev_alloc(&d->cuts, cuts_for(s->max_batch, nb) * sizeof(u32)))) {
+    dir_free(d);
     return rc;
   }
-  dev_free(&s->mkba);
-  dev_free(&s->bnodes);
-  dev_free(&s->cuts);
-  dev_free(&s->occ);
-  dev_free(&s->dir);
-  s->mkba = mk;
-  s->dir = dr;
-  s->bnodes = bn;
-  s->occ = oc;
-  s->cuts = cu;
-  s->nb_alloc = nb;
+  d->buckets = nb;
   return FLIX_OK;
+}
+// The store's directory is replaced by *d (if it holds one); the layout that the
+// old one described must not be used any more.
+void dir_take(flix_store* s, DirMem* d) {
+  if (!d->buckets) return;
+  std::swap(s->mkba, d->mkba);
+  std::swap(s->dir, d->dir);
+  std::swap(s->bnodes, d->bnodes);
+  std::swap(s->occ, d->occ);
+  std::swap(s->cuts, d->cuts);
+  std::swap(s->nb_alloc, d->buckets);
+  dir_free(d);
 }
 
 u32 auto_pool(const flix_store* s, u64 nbuckets) {
@@ -1072,6 +1141,14 @@ int epoch_apply_t(flix_store* s, EpochSlot* es, const flix_epoch* e, hipStream_t
   return FLIX_OK;
 }
 
+// FLIX_ENOMEM for a store whose last load ended without a pool.
+int check_layout(const flix_store* s) {
+  if (s->nb) return FLIX_OK;
+  std::snprintf(g_last_error, sizeof(g_last_error),
+                "the store has no node pool since a bulk load ran out of memory");
+  return FLIX_ENOMEM;
+}
+
 int epoch_validate(flix_store* s, uint32_t slot, const flix_epoch* e) {
   if (!s) return FLIX_ESTATE;
   if (!e || slot >= 2) return FLIX_EINVAL;
@@ -1082,7 +1159,7 @@ int epoch_validate(flix_store* s, uint32_t slot, const flix_epoch* e) {
   if (e->n_range && (!e->d_range_lo || !e->d_range_hi || !e->d_range_counts)) return FLIX_EINVAL;
   if (e->n_range && e->range_max && !e->d_range_vals && !e->d_range_keys) return FLIX_EINVAL;
   if (e->n_update && (!e->d_update_keys || !e->d_update_vals)) return FLIX_EINVAL;
-  return FLIX_OK;
+  return check_layout(s);
 }
 
 // ---- bulk load --------------------------------------------------------------
@@ -1229,13 +1306,15 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
   return FLIX_OK;
 }
 
-// Sorts straight into the pool's own free part when there is room (the auto
-// pool has: twice the nodes the keys fill): the pairs are sorted behind the
-// nodes they are then cut into, so a load allocates nothing.  The previous
-// contents are overwritten once the values have been checked and the node
-// count is known to suffice; until then they are kept.  (A load of 2^26 u32
-// pairs and a dump of them took 7.4 ms, 1.8 of it in allocating and freeing six
-// buffers, and 45 when the host had been idle; now 2.5.)
+// Sorts straight into the free part of the pool that the pairs are to fill when
+// there is room (an auto-sized pool has: twice the nodes the keys fill): the
+// pairs are sorted behind the nodes they are then cut into, so a load into a
+// pool of its size allocates nothing.  (A load of 2^26 u32 pairs and a dump of
+// them took 7.4 ms, 1.8 of it in allocating and freeing six buffers, and 45 when
+// the host had been idle; now 2.5.)
+// Memory of another size is had before the old contents go: a new pool stands
+// beside the old one until the layout is built.  Only where both do not fit does
+// the old one go first (pool_instead).
 template <typename K>
 int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream_t st) {
   if (n > 0xFFFFFFF0ull) return FLIX_EINVAL;
@@ -1249,51 +1328,66 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     HIP_TRY(hipMemcpyAsync(&err, &s->ctl->call_err, sizeof(u32), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (err) return FLIX_EINVAL;
+  } else {
+    HIP_TRY(hipStreamSynchronize(st));
   }
-  // sorted, deduplicated pairs: in the pool or in temporary buffers
-  K *tk0 = nullptr, *tk1 = nullptr, *tv0 = nullptr, *tv1 = nullptr, *ck = nullptr, *cv = nullptr;
-  u32* bsum = nullptr;
-  u64 nd = 0;
-  bool in_pool = false, keep_pool = false;
-  int rc = FLIX_OK;
-  auto cleanup = [&]() {
-    if (!in_pool) { dev_free(&tk0); dev_free(&tk1); dev_free(&tv0); dev_free(&tv1); }
-    dev_free(&ck); dev_free(&cv); dev_free(&bsum);
-  };
   auto pool_for = [&](u64 nodes) {
     return s->cfg.pool_bytes ? (u32)std::min<u64>(s->cfg.pool_bytes / node_bytes(s), 0xFFFFFFF0ull)
                              : auto_pool(s, nodes);
   };
+  // where the pairs are sorted: the store's pool, a new pool or temporary buffers
+  enum { kStore, kStage, kTemp } where = kTemp;
+  PoolMem stage, old;   // the new pool; the one that it replaced
+  DirMem dir;
+  K *tk[2] = {}, *tv[2] = {};   // the sort's two buffers
+  u32* bsum = nullptr;
+  int rc = FLIX_OK;
+  auto leave = [&](int r) {
+    if (where == kTemp) { dev_free(&tk[0]); dev_free(&tk[1]); dev_free(&tv[0]); dev_free(&tv[1]); }
+    dev_free(&bsum);
+    pool_free(&stage);
+    pool_free(&old);
+    dir_free(&dir);
+    return r;
+  };
+  u64 nd = 0;
   const K *sk = nullptr, *sv = nullptr;   // the pairs the layout is built from
   if (n) {
     if ((rc = ensure_sort_capacity(s, n))) return rc;
     const u64 nodes = (n + s->fill - 1) / s->fill;   // at most: duplicates shrink it
-    const u32 pool = nodes <= 0xFFFFFF00ull ? pool_for(nodes) : 0;
+    const u32 want = nodes <= 0xFFFFFF00ull ? pool_for(nodes) : 0;
     const u64 nr = (n + 15) / 16 * 16;               // whole 64-byte lines
-    if (nodes <= pool && ((u64)pool - nodes) * s->cap >= 2 * nr) {
-      // whatever can fail for want of memory comes before the old contents go
-      if ((rc = alloc_dir(s, (u32)nodes))) return rc;
-      if (pool != s->pool) {
-        HIP_TRY(hipStreamSynchronize(st));
-        if ((rc = alloc_pool(s, pool))) return rc;
+    const bool room = nodes <= want && ((u64)want - nodes) * s->cap >= 2 * nr;
+    if (room && dir_alloc(s, (u32)nodes, &dir) == FLIX_OK) {
+      if (want == s->pool) {
+        s->nb = 0;   // the old contents go
+        where = kStore;
+      } else if (pool_alloc(s, want, &stage) == FLIX_OK) {
+        where = kStage;
+      } else {
+        rc = pool_instead(s, want);
+        if (rc == FLIX_OK) where = kStore;
+        else if (s->nb == 0) return leave(rc);
       }
-      in_pool = true;
-      tk0 = (K*)s->nkeys + nodes * s->cap;
-      tk1 = tk0 + nr;
-      tv0 = (K*)s->nvals + nodes * s->cap;
-      tv1 = tv0 + nr;
-    } else if ((rc = dev_alloc(&tk0, n * sizeof(K))) || (rc = dev_alloc(&tk1, n * sizeof(K))) ||
-               (rc = dev_alloc(&tv0, n * sizeof(K))) || (rc = dev_alloc(&tv1, n * sizeof(K)))) {
-      cleanup();
-      return rc;
+      if (where == kTemp) dir_free(&dir);
+    }
+    if (where == kTemp) {
+      if ((rc = dev_alloc(&tk[0], n * sizeof(K))) || (rc = dev_alloc(&tk[1], n * sizeof(K))) ||
+          (rc = dev_alloc(&tv[0], n * sizeof(K))) || (rc = dev_alloc(&tv[1], n * sizeof(K))))
+        return leave(rc);
+    } else {
+      tk[0] = (K*)(where == kStore ? s->nkeys : stage.nkeys) + nodes * s->cap;
+      tv[0] = (K*)(where == kStore ? s->nvals : stage.nvals) + nodes * s->cap;
+      tk[1] = tk[0] + nr;
+      tv[1] = tv[0] + nr;
     }
     int r = 0;
     hipError_t e = s->rb == 4
-        ? radix_sort<K, K, 4, kPayValue>(keys, vals, tk0, tv0, tk1, tv1, (u32)n, s->ss, st, &r)
-        : radix_sort<K, K, 8, kPayValue>(keys, vals, tk0, tv0, tk1, tv1, (u32)n, s->ss, st, &r);
-    if (e != hipSuccess) { cleanup(); return note_hip_error(e, "bulk load sort", __LINE__); }
-    sk = r ? tk1 : tk0;
-    sv = r ? tv1 : tv0;
+        ? radix_sort<K, K, 4, kPayValue>(keys, vals, tk[0], tv[0], tk[1], tv[1], (u32)n, s->ss, st, &r)
+        : radix_sort<K, K, 8, kPayValue>(keys, vals, tk[0], tv[0], tk[1], tv[1], (u32)n, s->ss, st, &r);
+    if (e != hipSuccess) return leave(note_hip_error(e, "bulk load sort", __LINE__));
+    sk = tk[r];
+    sv = tv[r];
     // superseded keys; without any, the sorted pairs are the contents
     u32 dups = 0;
     e = hipMemsetAsync(&s->ctl->scan_total, 0, sizeof(u32), st);
@@ -1302,57 +1396,55 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess ||
         (e = hipMemcpyAsync(&dups, &s->ctl->scan_total, sizeof(u32), hipMemcpyDeviceToHost, st)) !=
             hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess) {
-      cleanup();
-      return note_hip_error(e, "bulk load duplicates", __LINE__);
-    }
+        (e = hipStreamSynchronize(st)) != hipSuccess)
+      return leave(note_hip_error(e, "bulk load duplicates", __LINE__));
     nd = n - dups;
-    if (dups) {
-      // compacted in buffers of their own when the pool is to change its size
-      // (or holds no scratch), else in the sort's other buffers
-      const u64 nodes_d = (nd + s->fill - 1) / s->fill;
+    if (dups) {   // compacted in the sort's other buffers
       const u32 nblk = (u32)((n + kCompactTile - 1) / kCompactTile);
-      K *ok = r ? tk0 : tk1, *ov = r ? tv0 : tv1;
-      u32* bs = s->free_ids;   // rebuilt with the layout; n / 2048 <= nodes <= pool
-      if (!in_pool) {
-        if ((rc = dev_alloc(&bsum, (u64)nblk * sizeof(u32)))) { cleanup(); return rc; }
+      u32* bs = where == kStore ? s->free_ids : stage.free_ids;   // n / 2048 <= nodes <= pool
+      if (where == kTemp) {
+        if ((rc = dev_alloc(&bsum, (u64)nblk * sizeof(u32)))) return leave(rc);
         bs = bsum;
-      } else if (pool_for(nodes_d) != s->pool) {
-        if (dev_alloc(&ck, nd * sizeof(K)) == FLIX_OK && dev_alloc(&cv, nd * sizeof(K)) == FLIX_OK) {
-          ok = ck;
-          ov = cv;
-        } else {
-          dev_free(&ck);   // no room for the move: the larger pool stays
-          keep_pool = true;
-        }
       }
       hipLaunchKernelGGL((k_compact_count<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, n, bs);
       hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, st, bs, nblk, &s->ctl->scan_total);
       hipLaunchKernelGGL((k_compact_scatter<K>), dim3(nblk), dim3(kCompactNT), 0, st, sk, sv, n, bs,
-                         ok, ov);
-      if ((e = hipGetLastError()) != hipSuccess) { cleanup(); return note_hip_error(e, "bulk load compaction", __LINE__); }
-      sk = ok;
-      sv = ov;
+                         tk[r ^ 1], tv[r ^ 1]);
+      if ((e = hipGetLastError()) != hipSuccess)
+        return leave(note_hip_error(e, "bulk load compaction", __LINE__));
+      sk = tk[r ^ 1];
+      sv = tv[r ^ 1];
     }
   }
-  u64 nbk = nd ? (nd + s->fill - 1) / s->fill : 1;
-  if (nbk > 0xFFFFFF00ull) { cleanup(); return FLIX_EINVAL; }
+  const u64 nbk = nd ? (nd + s->fill - 1) / s->fill : 1;
+  if (nbk > 0xFFFFFF00ull) return leave(FLIX_EINVAL);
   const u32 pool = pool_for(nbk);
-  if (nbk > pool) { cleanup(); return FLIX_ENOMEM; }
-  if (pool != s->pool && !keep_pool) {   // (never with the pairs still in the old pool)
-    HIP_TRY(hipStreamSynchronize(st));
-    if ((rc = alloc_pool(s, pool))) { cleanup(); return rc; }
+  if (nbk > pool) return leave(FLIX_ENOMEM);
+  if (where == kTemp && (rc = dir_alloc(s, (u32)nbk, &dir))) return leave(rc);
+  // the pool that the layout is built in; where the pairs lie stays until it is
+  if (stage.nodes == pool) {
+    std::swap(old, stage);
+    pool_swap(s, &old);
+  } else if (pool != s->pool) {
+    PoolMem m;
+    if (pool_alloc(s, pool, &m) == FLIX_OK) {
+      pool_swap(s, &m);
+      old = m;
+    } else if (stage.nodes) {   // duplicates made the pool smaller: the larger one stays
+      std::swap(old, stage);
+      pool_swap(s, &old);
+    } else if (where == kTemp && (rc = pool_instead(s, pool))) {
+      return leave(rc);
+    }
   }
-  if ((rc = alloc_dir(s, (u32)nbk))) { cleanup(); return rc; }
-  if ((rc = build_layout<K>(s, sk, sv, nd, (u32)nbk, st))) { cleanup(); return rc; }
-  hipError_t e1 = hipGetLastError();
-  if (!in_pool || ck) {
-    const hipError_t e2 = hipStreamSynchronize(st);
-    cleanup();
-    if (e2 != hipSuccess) return note_hip_error(e2, "bulk load sync", __LINE__);
+  dir_take(s, &dir);
+  rc = build_layout<K>(s, sk, sv, nd, (u32)nbk, st);
+  if (rc) return leave(rc);
+  if (where != kStore || old.nodes || stage.nodes) {
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return leave(note_hip_error(e, "bulk load sync", __LINE__));
   }
-  if (e1 != hipSuccess) return note_hip_error(e1, "bulk load kernels", __LINE__);
-  return FLIX_OK;
+  return leave(FLIX_OK);
 }
 
 // Bucket groups of the read path for the current directory: their shape,
@@ -1360,7 +1452,7 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
 template <typename K>
 int rebuild_groups(flix_store* s, hipStream_t st) {
   u32 g = 1, bpg = 1;
-  s->grp_ok = s->cfg.read_path == FLIX_READ_GROUPS && group_shape(s->nb, &g, &bpg) && s->gpre &&
+  s->grp_ok = s->cfg.read_path == FLIX_READ_GROUPS && s->nb != 0 && group_shape(s->nb, &g, &bpg) && s->gpre &&
               s->split && s->gtot;
   s->ngrp = g;
   s->bpg = bpg;
@@ -1375,11 +1467,14 @@ int rebuild_groups(flix_store* s, hipStream_t st) {
   return FLIX_OK;
 }
 
-// Bulk load, then the layout record and the bucket groups, also after a
-// failure part way (the directory or the pool may have been reallocated).
+// Bulk load, then the layout record and the bucket groups, also after a failure
+// part way (the pool may have been replaced).  A failed load that had to give up
+// the old contents leaves an empty store, or one without a pool (s->nb == 0),
+// which every call but a load, flix_status and flix_destroy refuses.
 template <typename K>
 int bulk_load_t(flix_store* s, const K* keys, const K* vals, u64 n, hipStream_t st) {
   const int rc = bulk_load_body<K>(s, keys, vals, n, st);
+  if (rc && !s->nb && s->pool && s->nb_alloc) (void)build_layout<K>(s, nullptr, nullptr, 0, 1, st);
   const int rp = publish_layout(s, st);
   const int rg = rebuild_groups<K>(s, st);
   const hipError_t e = hipStreamSynchronize(st);
@@ -1412,8 +1507,9 @@ int restructure_t(flix_store* s, hipStream_t st, u64* before, u64* after) {
       return rc;
     }
   }
-  // the old layout is no longer read: the directory may be replaced
-  if ((rc = alloc_dir(s, (u32)nbk))) { cleanup(); return rc; }
+  DirMem dir;
+  if ((rc = dir_alloc(s, (u32)nbk, &dir))) { cleanup(); return rc; }
+  dir_take(s, &dir);   // the old layout is no longer read
   rc = build_layout<K>(s, ck, cv, n, (u32)nbk, st);
   const hipError_t e = hipStreamSynchronize(st);
   cleanup();
@@ -1433,7 +1529,7 @@ int check_args(flix_store* s, u64 n, std::initializer_list<const void*> ptrs) {
   if (n > s->max_batch) return FLIX_EINVAL;
   for (const void* p : ptrs)
     if (!p) return FLIX_EINVAL;
-  return FLIX_OK;
+  return check_layout(s);
 }
 
 void destroy_all(flix_store* s) {
@@ -1529,7 +1625,7 @@ int drain_validate(flix_store* s, const flix_batch* h, u32 nbatch) {
     if (keyed && !b.d_keys_out) return FLIX_EINVAL;
     if (b.op == FLIX_OP_RANGE && !b.d_counts) return FLIX_EINVAL;
   }
-  return FLIX_OK;
+  return check_layout(s);
 }
 
 static_assert(sizeof(flix_batch) == sizeof(DrainBatch), "descriptor layouts must match");
@@ -1669,6 +1765,7 @@ int flix_bulk_load(flix_store* s, const void* d_keys, const void* d_vals, uint64
 int flix_restructure(flix_store* s, uint64_t* nodes_before, uint64_t* nodes_after, void* stream) {
   (void)hipGetLastError();  // drop errors left by other code on this thread
   if (!s) return FLIX_ESTATE;
+  if (const int c = check_layout(s)) return c;
   return s->kb == 32 ? restructure_t<u32>(s, S(stream), nodes_before, nodes_after)
                      : restructure_t<u64>(s, S(stream), nodes_before, nodes_after);
 }
@@ -1736,6 +1833,7 @@ int flix_range(flix_store* s, const void* d_lo, const void* d_hi, uint64_t n,
 int flix_size(flix_store* s, uint64_t* out, void* stream) {
   if (!s) return FLIX_ESTATE;
   if (!out) return FLIX_EINVAL;
+  if (const int c = check_layout(s)) return c;
   u64 v = 0;
   HIP_TRY(hipMemcpyAsync(&v, &s->ctl->nkeys, sizeof(u64), hipMemcpyDeviceToHost, S(stream)));
   HIP_TRY(hipStreamSynchronize(S(stream)));
@@ -1777,6 +1875,7 @@ int flix_dump(flix_store* s, void* d_keys_out, void* d_vals_out, uint64_t capaci
   (void)hipGetLastError();  // drop errors left by other code on this thread
   if (!s) return FLIX_ESTATE;
   if (!out_n) return FLIX_EINVAL;
+  if (const int c = check_layout(s)) return c;
   hipStream_t st = S(stream);
   u64 n = 0;
   HIP_TRY(hipMemcpyAsync(&n, &s->ctl->nkeys, sizeof(u64), hipMemcpyDeviceToHost, st));
@@ -1793,6 +1892,7 @@ int flix_dump_noalloc(flix_store* s, void* d_keys_out, void* d_vals_out, uint64_
   (void)hipGetLastError();  // drop errors left by other code on this thread
   if (!s) return FLIX_ESTATE;
   if (!out_n) return FLIX_EINVAL;
+  if (const int c = check_layout(s)) return c;
   if (s->nb > kNoAllocBuckets) {
     std::snprintf(g_last_error, sizeof(g_last_error),
                   "flix_dump_noalloc: %u buckets, at most %llu supported", s->nb,
@@ -1822,6 +1922,7 @@ int flix_dump_noalloc(flix_store* s, void* d_keys_out, void* d_vals_out, uint64_
 int flix_check(flix_store* s, void* stream) {
   (void)hipGetLastError();  // drop errors left by other code on this thread
   if (!s) return FLIX_ESTATE;
+  if (const int c = check_layout(s)) return c;
   hipStream_t st = S(stream);
   u32* mark = nullptr;
   u32* err = nullptr;
@@ -1866,6 +1967,7 @@ int flix_check(flix_store* s, void* stream) {
 int flix_get_stats(flix_store* s, flix_stats* out, void* stream) {
   if (!s) return FLIX_ESTATE;
   if (!out) return FLIX_EINVAL;
+  if (const int c = check_layout(s)) return c;
   Ctl hctl;
   HIP_TRY(hipMemcpyAsync(&hctl, s->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, S(stream)));
   HIP_TRY(hipStreamSynchronize(S(stream)));
@@ -1880,6 +1982,7 @@ int flix_get_stats(flix_store* s, flix_stats* out, void* stream) {
 int flix_copy_layout(flix_store* s, void* h_mkba, void* h_hdr, void* h_keys, void* h_vals,
                      uint32_t* h_free, uint64_t* h_free_top, void* stream) {
   if (!s) return FLIX_ESTATE;
+  if (const int c = check_layout(s)) return c;
   hipStream_t st = S(stream);
   if (h_mkba) HIP_TRY(hipMemcpyAsync(h_mkba, s->mkba, (u64)s->nb * s->ksz, hipMemcpyDeviceToHost, st));
   if (h_hdr) HIP_TRY(hipMemcpyAsync(h_hdr, s->hdr, (u64)s->pool * sizeof(NodeHdr), hipMemcpyDeviceToHost, st));
