@@ -95,6 +95,7 @@ struct flix_store {
   u32 nb = 0;          // buckets
   u32 nb_alloc = 0;    // capacity of the directory arrays
   u32 pool = 0;        // nodes
+  bool dup_load = false;   // the last load made its pool smaller for duplicate keys
   void* mkba = nullptr;
   NodeHdr* hdr = nullptr;
   void* nkeys = nullptr;
@@ -1312,6 +1313,11 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
 // pool of its size allocates nothing.  (A load of 2^26 u32 pairs and a dump of
 // them took 7.4 ms, 1.8 of it in allocating and freeing six buffers, and 45 when
 // the host had been idle; now 2.5.)
+// A load that expects duplicates to shrink its pool (the one before it did) takes
+// temporary buffers of half that size instead: the pool it would sort in is not
+// the one it ends with (2^20 u64 pairs over 0.43 * 2^20 keys, loaded again and
+// again: 1530 us with the pool sized twice a load, 620 in a pool beside the old
+// one, 390 with temporary buffers; 100,000 pairs 800, 186, 122).
 // Memory of another size is had before the old contents go: a new pool stands
 // beside the old one until the layout is built.  Only where both do not fit does
 // the old one go first (pool_instead).
@@ -1362,6 +1368,8 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
       if (want == s->pool) {
         s->nb = 0;   // the old contents go
         where = kStore;
+      } else if (s->dup_load) {
+        // temporary buffers
       } else if (pool_alloc(s, want, &stage) == FLIX_OK) {
         where = kStage;
       } else {
@@ -1438,6 +1446,7 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     }
   }
   dir_take(s, &dir);
+  s->dup_load = n && pool_for((n + s->fill - 1) / s->fill) != pool;
   rc = build_layout<K>(s, sk, sv, nd, (u32)nbk, st);
   if (rc) return leave(rc);
   if (where != kStore || old.nodes || stage.nodes) {

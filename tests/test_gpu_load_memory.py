@@ -142,3 +142,25 @@ def test_fixed_pool_too_small_keeps_the_contents():
     assert _refused(lambda: s.bulk_load(to_dev(big), to_dev(w.values_for(big, 3, 32))))
     assert_same_contents(s, o, 32)
     s.close()
+
+
+@pytest.mark.parametrize("kb", [32, 64])
+def test_loads_with_and_without_duplicates_in_turn(kb):
+    """The pool ends at the size a fresh store's would, whatever was loaded before."""
+    from oracle.oracle import Oracle
+    from paper_2604_16725_amd.flix import Store
+    s = Store(key_bits=kb, capacity=64, max_batch=1 << 12)
+    for i, (n, dup) in enumerate([(60000, 4), (60000, 4), (60000, 1), (60000, 1), (60000, 2),
+                                  (9000, 3), (9000, 3), (0, 1), (60000, 4)]):
+        k = np.tile(w.KeySpace(kb, 3 + i).build(max(n // dup, 1)), dup)[:n]
+        v = w.values_for(k, 4, kb) ^ np.arange(k.size).astype(k.dtype) % 64
+        log(f"kb={kb} n={n} dup={dup}")
+        o = Oracle(kb)
+        o.bulk_load(k, v)
+        fresh = Store(key_bits=kb, capacity=64, max_batch=1 << 12)
+        for x in (s, fresh):
+            x.bulk_load(to_dev(k), to_dev(v))
+            assert_same_contents(x, o, kb)
+        assert s.stats() == fresh.stats()
+        fresh.close()
+    s.close()
