@@ -1230,8 +1230,7 @@ int dump_launch(flix_store* s, void* ko, void* vo, u64 capacity, u32* tot, u32* 
     a.pool = s->pool;
     a.out_k = (K*)ko;
     a.out_v = (K*)vo;
-    hipLaunchKernelGGL((k_dump_copy<K>), dim3(std::min<u32>((nb + 255) / 256, 65535)), dim3(256), 0,
-                       st, a, (const u32*)off, capacity);
+    launch_dump_copy<K>(a, off, capacity, st);
   };
   if (s->kb == 32) copy(u32(0));
   else copy(u64(0));
@@ -1240,7 +1239,7 @@ int dump_launch(flix_store* s, void* ko, void* vo, u64 capacity, u32* tot, u32* 
 }
 
 // Every pair in ascending key order into ko / vo (at most `capacity` of them):
-// per-bucket totals, their scan, then one wave per bucket copies its chain.
+// per-bucket totals, their scan, then every chain is copied to its place.
 // Synchronizes st.
 int dump_body(flix_store* s, void* ko, void* vo, u64 capacity, hipStream_t st) {
   const u32 nb = s->nb;

@@ -1,6 +1,8 @@
 // Initial build (bulk load), contents dump and the device invariant checker.
 #pragma once
 
+#include <algorithm>
+
 #include "flix_device.hpp"
 #include "flix_direct.hpp"
 #include "flix_occ.hpp"
@@ -265,36 +267,122 @@ __global__ void k_scan_addback(u32* __restrict__ out, u32 n, const u32* __restri
   if (i < n) out[i] += bsum[blockIdx.x];
 }
 
-// A wave takes 64 buckets and copies their nodes together, one link of every
-// chain per step, as runs of one flattened list: 2^20 half-full nodes of 64
-// u32 pairs took 312 us with a wave per bucket (each waiting for its header,
-// offset and pairs in turn), 258 us so.
+__device__ __forceinline__ u64 readlane64(u64 v, int l) {
+  return ((u64)(u32)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+         (u32)__builtin_amdgcn_readlane((int)(u32)v, l);
+}
+
+// Runs of up to 256 pairs in lanes i to i + 7 (c pairs from slot src on to position
+// dst), copied by the whole wave.  All lanes of the wave call, i is uniform.
 template <typename K>
+__device__ __forceinline__ void wave_copy_eight(const ReadArgs<K>& a, u64 src, u64 dst, u32 c,
+                                                u32 i) {
+  constexpr u32 U = 8;
+  bool more = true;
+  for (u32 p = threadIdx.x & 63u; more; p += 64) {
+    K k[U], v[U];
+    more = false;
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) {
+      const u32 cu = (u32)__builtin_amdgcn_readlane((int)c, (int)(i + u));
+      const u64 from = readlane64(src, (int)(i + u));
+      if (p < cu) {
+        k[u] = a.nkeys[from + p];
+        v[u] = a.nvals[from + p];
+      }
+      more = more || cu > (p & ~63u) + 64;   // uniform
+    }
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) {
+      const u64 to = readlane64(dst, (int)(i + u));
+      if (p < (u32)__builtin_amdgcn_readlane((int)c, (int)(i + u))) {
+        a.out_k[to + p] = k[u];
+        a.out_v[to + p] = v[u];
+      }
+    }
+  }
+}
+
+// A wave takes bpw (1 to 64) buckets, a lane each, and copies their nodes link by
+// link: eight together (bpw <= 8), or, FLAT, as runs of one flattened list.  Chains
+// that go on after kDumpLinks links, when they are few, are followed one by one,
+// 64 links at a time.
+constexpr u32 kDumpLinks = 4;
+constexpr u32 kDumpFew = 4;
+
+template <typename K, bool FLAT>
 __global__ __launch_bounds__(256) void k_dump_copy(ReadArgs<K> a, const u32* __restrict__ off,
-                                                   u64 out_cap) {
+                                                   u64 out_cap, u32 bpw) {
   const u32 wave = (blockIdx.x * 256 + threadIdx.x) >> 6, nw = gridDim.x * 4u;
   const u32 lane = threadIdx.x & 63u;
-  for (u64 b0 = (u64)wave * 64; b0 < a.nb; b0 += (u64)nw * 64) {
+  auto head = [&](u32 node) { return *reinterpret_cast<const u64*>(&a.hdr[node].size); };
+  // pairs of a node to copy to position o
+  auto count = [&](u64 w, u64 o) {
+    const u32 sz = (u32)w < a.cap ? (u32)w : a.cap;
+    const u64 room = o < out_cap ? out_cap - o : 0;
+    return sz < room ? sz : (u32)room;
+  };
+  for (u64 b0 = (u64)wave * bpw; b0 < a.nb; b0 += (u64)nw * bpw) {
     const u64 b = b0 + lane;
-    u32 node = b < a.nb ? (u32)b : kNil;
-    u64 o = b < a.nb ? off[b] : 0;
-    u32 steps = 0;
-    while (wave_ballot(node < a.pool)) {
+    u32 node = lane < bpw && b < a.nb ? (u32)b : kNil;
+    u64 o = node != kNil ? off[b] : 0;
+    u32 steps = 0;   // nodes seen, the same for every chain still followed
+    u64 m = wave_ballot(node < a.pool);
+    while (m != 0 && (steps < kDumpLinks || (u32)__popcll(m) > kDumpFew)) {
       u32 c = 0, next = kNil;
       const u64 src = node < a.pool ? (u64)node * a.cap : 0;
       const u64 dst = o;
+      ++steps;
       if (node < a.pool) {
-        const u64 w = *reinterpret_cast<const u64*>(&a.hdr[node].size);
-        const u32 sz = (u32)w < a.cap ? (u32)w : a.cap;
-        const u64 room = o < out_cap ? out_cap - o : 0;
-        c = sz < room ? sz : (u32)room;
-        o += sz;
-        next = ++steps < a.pool ? (u32)(w >> 32) : kNil;
+        const u64 w = head(node);
+        c = count(w, o);
+        o += (u32)w < a.cap ? (u32)w : a.cap;
+        next = steps < a.pool ? (u32)(w >> 32) : kNil;
       }
-      wave_copy_runs<K>(a, src, dst, c);
+      if (FLAT) wave_copy_runs<K>(a, src, dst, c);
+      else wave_copy_eight<K>(a, src, dst, c, 0);
       node = next;
+      m = wave_ballot(node < a.pool);
+    }
+    for (; m; m &= m - 1) {
+      const int l = (int)ctz64(m);
+      u32 cur = (u32)__builtin_amdgcn_readlane((int)node, l);
+      u64 at = readlane64(o, l);
+      u32 seen = steps;
+      while (cur < a.pool) {
+        u64 src = 0, dst = 0;   // link i of this round in lane i
+        u32 c = 0, n = 0;
+        for (; n < 64 && cur < a.pool; ++n) {
+          const u64 w = head(cur);
+          if (lane == n) {
+            src = (u64)cur * a.cap;
+            dst = at;
+            c = count(w, at);
+          }
+          at += (u32)w < a.cap ? (u32)w : a.cap;
+          cur = ++seen < a.pool ? (u32)(w >> 32) : kNil;
+        }
+        for (u32 i = 0; i < n; i += 8) wave_copy_eight<K>(a, src, dst, c, i);
+      }
     }
   }
+}
+
+// Nodes of at most 16 slots leave most lanes of a wave idle when they are copied
+// one by one, so 64 of them go as one list (2^22 u32 keys in nodes of 8 slots: 150
+// us against 185; of 16, 145 to 170 either way; of 32, 210).  Larger nodes go eight
+// at a time (2^26 keys, 128 slots: 330 us against 400; 432 with a wave per bucket).
+// In a store of few buckets a wave takes fewer, down to one, as long as the chip
+// then has fewer than 32 waves per CU.
+template <typename K>
+void launch_dump_copy(const ReadArgs<K>& a, const u32* off, u64 out_cap, hipStream_t st) {
+  const bool flat = a.cap <= 16;
+  u32 bpw = 1;
+  while (bpw < (flat ? 64u : 8u) && (u64)bpw * 8192u < a.nb) bpw <<= 1;
+  const u32 per = 4 * bpw;
+  const dim3 g(std::min<u32>((a.nb + per - 1) / per, 65535)), b(256);
+  if (flat) hipLaunchKernelGGL((k_dump_copy<K, true>), g, b, 0, st, a, off, out_cap, bpw);
+  else hipLaunchKernelGGL((k_dump_copy<K, false>), g, b, 0, st, a, off, out_cap, bpw);
 }
 
 // ---------------------------------------------------------------------------
