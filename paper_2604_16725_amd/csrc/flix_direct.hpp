@@ -462,7 +462,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
 // in place is safe, its lane has read its key by then; nothing else is, so such a
 // batch is answered from a copy of its keys (the sorted forms always do that).
 template <typename K>
-__host__ __device__ inline bool answers_over_keys(int op, const void* keys, u64 n,
+inline bool answers_over_keys(int op, const void* keys, u64 n,
                                                   const void* out_k, const void* out_v,
                                                   const void* counts, u32 maxpq) {
   const u64 k0 = (u64)keys, k1 = k0 + n * sizeof(K);

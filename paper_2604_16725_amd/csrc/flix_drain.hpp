@@ -211,6 +211,15 @@ __device__ __forceinline__ bool spans_conflict(const BatchSpans& a, const BatchS
   }
   return c;
 }
+// answers_over_keys of a read batch with these spans.
+__device__ __forceinline__ bool spans_over_keys(const BatchSpans& s, bool range) {
+  bool c = false;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    c = c || ((range || s.out[i][0] != s.in[0][0]) && s.out[i][0] < s.in[0][1] &&
+              s.in[0][0] < s.out[i][1]);
+  return c;
+}
 
 // Read batch of a drain: units of Q * 64 queries go to the waves of the grid
 // in turn, from wave `rot` on.  Returns whether this wave had any.
@@ -310,15 +319,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // where it reads what a batch since the last barrier writes, or writes
     // what one reads or writes.  One lane compares with each of those batches
     // (at most 64).
+    bool copied = false;   // answers over keys still to be read
     {
       const u32 npend = bi - pend;
+      const BatchSpans own = batch_spans<K>(d, a.max_batch);
+      copied = !is_update && spans_over_keys(own, d.op == kOpRange);
       bool wait = npend >= 64u;
       if (!wait && npend > 0) {
         const u32 lane = threadIdx.x & 63u;
         bool c = false;
         if (lane < npend)
-          c = spans_conflict(batch_spans<K>(a.batches[pend + lane], a.max_batch),
-                             batch_spans<K>(d, a.max_batch));
+          c = spans_conflict(batch_spans<K>(a.batches[pend + lane], a.max_batch), own);
         wait = wave_ballot(c) != 0;
       }
       if (wait) {
@@ -327,11 +338,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     if (!is_update) {
-      // answers over keys still to be read: the batch gets a copy of its keys in
-      // the sort's scratch (which no batch since the last barrier uses)
-      const bool copied =
-          answers_over_keys<K>((int)d.op, d.keys, n, d.out_k, d.out_v, d.counts, d.maxpq);
-      if (copied) {
+      if (copied) {   // to the sort's scratch, which no batch since the last barrier uses
         for (u32 i = blk * 256 + threadIdx.x; i < n; i += G * 256) a.bk[0][i] = ((const K*)d.keys)[i];
         if (grid_sync(dc, G)) return;
       }
