@@ -267,13 +267,9 @@ __global__ void k_scan_addback(u32* __restrict__ out, u32 n, const u32* __restri
   if (i < n) out[i] += bsum[blockIdx.x];
 }
 
-__device__ __forceinline__ u64 readlane64(u64 v, int l) {
-  return ((u64)(u32)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
-         (u32)__builtin_amdgcn_readlane((int)(u32)v, l);
-}
-
-// Runs of up to 256 pairs in lanes i to i + 7 (c pairs from slot src on to position
-// dst), copied by the whole wave.  All lanes of the wave call, i is uniform.
+// Runs of up to a node's keys in lanes i to i + 7 (c pairs from slot src on to
+// position dst), copied by the whole wave.  All lanes of the wave call, i is
+// uniform.
 template <typename K>
 __device__ __forceinline__ void wave_copy_eight(const ReadArgs<K>& a, u64 src, u64 dst, u32 c,
                                                 u32 i) {
@@ -284,8 +280,8 @@ __device__ __forceinline__ void wave_copy_eight(const ReadArgs<K>& a, u64 src, u
     more = false;
 #pragma unroll
     for (u32 u = 0; u < U; ++u) {
-      const u32 cu = (u32)__builtin_amdgcn_readlane((int)c, (int)(i + u));
-      const u64 from = readlane64(src, (int)(i + u));
+      const u32 cu = wave_read(c, (int)(i + u));
+      const u64 from = wave_read(src, (int)(i + u));
       if (p < cu) {
         k[u] = a.nkeys[from + p];
         v[u] = a.nvals[from + p];
@@ -294,8 +290,8 @@ __device__ __forceinline__ void wave_copy_eight(const ReadArgs<K>& a, u64 src, u
     }
 #pragma unroll
     for (u32 u = 0; u < U; ++u) {
-      const u64 to = readlane64(dst, (int)(i + u));
-      if (p < (u32)__builtin_amdgcn_readlane((int)c, (int)(i + u))) {
+      const u64 to = wave_read(dst, (int)(i + u));
+      if (p < wave_read(c, (int)(i + u))) {
         a.out_k[to + p] = k[u];
         a.out_v[to + p] = v[u];
       }
@@ -346,8 +342,8 @@ __global__ __launch_bounds__(256) void k_dump_copy(ReadArgs<K> a, const u32* __r
     }
     for (; m; m &= m - 1) {
       const int l = (int)ctz64(m);
-      u32 cur = (u32)__builtin_amdgcn_readlane((int)node, l);
-      u64 at = readlane64(o, l);
+      u32 cur = wave_read(node, l);
+      u64 at = wave_read(o, l);
       u32 seen = steps;
       while (cur < a.pool) {
         u64 src = 0, dst = 0;   // link i of this round in lane i

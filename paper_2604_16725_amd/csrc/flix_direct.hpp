@@ -271,6 +271,97 @@ __device__ __forceinline__ void wave_copy_runs(const ReadArgs<K>& a, u64 src, u6
   }
 }
 
+__device__ __forceinline__ u32 wave_read(u32 v, int l) {
+  return (u32)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ u64 wave_read(u64 v, int l) {
+  return ((u64)(u32)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+         (u32)__builtin_amdgcn_readlane((int)(u32)v, l);
+}
+
+// Queries per wave (q or fewer) of a batch of m ranges on `waves` resident waves.
+// A range's results are copied by its wave (16 ranges of 2^18 results in one wave
+// took four times as long as in a wave each); but idle lanes cost, too, so a wave
+// takes fewer only while the batch then needs at most half the waves (20,000
+// ranges of 16 keys on 8192: 20 us with 4 per wave, 28 with 2).
+__host__ __device__ inline u32 range_queries_per_wave(u32 q, u32 m, u32 waves) {
+  while (q > 1 && (u64)(q / 2) * waves >= 2ull * m) q >>= 1;
+  return q;
+}
+
+// A range that the whole wave finishes (all fields uniform).
+template <typename K>
+struct WaveRange {
+  K hi;
+  u32 b, next;   // bucket of the last node counted, and that node's link
+  u32 cnt;       // keys counted
+  bool end, bad;
+};
+
+// The next up to 64 nodes of the range, one per lane (c keys of *node, 0 in the
+// lanes that are left): heads of the buckets that follow, a lane each, as far as
+// they lie within the range, and links of a chain.
+template <typename K>
+__device__ __forceinline__ u32 wave_gather(const ReadArgs<K>& a, const OccLevels& occ,
+                                           WaveRange<K>& r, u32* node) {
+  const u32 lane = threadIdx.x & 63u;
+  u32 c = 0, n = 0;   // n lanes are taken
+  while (n < 64 && !r.end) {
+    if (r.next != kNil) {
+      r.bad = r.bad || r.next >= a.pool;
+      if (r.bad) break;
+      const NodeHdr h = a.hdr[r.next];
+      const u32 size = wave_read(h.size, 0);
+      r.bad = size > a.cap;
+      if (r.bad) break;
+      r.end = wave_ballot(h.fence > (u64)r.hi) != 0;   // a fence bounds its node's keys from above
+      u32 take = size;
+      if (r.end) take = upper_bound_idx<K>(a.nkeys + (u64)r.next * a.cap, 0u, size, r.hi);
+      if (lane == n) {
+        *node = r.next;
+        c = take;
+      }
+      r.next = wave_read(h.next, 0);
+      ++n;
+    } else {
+      const u32 i = r.b + 1 + (lane - n);
+      const bool in = lane >= n && i < a.nb;
+      NodeHdr h;
+      h.fence = 0;
+      h.size = 0;
+      h.next = kNil;
+      if (in) h = a.hdr[i];
+      const u64 beyond = ~0ull << n;   // lanes not taken yet
+      const u64 stop = wave_ballot(!(in && h.fence <= (u64)r.hi)) & beyond;
+      const u64 chain = wave_ballot(h.next != kNil) & beyond;
+      const u32 ns = stop ? (u32)ctz64(stop) : 64u;
+      const u32 nc = chain ? (u32)ctz64(chain) : 64u;
+      // up to the first chain's head, or to the bucket that the range ends in
+      const u32 last = nc < ns ? nc : ns < 63 ? ns : 63u;
+      r.end = nc >= ns && ns < 64;
+      const bool mine = lane >= n && lane <= last;
+      r.bad = wave_ballot(mine && h.size > a.cap) != 0;
+      if (r.bad) break;
+      if (mine) {
+        *node = i;
+        c = h.size;
+        if (r.end && lane == last && in)
+          c = upper_bound_idx<K>(a.nkeys + (u64)i * a.cap, 0u, h.size, r.hi);
+      }
+      if (nc < ns) r.next = wave_read(h.next, (int)nc);
+      r.b += last + 1 - n;
+      if (!r.end && nc >= ns && !wave_ballot(mine && c != 0)) {   // a stretch of empty buckets
+        r.b = wave_read(occ_next(occ, a.nb, r.b), 0) - 1;
+        r.end = r.b + 1 >= a.nb;
+        if (n == 0) { c = 0; continue; }   // (the lanes hold nothing)
+      }
+      n = last + 1;
+    }
+  }
+  r.end = r.end || r.bad;
+  return r.bad ? 0u : c;
+}
+
 // Answers of queries j[0..Q) of every lane (live: it exists).  All lanes of
 // the wave call.
 template <typename K, int OP, int Q>
@@ -280,6 +371,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
   constexpr u32 B = 64 / sizeof(K);
   constexpr bool UPPER = OP == kOpPredecessor;   // bound: first key > x, else >= x
   const K NF = key_max<K>();
+  const u32 lane = threadIdx.x & 63u;
   const OccLevels occ = occ_levels(a.occ, a.nb);
   K x[Q], hi[Q];
 #pragma unroll
@@ -369,7 +461,11 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
   }
 
   if constexpr (OP == kOpRange) {
-    // the range's keys node by node: [p, ub) of each, copied by the wave
+    // the range's keys node by node: [p, ub) of each, copied by the wave.  What is
+    // left of ranges that have passed as many nodes as there are of them is
+    // finished range by range, 64 nodes at a time: bound by the latency of one
+    // wave's loads (one range of 2^20 u32 results 9.5 ms, of 2^20 u64 14.0; node by
+    // node 18.8 and 18.4, link by link with the wave's other ranges 25 and 28).
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       bool more = live[q] && !bad[q] && x[q] <= hi[q];
@@ -382,28 +478,65 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
       h.next = next[q];
       if (more && le[q] == valid[q] && ub < h.size)   // every key of the block is in the range
         ub = upper_bound_idx<K>(a.nkeys + (u64)node[q] * a.cap, ub, h.size, hi[q]);
-      while (wave_ballot(more)) {
-        const u32 got = more ? ub - p : 0u;
-        const u32 room = cnt < a.maxpq ? a.maxpq - cnt : 0u;
-        wave_copy_runs<K>(a, (u64)node[q] * a.cap + p, ob + cnt, got < room ? got : room);
-        cnt += got;
-        if (more && ub < h.size) more = false;   // a key above hi ends the range
-        if (more) {
-          NodeHdr g;
-          const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
-          if (nn == kNil || nn == kBadLink || g.size > a.cap) {
-            bad[q] = nn != kNil;
-            more = false;
-          } else {
-            node[q] = nn;
-            h = g;
-            p = 0;
-            // a fence bounds its node's keys from above
-            ub = h.fence <= (u64)hi[q]
-                     ? h.size
-                     : upper_bound_idx<K>(a.nkeys + (u64)nn * a.cap, 0u, h.size, hi[q]);
+      WaveRange<K> r;
+      int rl = -1;   // lane of the range that the wave finishes
+      u64 left;
+      for (u32 step = 0; (left = wave_ballot(more)) != 0; ++step) {
+        u32 c = 0;
+        u64 src, dst;
+        if (step > (u32)__popcll(left)) {
+          if (rl < 0) {
+            rl = (int)ctz64(left);
+            r.hi = wave_read(hi[q], rl);
+            r.b = wave_read(b[q], rl);
+            r.next = wave_read(h.next, rl);
+            r.cnt = wave_read(cnt, rl);
+            r.end = false;
+            r.bad = false;
           }
+          u32 nd = 0;
+          const u32 got = wave_gather<K>(a, occ, r, &nd);
+          const u32 incl = wave_scan(got);
+          const u32 at = r.cnt + incl - got;
+          const u32 room = at < a.maxpq ? a.maxpq - at : 0u;
+          c = got < room ? got : room;
+          src = (u64)nd * a.cap;
+          dst = wave_read(ob, rl) + at;
+          r.cnt += wave_read(incl, 63);
+          if (r.end) {
+            if (lane == (u32)rl) {
+              cnt = r.cnt;
+              bad[q] = r.bad;
+              more = false;
+            }
+            rl = -1;
+          }
+        } else {
+          if (step > 0 && more) {
+            NodeHdr g;
+            const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
+            if (nn == kNil || nn == kBadLink || g.size > a.cap) {
+              bad[q] = nn != kNil;
+              more = false;
+            } else {
+              node[q] = nn;
+              h = g;
+              p = 0;
+              // a fence bounds its node's keys from above
+              ub = h.fence <= (u64)hi[q]
+                       ? h.size
+                       : upper_bound_idx<K>(a.nkeys + (u64)nn * a.cap, 0u, h.size, hi[q]);
+            }
+          }
+          const u32 got = more ? ub - p : 0u;
+          const u32 room = cnt < a.maxpq ? a.maxpq - cnt : 0u;
+          c = got < room ? got : room;
+          src = (u64)node[q] * a.cap + p;
+          dst = ob + cnt;
+          cnt += got;
+          if (more && ub < h.size) more = false;   // a key above hi ends the range
         }
+        wave_copy_runs<K>(a, src, dst, c);
       }
       if (live[q]) a.counts[j[q]] = bad[q] ? 0u : cnt;
     }
@@ -502,8 +635,7 @@ __device__ __forceinline__ void load_top(const DirTree<K>& t, K* s_top) {
   __syncthreads();
 }
 
-// qpw queries per wave (64, or fewer for a range batch too small to fill the
-// chip: the copies of its results then spread over more waves).
+// qpw queries per wave: 64, for ranges range_queries_per_wave.
 template <typename K, int NT, int OP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_read_direct(
     ReadArgs<K> a, DirTree<K> t, u32 qpw) {

@@ -221,21 +221,22 @@ __device__ __forceinline__ bool spans_over_keys(const BatchSpans& s, bool range)
   return c;
 }
 
-// Read batch of a drain: units of Q * 64 queries go to the waves of the grid
-// in turn, from wave `rot` on.  Returns whether this wave had any.
+// Read batch of a drain: units of Q * qpw queries (Q of each lane) go to the
+// waves of the grid in turn, from wave `rot` on.  Returns whether this wave had any.
 template <typename K, int OP, int Q>
 __device__ __forceinline__ bool drain_read(const ReadArgs<K>& ra, const DirTree<K>& tree,
-                                           const K* s_top, u32 wave, u32 waves, u32 rot) {
+                                           const K* s_top, u32 wave, u32 waves, u32 rot,
+                                           u32 qpw) {
   const u32 lane = threadIdx.x & 63u;
-  const u32 units = (ra.m + 64 * Q - 1) / (64 * Q);
+  const u32 units = (ra.m + qpw * Q - 1) / (qpw * Q);
   bool any = false;
   for (u32 u = wave >= rot ? wave - rot : wave + waves - rot; u < units; u += waves) {
     u32 j[Q];
     bool live[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      j[q] = (u * Q + q) * 64u + lane;
-      live[q] = j[q] < ra.m;
+      j[q] = (u * Q + q) * qpw + lane;
+      live[q] = lane < qpw && j[q] < ra.m;
     }
     direct_read<K, OP, Q>(ra, tree, s_top, j, live);
     any = true;
@@ -365,16 +366,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       bool any;
       u32 per = 64 * Q;
       switch (d.op) {
-        case kOpLookup: any = drain_read<K, kOpLookup, Q>(ra, tree, s_top, wave, waves, rot); break;
+        case kOpLookup:
+          any = drain_read<K, kOpLookup, Q>(ra, tree, s_top, wave, waves, rot, 64);
+          break;
         case kOpSuccessor:
-          any = drain_read<K, kOpSuccessor, Q>(ra, tree, s_top, wave, waves, rot);
+          any = drain_read<K, kOpSuccessor, Q>(ra, tree, s_top, wave, waves, rot, 64);
           break;
         case kOpRange:
-          any = drain_read<K, kOpRange, 1>(ra, tree, s_top, wave, waves, rot);
-          per = 64;
+          per = range_queries_per_wave(64, n, waves);
+          any = drain_read<K, kOpRange, 1>(ra, tree, s_top, wave, waves, rot, per);
           break;
         default:
-          any = drain_read<K, kOpPredecessor, Q>(ra, tree, s_top, wave, waves, rot);
+          any = drain_read<K, kOpPredecessor, Q>(ra, tree, s_top, wave, waves, rot, 64);
           break;
       }
       rot = (u32)((rot + (n + per - 1) / per) % waves);

@@ -109,11 +109,13 @@ template <typename K>
 void launch_direct(const ReadArgs<K>& a, const DirTree<K>& t, int op, hipStream_t st,
                    hipEvent_t e0, hipEvent_t e1) {
   constexpr int NT = 256;
-  // ranges: fewer queries per wave while that leaves the chip under 32 waves
-  // per CU (the results of a range are copied by its wave)
+  // ranges: fewer queries per wave, down to four, while that leaves the chip under
+  // 32 waves per CU, and down to one for the shortest batches
   u32 qpw = 64;
-  if (op == kOpRange)
+  if (op == kOpRange) {
     while (qpw > 4 && (u64)qpw * 8192u > a.m) qpw >>= 1;
+    qpw = range_queries_per_wave(qpw, a.m, 8192u);
+  }
   const u32 per = qpw * (NT / 64);
   const dim3 g((a.m + per - 1) / per), b(NT);
   switch (op) {
