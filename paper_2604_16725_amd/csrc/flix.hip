@@ -129,7 +129,7 @@ struct flix_store {
   int drain_grid = 0;                 // co-resident workgroups of the drain kernel
   size_t drain_shm = 0;
   StoreLayout* d_layout = nullptr;    // layout record read by drains (graph replays)
-  u32 upd_resident[4] = {0, 0, 0, 0}; // resident workgroups of each update kernel
+  u32 upd_resident[2][4] = {};        // resident workgroups of each update kernel
   // epoch slots (allocated by the first epoch call)
   EpochSlot* ep[2] = {nullptr, nullptr};
 };
@@ -695,25 +695,26 @@ u32 upd_lds_items(const flix_store* s) { return s->cap + upd_chunk(s); }
 // The grid gives every lane group one work item when there are few and is
 // capped at the resident workgroup count when there are many, so each group
 // then walks a run of items with the next one's loads in flight.
-template <typename K, int GL>
-void launch_update(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, hipStream_t st,
-                   u32 lds_items, const u32* m_dev, const TmTok& t) {
+template <typename K, int GL, bool FLAT>
+void launch_update_form(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, hipStream_t st,
+                        u32 lds_items, const u32* m_dev, const TmTok& t) {
   size_t shm = (size_t)(kUpdNT / GL) * 2 * lds_items * sizeof(K);
   static size_t attr_set[4] = {0, 0, 0, 0};
   const int which = (insert ? 1 : 0) + (m_dev ? 2 : 0);
   const void* fn;
   switch (which) {
-    case 0: fn = reinterpret_cast<const void*>(&k_delete_apply<K, GL, kUpdNT>); break;
-    case 1: fn = reinterpret_cast<const void*>(&k_insert_apply<K, GL, kUpdNT>); break;
-    case 2: fn = reinterpret_cast<const void*>(&k_delete_counted<K, GL, kUpdNT>); break;
-    default: fn = reinterpret_cast<const void*>(&k_insert_counted<K, GL, kUpdNT>); break;
+    case 0: fn = reinterpret_cast<const void*>(&k_delete_apply<K, GL, kUpdNT, FLAT>); break;
+    case 1: fn = reinterpret_cast<const void*>(&k_insert_apply<K, GL, kUpdNT, FLAT>); break;
+    case 2: fn = reinterpret_cast<const void*>(&k_delete_counted<K, GL, kUpdNT, FLAT>); break;
+    default: fn = reinterpret_cast<const void*>(&k_insert_counted<K, GL, kUpdNT, FLAT>); break;
   }
   if (shm > 65536 && shm > attr_set[which]) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e == hipSuccess) attr_set[which] = shm;
     (void)hipGetLastError();
   }
-  if (s->upd_resident[which] == 0) {
+  u32& resident = s->upd_resident[FLAT][which];
+  if (resident == 0) {
     int per_cu = 0, dev = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kUpdNT, shm) != hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
@@ -723,29 +724,37 @@ void launch_update(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, h
       cus = 256;
     }
     (void)hipGetLastError();
-    s->upd_resident[which] = (u32)(per_cu * cus);
+    resident = (u32)(per_cu * cus);
   }
   const u32 gpb = kUpdNT / GL;
   u64 g2 = (items + gpb - 1) / gpb;
   if (g2 < 1) g2 = 1;
-  if (g2 > s->upd_resident[which]) g2 = s->upd_resident[which];
+  if (g2 > resident) g2 = resident;
   const u32 grid = (u32)g2;
   const dim3 g(grid), blk(kUpdNT);
   const uint32_t sh = (uint32_t)shm;
   switch (which) {
     case 0:
-      launch_timed(t.b, t.e, k_delete_apply<K, GL, kUpdNT>, g, blk, sh, st, a, lds_items);
+      launch_timed(t.b, t.e, k_delete_apply<K, GL, kUpdNT, FLAT>, g, blk, sh, st, a, lds_items);
       break;
     case 1:
-      launch_timed(t.b, t.e, k_insert_apply<K, GL, kUpdNT>, g, blk, sh, st, a, lds_items);
+      launch_timed(t.b, t.e, k_insert_apply<K, GL, kUpdNT, FLAT>, g, blk, sh, st, a, lds_items);
       break;
     case 2:
-      launch_timed(t.b, t.e, k_delete_counted<K, GL, kUpdNT>, g, blk, sh, st, a, lds_items, m_dev);
+      launch_timed(t.b, t.e, k_delete_counted<K, GL, kUpdNT, FLAT>, g, blk, sh, st, a, lds_items,
+                   m_dev);
       break;
     default:
-      launch_timed(t.b, t.e, k_insert_counted<K, GL, kUpdNT>, g, blk, sh, st, a, lds_items, m_dev);
+      launch_timed(t.b, t.e, k_insert_counted<K, GL, kUpdNT, FLAT>, g, blk, sh, st, a, lds_items,
+                   m_dev);
       break;
   }
+}
+template <typename K, int GL>
+void launch_update(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, hipStream_t st,
+                   u32 lds_items, const u32* m_dev, const TmTok& t) {
+  if (a.flat) launch_update_form<K, GL, true>(s, insert, a, items, st, lds_items, m_dev, t);
+  else launch_update_form<K, GL, false>(s, insert, a, items, st, lds_items, m_dev, t);
 }
 
 template <typename K>

@@ -441,11 +441,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       ua.ctl = a.ctl;
       ua.status = &a.ctl->status;
       ua.occ = L.occ;
-      ua.flat = true;
       ua.parts = a.ctl->part;
       ua.nparts = ins ? units : 0u;
-      if (ins) insert_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
-      else delete_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
+      if (ins) insert_items<K, GL, 256, true>(ua, a.lds_items, blk, G, smem, s_upd);
+      else delete_items<K, GL, 256, true>(ua, a.lds_items, blk, G, smem, s_upd);
       if (grid_sync(dc, G)) return;
       pend = bi + 1;
       if (blk == 0 && threadIdx.x == 0 && a.tstamp)
@@ -548,9 +547,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       ua.status = &a.ctl->status;
       ua.occ = L.occ;
       if (d.op == kOpInsert)
-        insert_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
+        insert_items<K, GL, 256, false>(ua, a.lds_items, blk, G, smem, s_upd);
       else
-        delete_items<K, GL, 256>(ua, a.lds_items, blk, G, smem, s_upd);
+        delete_items<K, GL, 256, false>(ua, a.lds_items, blk, G, smem, s_upd);
     }
     if (grid_sync(dc, G)) return;
     pend = bi + 1;

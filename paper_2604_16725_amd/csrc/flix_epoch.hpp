@@ -188,7 +188,7 @@ __global__ __launch_bounds__(NT) void k_slices_counted(SliceArgs<K> a, const u32
   slices_share<K, NT, S, INSERT>(a, blockIdx.x, sm);
 }
 
-template <typename K, int GL, int NT>
+template <typename K, int GL, int NT, bool FLAT>
 __global__ __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 6 : 1))) void k_insert_counted(
     UpdArgs<K> a, u32 lds_items, const u32* __restrict__ m_dev) {
@@ -196,17 +196,17 @@ __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 6 : 1))) void k_insert_count
   __shared__ UpdShared sh;
   a.m = *m_dev;
   if (a.m == 0) return;
-  insert_items<K, GL, NT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
+  insert_items<K, GL, NT, FLAT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
 }
 
-template <typename K, int GL, int NT>
+template <typename K, int GL, int NT, bool FLAT>
 __global__ __launch_bounds__(NT) void k_delete_counted(UpdArgs<K> a, u32 lds_items,
                                                        const u32* __restrict__ m_dev) {
   extern __shared__ unsigned char s_dyn[];
   __shared__ UpdShared sh;
   a.m = *m_dev;
   if (a.m == 0) return;
-  delete_items<K, GL, NT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
+  delete_items<K, GL, NT, FLAT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
 }
 
 }  // namespace flix

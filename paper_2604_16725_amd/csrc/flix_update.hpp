@@ -424,8 +424,8 @@ struct UpdArgs {
                       // their slice belong to the workgroup-wide insert kernel
   u32 wide_cap = 0;
   const WorkItem* wide = nullptr;   // those items, listed by the slice kernel
-  bool flat = false;  // short list: item i at position i (empty ones are no
-                      // bucket's first key), headers not yet read
+  bool flat = false;  // short list (the kernels' FLAT form): item i at position i
+                      // (empty ones are no bucket's first key), headers not yet read
   u32 nparts = 0;     // > 0: the call's node bound is the sum of these parts
   const u64* parts = nullptr;
 };
@@ -433,12 +433,12 @@ struct UpdArgs {
 // Whether the call as a whole is rejected, and the error to report (0: a
 // batch rejected before).  Every workgroup decides alike: the words it reads
 // are not written while the apply kernels run.  All lanes of a wave call.
-template <typename K>
+template <typename K, bool FLAT>
 __device__ __forceinline__ bool call_rejected(const UpdArgs<K>& a, u32* err) {
   const Ctl* ctl = a.ctl;
   u64 need = ctl->need;
   u32 e = ctl->call_err;
-  if (a.nparts) {
+  if (FLAT && a.nparts) {
     u64 v = 0;
     bool bad = false;
     for (u32 i = threadIdx.x & 63u; i < a.nparts; i += 64) {
@@ -501,7 +501,9 @@ __device__ __forceinline__ u32 piece_of(u32 pos, u32 c, u32 k) {
 // ---------------------------------------------------------------------------
 // Insert work of workgroup `blk` of `nblk` (groups stride over the work list).
 // `s_dyn`: per-group LDS regions; `sh`: workgroup-shared counter and work map.
-template <typename K, int GL, int NT>
+// FLAT is the form for short lists, compiled apart: in one kernel the other form
+// spilled 13 scalars a lane instead of 4 and was 1 to 8% slower.
+template <typename K, int GL, int NT, bool FLAT>
 __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nblk,
                              unsigned char* s_dyn, UpdShared& sh) {
   unsigned long long& s_added = sh.counter;
@@ -517,12 +519,12 @@ __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   if (threadIdx.x == 0) s_added = 0;
   __syncthreads();
   u32 call_err;
-  if (call_rejected(a, &call_err)) {
+  if (call_rejected<K, FLAT>(a, &call_err)) {
     if (blk == 0 && threadIdx.x == 0) atomicCAS(a.status, 0u, call_err != 0 ? call_err : kErrNomem);
     __syncthreads();
     return;
   }
-  const u32 nitems = a.flat ? a.m : load_work_map(a.ctl, sh.pre);
+  const u32 nitems = FLAT ? a.m : load_work_map(a.ctl, sh.pre);
   // a call-level choice that gives this kernel nothing ends it here (uniform)
   if ((a.sel == kSelRound || a.sel == kSelRoundL) && !sel_takes(a.sel, a.st_max, 0u, a.m, nitems))
     return;
@@ -532,15 +534,15 @@ __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   u32 it = blk * GPB + gid;
   WorkItem wnext;
   WorkCursor cur;
-  if (!a.flat) cur.seek(sh.pre, it);
-  if (it < nitems) wnext = a.work[a.flat ? it : cur.slot(it, a.rcap)];
+  if (!FLAT) cur.seek(sh.pre, it);
+  if (it < nitems) wnext = a.work[FLAT ? it : cur.slot(it, a.rcap)];
   for (; it < nitems; it += stride) {
     WorkItem w = wnext;
     if (it + stride < nitems) {   // prefetch
-      if (!a.flat) cur.move(sh.pre, it + stride);
-      wnext = a.work[a.flat ? it + stride : cur.slot(it + stride, a.rcap)];
+      if (!FLAT) cur.move(sh.pre, it + stride);
+      wnext = a.work[FLAT ? it + stride : cur.slot(it + stride, a.rcap)];
     }
-    if (a.flat) {
+    if (FLAT) {
       if (w.s == w.e) continue;   // no slice begins at this key
       const u64 hw = *reinterpret_cast<const u64*>(&a.hdr[w.b].size);
       w.head = (u32)(hw >> 32) == kNil ? ((u32)hw | kSingleNode) : (u32)hw;
@@ -855,13 +857,13 @@ __device__ void insert_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
 // Five waves per SIMD for 32-bit keys (85 VGPRs, no spills): the register
 // path of a node that fits the registers needs more than the 80 registers of
 // six waves, which spilled and was 6% slower; 64-bit keys take what they need.
-template <typename K, int GL, int NT>
+template <typename K, int GL, int NT, bool FLAT>
 __global__ __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(sizeof(K) == 4 ? 5 : 1))) void k_insert_apply(
     UpdArgs<K> a, u32 lds_items) {
   extern __shared__ unsigned char s_dyn[];
   __shared__ UpdShared sh;
-  insert_items<K, GL, NT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
+  insert_items<K, GL, NT, FLAT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -1253,7 +1255,7 @@ __global__ __launch_bounds__(NT) void k_insert_wide(UpdArgs<K> a) {
   __shared__ WideLds<K> L;
   const Ctl* ctl = a.ctl;
   u32 call_err;
-  if (call_rejected(a, &call_err)) return;   // the other kernels report it
+  if (call_rejected<K, true>(a, &call_err)) return;   // the other kernels report it
   const u32 n = ctl->wide_n < a.wide_cap ? ctl->wide_n : a.wide_cap;
   unsigned long long added = 0;
   for (u32 i = blockIdx.x; i < n; i += gridDim.x) {
@@ -1273,7 +1275,7 @@ __global__ __launch_bounds__(NT) void k_insert_wide(UpdArgs<K> a) {
 // returned to the free list; this also unlinks every emptied non-head node
 // (Section 4.4 step 5).  The head node is never freed.
 // ---------------------------------------------------------------------------
-template <typename K, int GL, int NT>
+template <typename K, int GL, int NT, bool FLAT>
 __device__ void delete_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nblk,
                              unsigned char* s_dyn, UpdShared& sh) {
   unsigned long long& s_removed = sh.counter;
@@ -1287,23 +1289,23 @@ __device__ void delete_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   __syncthreads();
   if (a.ctl->call_abort != 0) return;   // an epoch rejected as a whole (uniform)
   u32 call_err;
-  if (a.nparts && call_rejected(a, &call_err)) return;   // (a short epoch: its upserts' bound)
-  const u32 nitems = a.flat ? a.m : load_work_map(a.ctl, sh.pre);
+  if (FLAT && a.nparts && call_rejected<K, FLAT>(a, &call_err)) return;   // (a short epoch: its upserts' bound)
+  const u32 nitems = FLAT ? a.m : load_work_map(a.ctl, sh.pre);
   const u32 f = a.cap / 2;
   u64 removed = 0;
   const u32 stride = nblk * GPB;
   u32 it = blk * GPB + gid;
   WorkItem wnext;
   WorkCursor cur;
-  if (!a.flat) cur.seek(sh.pre, it);
-  if (it < nitems) wnext = a.work[a.flat ? it : cur.slot(it, a.rcap)];
+  if (!FLAT) cur.seek(sh.pre, it);
+  if (it < nitems) wnext = a.work[FLAT ? it : cur.slot(it, a.rcap)];
   for (; it < nitems; it += stride) {
     WorkItem w = wnext;
     if (it + stride < nitems) {   // prefetch
-      if (!a.flat) cur.move(sh.pre, it + stride);
-      wnext = a.work[a.flat ? it + stride : cur.slot(it + stride, a.rcap)];
+      if (!FLAT) cur.move(sh.pre, it + stride);
+      wnext = a.work[FLAT ? it + stride : cur.slot(it + stride, a.rcap)];
     }
-    if (a.flat) {
+    if (FLAT) {
       if (w.s == w.e) continue;   // no slice begins at this key
       const u64 hw = *reinterpret_cast<const u64*>(&a.hdr[w.b].size);
       w.head = (u32)(hw >> 32) == kNil ? ((u32)hw | kSingleNode) : (u32)hw;
@@ -1502,11 +1504,11 @@ __device__ void delete_items(const UpdArgs<K>& a, u32 lds_items, u32 blk, u32 nb
   __syncthreads();
 }
 
-template <typename K, int GL, int NT>
+template <typename K, int GL, int NT, bool FLAT>
 __global__ __launch_bounds__(NT) void k_delete_apply(UpdArgs<K> a, u32 lds_items) {
   extern __shared__ unsigned char s_dyn[];
   __shared__ UpdShared sh;
-  delete_items<K, GL, NT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
+  delete_items<K, GL, NT, FLAT>(a, lds_items, blockIdx.x, gridDim.x, s_dyn, sh);
 }
 
 // ---------------------------------------------------------------------------
