@@ -274,8 +274,10 @@ typedef struct {
  * h_batches (host) is validated like the per-batch calls; d_batches is the
  * same array in device memory, read by the kernel.  d_timestamps (device,
  * nbatch+1 entries, may be NULL) receives the device wall clock at the start
- * and after each batch (rate: flix_drain_info).  Device-detected update
- * errors behave as in flix_insert (batch cancelled, sticky status). */
+ * and, for each batch, when its results and those of all batches before it were
+ * stored (rate: flix_drain_info); read batches run into one another, so the time
+ * between two stamps is not one batch's own.  Device-detected update errors
+ * behave as in flix_insert (batch cancelled, sticky status). */
 int flix_drain(flix_store* s, const flix_batch* h_batches, const flix_batch* d_batches,
                uint32_t nbatch, uint64_t* d_timestamps, void* stream);
 

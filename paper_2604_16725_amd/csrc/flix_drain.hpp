@@ -211,6 +211,16 @@ __device__ __forceinline__ bool spans_conflict(const BatchSpans& a, const BatchS
   }
   return c;
 }
+// Time stamp of a wave's part of a batch, taken when its answers are stored: its
+// stores are counted by vmcnt, which a release within the workgroup does not wait
+// for.  (An agent-scope release would, but writes the XCD's L2 back: 11 us and
+// more.)
+__device__ __forceinline__ void stamp_stored(unsigned long long* at) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // no store sinks below
+  __builtin_amdgcn_s_waitcnt(0);
+  if ((threadIdx.x & 63u) == 0) atomicMax(at, (unsigned long long)wall_clock64());
+}
+
 // answers_over_keys of a read batch with these spans.
 __device__ __forceinline__ bool spans_over_keys(const BatchSpans& s, bool range) {
   bool c = false;
@@ -381,10 +391,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
           break;
       }
       rot = (u32)((rot + (n + per - 1) / per) % waves);
-      if (any && a.tstamp) {   // the last wave to end leaves its time
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        if ((threadIdx.x & 63u) == 0) atomicMax(&a.tstamp[bi + 1], (unsigned long long)wall_clock64());
-      }
+      if (any && a.tstamp) stamp_stored(&a.tstamp[bi + 1]);   // the last wave's time stays
       if (copied) {   // the scratch is free for the next batch
         if (grid_sync(dc, G)) return;
         pend = bi + 1;
