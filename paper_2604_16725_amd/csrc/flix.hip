@@ -504,17 +504,15 @@ int read_apply_sorted(flix_store* s, int op, const K* skeys, const u32* sidx, u6
   a.err = &s->ctl->status;
   a.occ = s->occl.w0;
   u64 grid = ((u64)n + s->nb + a.share - 1) / a.share;
-  // cut list: half a wave per share boundary (the list holds cuts_for(max_batch,
-  // nb_alloc) >= grid + 1 entries)
-  a.cuts = nullptr;
-  if (s->cuts && grid + 1 <= cuts_for(s->max_batch, s->nb_alloc)) {
-    const u32 ncuts = (u32)grid + 1u;
-    const TmTok tc = tm_arm(s, F_CUTS);
-    launch_timed(tc.b, tc.e, k_merge_cuts<K>, dim3((ncuts + 7) / 8), dim3(256), 0, st, skeys,
-                 (u32)n, (const K*)s->mkba, s->nb, a.share, ncuts, s->cuts);
-    tm_done(s, F_CUTS, tc);
-    a.cuts = s->cuts;
-  }
+  // cut list: half a wave per share boundary (shares of at least 512 items, so
+  // the list has room)
+  static_assert(ReadCfg<K>::S >= 512, "the cut list is sized for shares of 512 items");
+  const u32 ncuts = (u32)grid + 1u;
+  const TmTok tc = tm_arm(s, F_CUTS);
+  launch_timed(tc.b, tc.e, k_merge_cuts<K>, dim3((ncuts + 7) / 8), dim3(256), 0, st, skeys, (u32)n,
+               (const K*)s->mkba, s->nb, a.share, ncuts, s->cuts);
+  tm_done(s, F_CUTS, tc);
+  a.cuts = s->cuts;
   const TmTok t = tm_arm(s, F_READ);
   launch_read2<K>(s->gl, s->cap, a, op, (u32)grid, st, t.b, t.e);
   tm_done(s, F_READ, t);

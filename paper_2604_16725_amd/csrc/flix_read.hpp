@@ -22,8 +22,8 @@ constexpr int kOpPredecessor = 5;   // 3 and 4 are the update operations
 
 template <typename K>
 struct ReadArgs {
-  const K* skeys;      // sorted batch keys [m]
-  const u32* sidx;     // input position of each sorted key [m]
+  const K* skeys;      // batch keys [m]: sorted, or in input order (direct reads)
+  const u32* sidx;     // input position of each sorted key [m] (direct reads: null)
   u32 m;
   const K* mkba;       // [nb]
   u32 nb;
@@ -31,7 +31,7 @@ struct ReadArgs {
   const K* nkeys;      // [pool * cap]
   const K* nvals;      // [pool * cap]
   u32 cap;
-  u32 share;           // merged items (buckets + keys) per workgroup
+  u32 share;           // flipped form: merged items (buckets + keys) per workgroup
   K* out_v;            // lookup, successor, range values
   K* out_k;            // successor, range keys (range: may be null)
   const K* hi;         // range upper bounds in input order
@@ -41,8 +41,8 @@ struct ReadArgs {
   u32* err;            // sticky status word for internal errors
   u64* occ;            // occupancy summary of the nb buckets, its three levels
                        // laid out from here (flix_occ.hpp: occ_levels)
-  const u32* cuts;     // merge-path cut of every share boundary [nshares + 1], or
-                       // nullptr: each workgroup searches its own two cuts
+  const u32* cuts;     // flipped form: merge-path cut of every share boundary
+                       // [nshares + 1]
 };
 
 // Cooperative merge-path cut for the two diagonals d[0], d[1] of one

@@ -1,12 +1,10 @@
-// Read batches, register-resident form (the default read kernel).
+// Read batches, register-resident flipped form (long batches).
 //
 // Same flipped structure as flix_read.hpp (Section 3.3: every bucket pulls the
 // slice of the sorted batch that falls into (MKBA[i-1], MKBA[i]]), organised
 // for wave64 latency hiding:
 //   1. merge-path cut of "MKBA (+) sorted batch" into equal shares: loaded
-//      from the cut list (written by the run sort, else by k_merge_cuts), or
-//      (persistent drain) found by a cooperative 128-ary search (three
-//      dependent rounds instead of ~21);
+//      from the cut list that k_merge_cuts writes;
 //   2. one coalesced round of loads: the share's keys, their input positions,
 //      MKBA entries and node headers (and range upper bounds);
 //   3. every bucket takes its slice by upper_bound of its maxBucket in LDS;
@@ -78,7 +76,7 @@ struct ReadSmem {
   u32 hw[S + 1];    // head node: size | kChainBit when the bucket has more nodes
   unsigned short tl[S + 1];
   u32 tmp[NT / 64 + 1];
-  u32 lo[2], hiw[2], wc[4], cut[2], ntouch;
+  u32 cut[2], ntouch;
   u32 nslow;        // ranges listed for the wave-wide copy
 };
 
@@ -559,9 +557,6 @@ __device__ __forceinline__ void read_share(const ReadArgs<K>& a, int op, u32 vb,
   u32* s_hw = sm.hw;
   unsigned short* s_tl = sm.tl;
   u32* s_tmp = sm.tmp;
-  u32* s_lo = sm.lo;
-  u32* s_hiw = sm.hiw;
-  u32* s_wc = sm.wc;
   u32* s_cut = sm.cut;
   u32& s_ntouch = sm.ntouch;
 
@@ -570,12 +565,8 @@ __device__ __forceinline__ void read_share(const ReadArgs<K>& a, int op, u32 vb,
   u64 d[2];
   d[0] = (u64)vb * a.share;
   d[1] = d[0] + a.share < total ? d[0] + a.share : total;
-  if (a.cuts) {
-    if (tid < 2) s_cut[tid] = a.cuts[vb + tid];
-    __syncthreads();
-  } else {
-    coop_merge_path<K>(a.skeys, a.m, a.mkba, a.nb, d, s_lo, s_hiw, s_wc, s_cut);
-  }
+  if (tid < 2) s_cut[tid] = a.cuts[vb + tid];
+  __syncthreads();
   const u32 q0 = s_cut[0], q1 = s_cut[1];
   // Cuts of a sorted batch are ordered; anything else (an unsorted batch)
   // is reported instead of indexing past the share.
