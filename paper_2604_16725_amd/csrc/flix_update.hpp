@@ -125,7 +125,12 @@ __device__ void slices_share(const SliceArgs<K>& a, u32 vb, SliceSmem<K, S, NT>&
   const u32 nbl = b1 - b0;
   // A bucket is emitted by the share that holds its maxBucket entry, with its
   // whole slice; only local bucket 0 can have keys in earlier shares.
-  if (nbl == 0) {
+  if (nbl == 0) {   // the middle of a long slice: only its values are looked at here
+    if (INSERT) {
+      bool bad = false;
+      for (u32 j = tid; j < nq; j += NT) bad = bad || a.svals[q0 + j] == key_max<K>();
+      if (bad) atomicExch(&a.ctl->call_err, kErrInval);
+    }
     __syncthreads();
     return;
   }

@@ -29,7 +29,7 @@ def _store(kb, cap, seed):
 
     both(ks.fresh(50000))                                  # some short chains
     for at, links in ((1000, 3), (1500, 70), (1520, 64), (40000, 130), (119000, 20)):
-        both((order[at] + np.arange(1, links * cap // 2)).astype(ktype(kb)))
+        both(order[at] + np.arange(1, links * cap // 2).astype(ktype(kb)))
     gone = o.dump()[0][90000:130000]                       # hundreds of empty buckets
     s.delete(to_dev(gone))
     o.delete(gone)

@@ -32,7 +32,7 @@ def _grown(kb, cap, lanes, max_batch, seed, n=60000):
     order = np.sort(k)
     both(ks.fresh(n // 2))
     for at, links in ((n // 9, 5), (n // 5, 40)):              # chains
-        both((order[at] + np.arange(1, links * max(cap // 2, 8))).astype(ktype(kb)))
+        both(order[at] + np.arange(1, links * max(cap // 2, 8)).astype(ktype(kb)))
     gone = o.dump()[0]
     gone = np.concatenate([gone[n // 2: n // 2 + n // 5], gone[: n // 9: 3]])
     s.delete(to_dev(gone))                                     # empty buckets, shrunken nodes
