@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <mutex>
 #include <cstring>
@@ -542,12 +543,8 @@ int read_batch_groups(flix_store* s, int op, const K* keys, u64 n, void* out_k, 
   pa.gtot_clear = gnext;
   {
     using L = PartLds<K, u32, kPayIndex>;
-    static bool attr = false;
-    if (!attr && L::bytes > 65536) {
-      HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_part<K, u32, kPayIndex>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)L::bytes));
-      attr = true;
-    }
+    static std::atomic<u64> lds_ok{0};
+    HIP_TRY(allow_lds(reinterpret_cast<const void*>(&k_part<K, u32, kPayIndex>), L::bytes, lds_ok));
     const TmTok t = tm_arm(s, F_PART);
     launch_timed(t.b, t.e, k_part<K, u32, kPayIndex>, dim3(ntiles), dim3(kPartNT),
                  (uint32_t)L::bytes, st, pa);
@@ -687,6 +684,7 @@ u32 wide_min_keys(u32 cap) { return std::max<u32>(4 * cap, 256u); }
 // capacity 128 a group's LDS is then 1.5 KB, so six workgroups fit a CU.
 u32 upd_chunk(const flix_store* s) { return std::max<u32>(s->cap / 2, 64u); }
 u32 upd_lds_items(const flix_store* s) { return s->cap + upd_chunk(s); }
+constexpr size_t kUpdLdsMax = (size_t)(kUpdNT / 16) * 2 * (256 + 128) * sizeof(u64);
 
 // m_dev: null for a list of host-known length n; otherwise the length is read
 // from device memory and n is its upper bound (grid sizing only).
@@ -697,7 +695,7 @@ template <typename K, int GL, bool FLAT>
 void launch_update_form(flix_store* s, bool insert, const UpdArgs<K>& a, u64 items, hipStream_t st,
                         u32 lds_items, const u32* m_dev, const TmTok& t) {
   size_t shm = (size_t)(kUpdNT / GL) * 2 * lds_items * sizeof(K);
-  static size_t attr_set[4] = {0, 0, 0, 0};
+  static std::atomic<u64> lds_ok[4];
   const int which = (insert ? 1 : 0) + (m_dev ? 2 : 0);
   const void* fn;
   switch (which) {
@@ -706,11 +704,9 @@ void launch_update_form(flix_store* s, bool insert, const UpdArgs<K>& a, u64 ite
     case 2: fn = reinterpret_cast<const void*>(&k_delete_counted<K, GL, kUpdNT, FLAT>); break;
     default: fn = reinterpret_cast<const void*>(&k_insert_counted<K, GL, kUpdNT, FLAT>); break;
   }
-  if (shm > 65536 && shm > attr_set[which]) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-    if (e == hipSuccess) attr_set[which] = shm;
+  // (the largest that a capacity asks for: stores of several may share a device)
+  if (shm > 65536 && allow_lds(fn, kUpdLdsMax, lds_ok[which]) != hipSuccess)
     (void)hipGetLastError();
-  }
   u32& resident = s->upd_resident[FLAT][which];
   if (resident == 0) {
     int per_cu = 0, dev = 0, cus = 0;

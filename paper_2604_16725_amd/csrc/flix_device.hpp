@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace flix {
 
 typedef uint32_t u32;
@@ -64,6 +66,20 @@ __host__ __device__ inline u32 work_region_cap(u64 max_batch) {
 }
 __host__ __device__ inline u64 work_slots(u64 max_batch) {
   return (u64)kWorkRegions * work_region_cap(max_batch) + max_batch;
+}
+
+// Lets a kernel ask for `bytes` of dynamic LDS, once per device (`done`: a mask of
+// the devices that have it, one per kernel).  Any thread may call.
+inline hipError_t allow_lds(const void* kernel, size_t bytes, std::atomic<u64>& done) {
+  if (bytes <= 65536) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const u64 bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+  if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
 }
 
 // Per-call reset of the work-list counters (region r by thread r).

@@ -52,13 +52,10 @@ void group_k(const GroupArgs<K>& ga, const ReadArgs<K>& a, int op, u32 grid, hip
   constexpr int U = KW >= 16 ? 2 : 4;
   auto fn = k_group_read<K, 256, 8, GL, KPL, U>;
   const GroupLds<K> L(2048, 256, kGroupBucketsMax, op == kOpRange);
-  static size_t attr = 0;
-  if (L.bytes > 65536 && L.bytes > attr) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.bytes) == hipSuccess)
-      attr = L.bytes;
+  static std::atomic<u64> lds_ok{0};   // (ranges need the most)
+  if (allow_lds(reinterpret_cast<const void*>(fn), GroupLds<K>(2048, 256, kGroupBucketsMax, true).bytes,
+                lds_ok) != hipSuccess)
     (void)hipGetLastError();
-  }
   launch_timed(e0, e1, fn, dim3(grid), dim3(256), (uint32_t)L.bytes, st, ga, a, op);
 }
 

@@ -1639,13 +1639,9 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     constexpr size_t lds = run_sort_lds<K, V, PAY>();
-    static bool lds_set = false;
-    if (!lds_set) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run_sort<K, V, PAY>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      lds_set = true;
-    }
+    static std::atomic<u64> lds_ok{0};
+    e = allow_lds(reinterpret_cast<const void*>(&k_run_sort<K, V, PAY>), lds, lds_ok);
+    if (e != hipSuccess) return e;
     {
       SortTimer t(s, 2);
       launch_timed(t.e0, t.e1, k_run_sort<K, V, PAY>, dim3(R), dim3(kLocalNT), (uint32_t)lds, st,
@@ -1704,13 +1700,9 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
     if constexpr (RB == 8) {
       if (!local) {
         constexpr size_t lds = sizeof(BigPassSmem<K, V, PAY>);
-        static bool lds_set = false;
-        if (!lds_set && lds > 65536) {
-          e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_onesweep_big<K, V, PAY>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-          if (e != hipSuccess) return e;
-          lds_set = true;
-        }
+        static std::atomic<u64> lds_ok{0};
+        e = allow_lds(reinterpret_cast<const void*>(&k_onesweep_big<K, V, PAY>), lds, lds_ok);
+        if (e != hipSuccess) return e;
         launch_timed(t.e0, t.e1, k_onesweep_big<K, V, PAY>,
                      dim3((n + BigTile<K, PAY>::N - 1) / BigTile<K, PAY>::N), dim3(kBigNT), (uint32_t)lds, st, pa);
         t.end();
@@ -1727,13 +1719,9 @@ hipError_t radix_sort(const K* kin, const V* vin, K* k0, V* v0, K* k1, V* v1, u3
   }
   if (local) {
     constexpr size_t lds = local_sort_lds<K, V, PAY>();
-    static bool lds_set = false;
-    if (!lds_set) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_local_sort<K, V, PAY>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      lds_set = true;
-    }
+    static std::atomic<u64> lds_ok{0};
+    e = allow_lds(reinterpret_cast<const void*>(&k_local_sort<K, V, PAY>), lds, lds_ok);
+    if (e != hipSuccess) return e;
     SortTimer t(s, 2);
     launch_timed(t.e0, t.e1, k_local_sort<K, V, PAY>, dim3(R), dim3(kLocalNT), (uint32_t)lds, st,
                  k0, v0, k1, v1, (const u32*)(hist + (P - 1) * R), (u32)(P - 1), n, s.err);
