@@ -96,7 +96,8 @@ struct flix_store {
   u32 nb = 0;          // buckets
   u32 nb_alloc = 0;    // capacity of the directory arrays
   u32 pool = 0;        // nodes
-  bool dup_load = false;   // the last load made its pool smaller for duplicate keys
+  u32 dup_loads = 0;       // loads in a row whose pool shrank for duplicate keys
+  bool fresh = true;       // nothing was ever put into it
   void* mkba = nullptr;
   NodeHdr* hdr = nullptr;
   void* nkeys = nullptr;
@@ -324,7 +325,7 @@ void pool_swap(flix_store* s, PoolMem* m) {
 // left without a pool.
 int pool_instead(flix_store* s, u32 nodes) {
   size_t avail = 0, total = 0;
-  if (!s->pool || (!g_alloc.alloc && hipMemGetInfo(&avail, &total) == hipSuccess &&
+  if (!s->pool || (!s->fresh && !g_alloc.alloc && hipMemGetInfo(&avail, &total) == hipSuccess &&
                    (u64)nodes * (node_bytes(s) + 4) > avail + (u64)s->pool * (node_bytes(s) + 4)))
     return FLIX_ENOMEM;
   PoolMem old, now;
@@ -1315,14 +1316,15 @@ int build_layout(flix_store* s, const K* ck, const K* cv, u64 nd, u32 nbk, hipSt
 // pool of its size allocates nothing.  (A load of 2^26 u32 pairs and a dump of
 // them took 7.4 ms, 1.8 of it in allocating and freeing six buffers, and 45 when
 // the host had been idle; now 2.5.)
-// A load that expects duplicates to shrink its pool (the one before it did) takes
+// A load that expects duplicates to shrink its pool (the last two did) takes
 // temporary buffers of half that size instead: the pool it would sort in is not
 // the one it ends with (2^20 u64 pairs over 0.43 * 2^20 keys, loaded again and
 // again: 1530 us with the pool sized twice a load, 620 in a pool beside the old
 // one, 390 with temporary buffers; 100,000 pairs 800, 186, 122).
 // Memory of another size is had before the old contents go: a new pool stands
 // beside the old one until the layout is built.  Only where both do not fit does
-// the old one go first (pool_instead).
+// the old one go first (pool_instead), and in a new store, which has nothing to
+// lose (2^20 u32 pairs into a new store: 440 us, 970 with both pools).
 template <typename K>
 int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream_t st) {
   if (n > 0xFFFFFFF0ull) return FLIX_EINVAL;
@@ -1370,14 +1372,14 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
       if (want == s->pool) {
         s->nb = 0;   // the old contents go
         where = kStore;
-      } else if (s->dup_load) {
+      } else if (s->dup_loads >= 2) {
         // temporary buffers
-      } else if (pool_alloc(s, want, &stage) == FLIX_OK) {
+      } else if (!s->fresh && pool_alloc(s, want, &stage) == FLIX_OK) {
         where = kStage;
-      } else {
-        rc = pool_instead(s, want);
-        if (rc == FLIX_OK) where = kStore;
-        else if (s->nb == 0) return leave(rc);
+      } else if ((rc = pool_instead(s, want)) == FLIX_OK) {
+        where = kStore;
+      } else if (!s->pool) {
+        return leave(rc);
       }
       if (where == kTemp) dir_free(&dir);
     }
@@ -1448,7 +1450,8 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     }
   }
   dir_take(s, &dir);
-  s->dup_load = n && pool_for((n + s->fill - 1) / s->fill) != pool;
+  s->fresh = s->fresh && n == 0;
+  s->dup_loads = n && pool_for((n + s->fill - 1) / s->fill) != pool ? s->dup_loads + 1 : 0;
   rc = build_layout<K>(s, sk, sv, nd, (u32)nbk, st);
   if (rc) return leave(rc);
   if (where != kStore || old.nodes || stage.nodes) {
@@ -1786,6 +1789,7 @@ int flix_insert(flix_store* s, const void* d_keys, const void* d_vals, uint64_t 
   (void)hipGetLastError();  // drop errors left by other code on this thread
   int c = check_args(s, n, {d_keys, d_vals});
   if (c) return c > 0 ? FLIX_OK : c;
+  s->fresh = false;
   return s->kb == 32 ? update_batch<u32>(s, true, d_keys, d_vals, n, S(stream))
                      : update_batch<u64>(s, true, d_keys, d_vals, n, S(stream));
 }
@@ -2054,6 +2058,7 @@ int flix_epoch_apply(flix_store* s, uint32_t slot, const flix_epoch* e, void* st
     return FLIX_EINVAL;
   es->prepared = false;
   hipStream_t st = S(stream);
+  s->fresh = false;
   return s->kb == 32 ? epoch_apply_t<u32>(s, es, e, st) : epoch_apply_t<u64>(s, es, e, st);
 }
 
@@ -2065,6 +2070,7 @@ int flix_drain(flix_store* s, const flix_batch* h_batches, const flix_batch* d_b
   if (!h_batches || !d_batches) return FLIX_EINVAL;
   int rc = drain_validate(s, h_batches, nbatch);
   if (rc) return rc;
+  s->fresh = false;
   return drain_launch(s, reinterpret_cast<const DrainBatch*>(d_batches), nbatch,
                       reinterpret_cast<unsigned long long*>(d_timestamps), S(stream));
 }
@@ -2077,6 +2083,7 @@ int flix_drain_graph(flix_store* s, const flix_batch* h_batches, const flix_batc
   *graph_exec = nullptr;
   int rc = drain_validate(s, h_batches, nbatch);
   if (rc) return rc;
+  s->fresh = false;
   hipStream_t st = S(stream);
   // size the grid outside the capture (occupancy queries are not captured)
   if (s->drain_grid == 0) {

@@ -81,7 +81,8 @@ def test_refused_allocations(kb, n0, n1, dup, rest):
         for i in range(40):
             hook.refuse(lambda j: False)
             s = Store(key_bits=kb, capacity=64, max_batch=1 << 15)
-            s.bulk_load(to_dev(ka), to_dev(va))
+            if n0:
+                s.bulk_load(to_dev(ka), to_dev(va))
             out = torch.zeros(probe.size, dtype=s.dtype, device="cuda")
             st = torch.cuda.Stream()
             dprobe = to_dev(probe)
@@ -150,7 +151,8 @@ def test_loads_with_and_without_duplicates_in_turn(kb):
     from oracle.oracle import Oracle
     from paper_2604_16725_amd.flix import Store
     s = Store(key_bits=kb, capacity=64, max_batch=1 << 12)
-    for i, (n, dup) in enumerate([(60000, 4), (60000, 4), (60000, 1), (60000, 1), (60000, 2),
+    for i, (n, dup) in enumerate([(60000, 4), (60000, 4), (60000, 4), (60000, 4), (60000, 1),
+                                  (60000, 1), (60000, 2), (60000, 3), (60000, 2), (60000, 1),
                                   (9000, 3), (9000, 3), (0, 1), (60000, 4)]):
         k = np.tile(w.KeySpace(kb, 3 + i).build(max(n // dup, 1)), dup)[:n]
         v = w.values_for(k, 4, kb) ^ np.arange(k.size).astype(k.dtype) % 64
