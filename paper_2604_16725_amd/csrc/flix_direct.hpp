@@ -295,6 +295,7 @@ struct WaveRange {
   K hi;
   u32 b, next;   // bucket of the last node counted, and that node's link
   u32 cnt;       // keys counted
+  bool walk;     // follow chains, too (else stop at the first link of one)
   bool end, bad;
 };
 
@@ -308,6 +309,7 @@ __device__ __forceinline__ u32 wave_gather(const ReadArgs<K>& a, const OccLevels
   u32 c = 0, n = 0;   // n lanes are taken
   while (n < 64 && !r.end) {
     if (r.next != kNil) {
+      if (!r.walk) break;
       r.bad = r.bad || r.next >= a.pool;
       if (r.bad) break;
       const NodeHdr h = a.hdr[r.next];
@@ -461,11 +463,14 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
   }
 
   if constexpr (OP == kOpRange) {
-    // the range's keys node by node: [p, ub) of each, copied by the wave.  What is
-    // left of ranges that have passed as many nodes as there are of them is
-    // finished range by range, 64 nodes at a time: bound by the latency of one
-    // wave's loads (one range of 2^20 u32 results 9.5 ms, of 2^20 u64 14.0; node by
-    // node 18.8 and 18.4, link by link with the wave's other ranges 25 and 28).
+    // the range's keys node by node: [p, ub) of each, copied by the wave.  A range
+    // that has passed more buckets than there are ranges left goes on 64 buckets at
+    // a time, taken by the whole wave.  Chains are followed side by side, a lane
+    // each (one by one, 2^20 ranges of which a fifth ran through chains of 500 nodes
+    // took 3.8 ms, so 1.2); the last range left has its own followed 64 links at a
+    // time.  Long ranges are bound by the latency of one wave's loads: one of 2^20
+    // u32 results 9.5 ms, of 2^20 u64 14.0 (node by node 18.8 and 18.4, link by link
+    // with the wave's other ranges 25 and 28).
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       bool more = live[q] && !bad[q] && x[q] <= hi[q];
@@ -478,15 +483,19 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
       h.next = next[q];
       if (more && le[q] == valid[q] && ub < h.size)   // every key of the block is in the range
         ub = upper_bound_idx<K>(a.nkeys + (u64)node[q] * a.cap, ub, h.size, hi[q]);
+      u32 run = 0;   // buckets passed since the last link of a chain
       WaveRange<K> r;
       int rl = -1;   // lane of the range that the wave finishes
       u64 left;
       for (u32 step = 0; (left = wave_ballot(more)) != 0; ++step) {
         u32 c = 0;
         u64 src, dst;
-        if (step > (u32)__popcll(left)) {
-          if (rl < 0) {
-            rl = (int)ctz64(left);
+        if (rl < 0 && (step & 3u) == 2u) {   // (looked at now and then)
+          r.walk = (left & (left - 1)) == 0;
+          const u64 ready =
+              r.walk ? left : wave_ballot(more && h.next == kNil && run > (u32)__popcll(left));
+          if (ready) {
+            rl = (int)ctz64(ready);
             r.hi = wave_read(hi[q], rl);
             r.b = wave_read(b[q], rl);
             r.next = wave_read(h.next, rl);
@@ -494,6 +503,8 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
             r.end = false;
             r.bad = false;
           }
+        }
+        if (rl >= 0) {
           u32 nd = 0;
           const u32 got = wave_gather<K>(a, occ, r, &nd);
           const u32 incl = wave_scan(got);
@@ -503,16 +514,19 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
           src = (u64)nd * a.cap;
           dst = wave_read(ob, rl) + at;
           r.cnt += wave_read(incl, 63);
-          if (r.end) {
+          if (r.end || (r.next != kNil && !r.walk)) {
             if (lane == (u32)rl) {
               cnt = r.cnt;
+              b[q] = r.b;
+              h.next = r.next;
               bad[q] = r.bad;
-              more = false;
+              more = !r.end;
             }
             rl = -1;
           }
         } else {
           if (step > 0 && more) {
+            run = h.next == kNil ? run + 1 : 0u;
             NodeHdr g;
             const u32 nn = next_nonempty(a.hdr, occ, a.nb, a.pool, &b[q], h, &g);
             if (nn == kNil || nn == kBadLink || g.size > a.cap) {
@@ -536,7 +550,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
           cnt += got;
           if (more && ub < h.size) more = false;   // a key above hi ends the range
         }
-        wave_copy_runs<K>(a, src, dst, c);
+        if (wave_ballot(c != 0)) wave_copy_runs<K>(a, src, dst, c);   // (else only counted)
       }
       if (live[q]) a.counts[j[q]] = bad[q] ? 0u : cnt;
     }
