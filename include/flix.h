@@ -5,11 +5,12 @@
  * 2604.16725) keeps an ordered map entirely in GPU memory with no index
  * layer.  Keys live in buckets; bucket i holds the keys in
  * (maxBucket[i-1], maxBucket[i]] as a chain of fixed-capacity sorted nodes
- * (Section 3.2).  Every operation batch is sorted on the device; then each
- * bucket binary-searches the sorted batch for its own slice and applies it in
- * place (Sections 3.3 and 4.1): point lookup, successor, range, merge-insert
- * with node split (Section 4.3.2), compact-delete with node reclamation
- * (Section 4.4).
+ * (Section 3.2).  An update batch is sorted on the device; then each bucket
+ * takes its own slice of it and applies it in place (Sections 3.3 and 4.1):
+ * merge-insert with node split (Section 4.3.2), compact-delete with node
+ * reclamation (Section 4.4).  Point lookups, successors, predecessors and ranges
+ * go the same way in long batches; others are answered in input order by a search
+ * of the maxBucket directory (FLIX_READ_SORTED below).
  *
  * Conventions for every entry point
  *  - Keys and values have the same width: 32 or 64 bits (flix_config.key_bits).
@@ -79,13 +80,13 @@ typedef struct {
   uint32_t reserved;        /* must be 0 */
 } flix_config;
 
-/* Read-batch pipelines (same results).  SORTED, the default, answers all but
- * long batches (above 3 * 2^21 32-bit point reads, 2^24 others) in input order,
- * one lane per query, by a search of the maxBucket directory; those go through
- * Section 3.3 / 4.1: the whole batch is sorted on the device (onesweep), then
- * merge-path shares let every bucket resolve its slice.  GROUPS splits the batch by groups of consecutive
- * buckets in one pass and sorts each group's items in LDS inside the resolving
- * workgroup (no device-wide sort). */
+/* Read-batch pipelines (same results).  SORTED, the default, sorts long batches
+ * only (above 3 * 2^21 32-bit point reads, 2^24 others) and lets every bucket
+ * resolve its slice in merge-path shares (Sections 3.3 and 4.1); all others it
+ * answers in input order, one lane per query, by a search of the maxBucket
+ * directory.  GROUPS splits the batch by groups of consecutive buckets in one pass
+ * and sorts each group's items in LDS inside the resolving workgroup (no
+ * device-wide sort). */
 #define FLIX_READ_SORTED 0
 #define FLIX_READ_GROUPS 1
 
@@ -240,17 +241,19 @@ int flix_get_stats(flix_store* s, flix_stats* out, void* stream);
 int flix_copy_layout(flix_store* s, void* h_mkba, void* h_hdr, void* h_keys, void* h_vals,
                      uint32_t* h_free, uint64_t* h_free_top, void* stream);
 
-/* Stable device radix sort of (key, index) used by every batch call, exposed
- * for verification: d_keys_out = keys ascending, d_idx_out = input position of
+/* Stable device radix sort of (key, index) pairs, exposed for verification (long
+ * updates and bulk loads sort with the same kernels, long read batches with
+ * this very form): d_keys_out = keys ascending, d_idx_out = input position of
  * each output key (ties keep input order).  n <= max_batch.  Asynchronous. */
 int flix_sort_pairs(flix_store* s, const void* d_keys, uint64_t n, void* d_keys_out,
                     uint32_t* d_idx_out, void* stream);
 
 /* ---- Persistent fused drain (a queue of mixed batches in one launch) ----
- * One co-resident grid executes the batches in order with the same phases as
- * the per-batch calls (sort, bound search, apply) separated by grid barriers,
- * so a whole queue costs one launch (or one hipGraph replay).  Results are
- * identical to issuing the batches one by one with the calls above. */
+ * One co-resident grid executes the batches in order, so a whole queue costs one
+ * launch (or one hipGraph replay).  Read batches are answered in input order and
+ * run into one another except where one's buffers overlap another's; update
+ * batches have their phases (sort, slices, apply) separated by grid barriers.
+ * Results are identical to issuing the batches one by one with the calls above. */
 #define FLIX_OP_LOOKUP 0
 #define FLIX_OP_SUCCESSOR 1
 #define FLIX_OP_RANGE 2
@@ -305,10 +308,10 @@ int flix_drain_info(flix_store* s, uint32_t* grid_blocks, uint64_t* timestamp_hz
  * all-ones pattern deletes the key, any other value upserts it.
  *
  * Two slots let one epoch be prepared while the previous one is applied:
- * flix_epoch_prepare sorts the epoch's three lists into the slot and folds
- * the updates (it reads only the epoch's inputs, never the store), and
- * flix_epoch_apply runs the bucket kernels of the prepared slot: lookups,
- * ranges (as flix_lookup / flix_range), then the folded deletes and upserts.
+ * flix_epoch_prepare copies the epoch's read lists into the slot (sorted where
+ * they are long, as in flix_lookup / flix_range), sorts its updates and folds
+ * them (it reads only the epoch's inputs, never the store), and flix_epoch_apply
+ * runs the prepared slot: lookups, ranges, then the folded deletes and upserts.
  * The caller orders the two streams with events: a slot's apply after its
  * prepare, a slot's next prepare after its previous apply, and all applies
  * in epoch order on one stream.  apply must get the same descriptor as the
@@ -354,8 +357,8 @@ const char* flix_last_error(void);
  * "sort_pass" (one onesweep pass or tile split), "sort_local" (the per-run sort
  * of batches of up to 2^22 keys, or the sort by counting of short updates),
  * "read_apply" (lookup/successor/range kernel), "read_cuts" (merge-path cuts of
- * the shares of read batches that are sorted), "slices" (update slice discovery and node budget),
- * "insert_apply", "delete_apply".  flix_set_timing(s, enable) times every
+ * the shares of read batches that are sorted), "slices" (update slice discovery
+ * and node budget), "insert_apply", "delete_apply".  flix_set_timing(s, enable) times every
  * family (enable != 0) or none; flix_set_timing_only(s, family) times only
  * the named family, leaving the other launches uninstrumented (FLIX_EINVAL
  * for an unknown name).  Both reset the sums.  Host-side and synchronous with

@@ -592,13 +592,15 @@ int read_batch_groups(flix_store* s, int op, const K* keys, u64 n, void* out_k, 
 }
 
 // Read batches up to this length are answered in input order.  Sorting a batch
-// first pays for long batches of 32-bit point reads (four passes; eight for
-// 64-bit keys), spread over a store that does not fit the caches; the others were
-// faster unsorted at every length measured, up to 12.3 M.  2^26 u32
-// keys, direct against sorted, us: lookups of 2^20 82, 107; 2^22 291, 451; 2^23
-// 572, 525; 12.3 M 845, 707; successors of 2^22 383, 524; 2^23 750, 634.  2^25
-// u64 keys, lookups of 2^23 590, 824; 12.3 M 860, 1246.  Ranges of 16 keys, 2^22
-// 778, 3520.  2^22 Zipf lookups 219, 1010; on 2^20 keys 143, 501.
+// first pays for long batches of 32-bit point reads (four passes; eight for 64-bit
+// keys) spread over a store that does not fit the caches: 2^26 u32 keys, direct
+// against sorted, us: lookups of 2^20 82, 107; 2^22 291, 451; 3 * 2^21 456, 451;
+// 2^23 572, 525; 12.3 M 845, 707; successors of 3 * 2^21 566, 528.  The rule looks
+// at width and length only: at 3 * 2^21 skewed lookups take 310, 600 and lookups
+// on 2^20 keys 225, 605, so above the limit such batches get the slower form.
+// Nothing else was faster sorted at any length measured: at 2^24, where the limit
+// ends the measured range, u64 lookups on 2^25 keys take 1190, 1654 (on 2^20 keys
+// 755, 2528) and ranges of four keys 2413, 3509 (u32 on 2^26 keys 1956, 2674).
 template <typename K>
 constexpr u64 direct_max(int op) {
   return sizeof(K) == 8 || op == kOpRange ? 1ull << 24 : 3ull << 21;

@@ -20,8 +20,8 @@
 // between the ends of its bucket (bisecting by the last keys of the blocks read
 // one more: lookups of 2^20 95 us, 108 on 2^25 u64 keys, now 83, and with 256
 // slots per node, now 74).  Against the sorted form before: lookups of 2^20 keys
-// 109 -> 82 us, Zipf 351 -> 60, 256 lookups 22 -> 10 (one launch), 2^20 ranges
-// of 16 keys each 918 -> 223 us, 2^16 of 256 keys 236 -> 107.
+// 109 -> 82 us, Zipf 300 to 350 -> 60, 256 lookups 22 -> 8 (one launch), 2^20 ranges
+// of 16 keys each 918 -> 218 us, 2^16 of 256 keys 236 -> 107.
 #pragma once
 
 #include "flix_device.hpp"

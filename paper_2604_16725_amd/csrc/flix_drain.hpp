@@ -3,16 +3,18 @@
 // Read batches are answered in input order by the searches of flix_direct.hpp
 // and run into one another: the grid meets at a barrier before a read batch
 // only where its buffers overlap those of a batch since the last barrier.
-// Update batches run the phases of the per-batch launches (histogram, onesweep
-// passes, slices + update kernel) with a grid barrier between them instead of
-// a kernel boundary.  The queue lives in device memory, so one launch (or one
-// hipGraph replay) drains it, and the batches can change between replays.
+// Update batches run in phases with a grid barrier between them instead of a
+// kernel boundary: short ones sort by counting, slices, update kernel; longer ones
+// histogram, onesweep passes, slices, update kernel.  The queue lives in device
+// memory, so one launch (or one hipGraph replay) drains it, and the batches can
+// change between replays.
 //
 // What bounds it: a barrier of the grid costs 11 to 20 us (the release of each
 // workgroup writes its XCD's L2 back).  While every batch was sorted, with
 // P + 3 barriers, 40 batches of 2^8 to 2^20 operations on 2^26 keys (4.9 M
-// reads, eight updates of 0.5 k to 49 k keys) took 8.7 ms; they take 2.26 ms,
-// about 1.4 of it in the eight updates.
+// reads, eight updates of 0.5 k to 49 k keys) took 8.7 ms; they take 1.5 ms.
+// Eight updates of 12,288 u32 keys take 0.78 ms, of 12,289 1.63 (u64 0.86, 2.49):
+// the limit of the short form is that of the calls, not where a drain would have it.
 //
 // Ordering and memory: a grid barrier is arrive (agent-scope release +
 // atomic) / wait (generation word) / agent-scope acquire.  Tiles of a pass are

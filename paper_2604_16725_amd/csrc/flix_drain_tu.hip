@@ -26,10 +26,11 @@ hipError_t drain_t(const DrainLaunch& d, hipStream_t st) {
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
       return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
-    // At most two workgroups per CU: every batch pays several grid barriers,
-    // whose cost grows with the arrivals; measured on the mixed-batch stream,
-    // two per CU beat three (540 vs 475 Mops/s) and one (537, slower on large
-    // batches).
+    // At most two workgroups per CU: updates pay several grid barriers, whose
+    // cost grows with the arrivals, reads gain from more waves.  A queue of 40
+    // mixed batches (flix_drain.hpp) takes 1.47 ms with one, 1.50 with two, 1.67
+    // with three; two were best on the longer mixed-batch stream while reads were
+    // sorted and paid barriers, too (540 Mops/s; one 537, three 475).
     *d.grid = std::min(per_cu, 2) * cus;
     *d.shm = shm;
   }
