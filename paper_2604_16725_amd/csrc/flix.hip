@@ -1370,26 +1370,33 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
     const u32 want = nodes <= 0xFFFFFF00ull ? pool_for(nodes) : 0;
     const u64 nr = (n + 15) / 16 * 16;               // whole 64-byte lines
     const bool room = nodes <= want && ((u64)want - nodes) * s->cap >= 2 * nr;
-    if (room && dir_alloc(s, (u32)nodes, &dir) == FLIX_OK) {
+    auto in_pool = [&]() {
+      if (!room || dir_alloc(s, (u32)nodes, &dir) != FLIX_OK) return;
+      if (s->fresh) {
+        s->nb = 0;
+        dir_take(s, &dir);   // (frees what the pool may then reuse)
+      }
       if (want == s->pool) {
         s->nb = 0;   // the old contents go
         where = kStore;
-      } else if (s->dup_loads >= 2) {
-        // temporary buffers
       } else if (!s->fresh && pool_alloc(s, want, &stage) == FLIX_OK) {
         where = kStage;
-      } else if ((rc = pool_instead(s, want)) == FLIX_OK) {
+      } else if (pool_instead(s, want) == FLIX_OK) {
         where = kStore;
-      } else if (!s->pool) {
-        return leave(rc);
+      } else {
+        dir_free(&dir);
       }
-      if (where == kTemp) dir_free(&dir);
+    };
+    const bool buffers_first = s->dup_loads >= 2 && want != s->pool;
+    if (!buffers_first) in_pool();
+    if (where == kTemp &&
+        ((rc = dev_alloc(&tk[0], n * sizeof(K))) || (rc = dev_alloc(&tk[1], n * sizeof(K))) ||
+         (rc = dev_alloc(&tv[0], n * sizeof(K))) || (rc = dev_alloc(&tv[1], n * sizeof(K))))) {
+      dev_free(&tk[0]); dev_free(&tk[1]); dev_free(&tv[0]); dev_free(&tv[1]);
+      if (buffers_first) in_pool();
+      if (where == kTemp) return leave(rc);
     }
-    if (where == kTemp) {
-      if ((rc = dev_alloc(&tk[0], n * sizeof(K))) || (rc = dev_alloc(&tk[1], n * sizeof(K))) ||
-          (rc = dev_alloc(&tv[0], n * sizeof(K))) || (rc = dev_alloc(&tv[1], n * sizeof(K))))
-        return leave(rc);
-    } else {
+    if (where != kTemp) {
       tk[0] = (K*)(where == kStore ? s->nkeys : stage.nkeys) + nodes * s->cap;
       tv[0] = (K*)(where == kStore ? s->nvals : stage.nvals) + nodes * s->cap;
       tk[1] = tk[0] + nr;
@@ -1434,22 +1441,21 @@ int bulk_load_body(flix_store* s, const K* keys, const K* vals, u64 n, hipStream
   if (nbk > 0xFFFFFF00ull) return leave(FLIX_EINVAL);
   const u32 pool = pool_for(nbk);
   if (nbk > pool) return leave(FLIX_ENOMEM);
-  if (where == kTemp && (rc = dir_alloc(s, (u32)nbk, &dir))) return leave(rc);
   // the pool that the layout is built in; where the pairs lie stays until it is
+  PoolMem m;
   if (stage.nodes == pool) {
-    std::swap(old, stage);
-    pool_swap(s, &old);
-  } else if (pool != s->pool) {
-    PoolMem m;
-    if (pool_alloc(s, pool, &m) == FLIX_OK) {
-      pool_swap(s, &m);
-      old = m;
-    } else if (stage.nodes) {   // duplicates made the pool smaller: the larger one stays
-      std::swap(old, stage);
-      pool_swap(s, &old);
-    } else if (where == kTemp && (rc = pool_instead(s, pool))) {
-      return leave(rc);
-    }
+    std::swap(m, stage);
+  } else if (pool != s->pool && pool_alloc(s, pool, &m) != FLIX_OK) {
+    if (stage.nodes) std::swap(m, stage);   // duplicates made the pool smaller: the larger stays
+    else if (where == kTemp && (rc = pool_instead(s, pool))) return leave(rc);
+  }
+  if (where == kTemp && (rc = dir_alloc(s, (u32)nbk, &dir))) {
+    pool_free(&m);
+    return leave(rc);
+  }
+  if (m.nodes) {
+    pool_swap(s, &m);
+    old = m;
   }
   dir_take(s, &dir);
   s->fresh = s->fresh && n == 0;

@@ -59,12 +59,14 @@ def _refused(fn):
     return False
 
 
-# the second load's size: larger (sort scratch, directory and pool grow), smaller
-# (the pool shrinks), with duplicates (the pool changes its size twice)
-@pytest.mark.parametrize("kb,n0,n1,dup", [(32, 20000, 150000, 1), (64, 90000, 3000, 1),
-                                          (32, 50000, 120000, 5), (64, 0, 40000, 1)])
+# the load that runs out: larger than what is stored (sort scratch, directory and
+# pool grow), smaller (the pool shrinks), with duplicates (the pool changes its size
+# twice), into a new store, after loads with duplicates (temporary buffers first)
+@pytest.mark.parametrize("kb,n0,n1,dup,loads", [
+    (32, 20000, 150000, 1, 1), (64, 90000, 3000, 1, 1), (32, 50000, 120000, 5, 1),
+    (64, 0, 40000, 1, 0), (64, 20000, 90000, 3, 3), (32, 60000, 100000, 2, 3)])
 @pytest.mark.parametrize("rest", [False, True])
-def test_refused_allocations(kb, n0, n1, dup, rest):
+def test_refused_allocations(kb, n0, n1, dup, loads, rest):
     import torch
     from oracle.oracle import Oracle
     from paper_2604_16725_amd.flix import DrainGraph, Store
@@ -81,8 +83,9 @@ def test_refused_allocations(kb, n0, n1, dup, rest):
         for i in range(40):
             hook.refuse(lambda j: False)
             s = Store(key_bits=kb, capacity=64, max_batch=1 << 15)
-            if n0:
-                s.bulk_load(to_dev(ka), to_dev(va))
+            for _ in range(loads):
+                twice = 2 if loads > 1 else 1
+                s.bulk_load(to_dev(np.tile(ka, twice)), to_dev(np.tile(va, twice)))
             out = torch.zeros(probe.size, dtype=s.dtype, device="cuda")
             st = torch.cuda.Stream()
             dprobe = to_dev(probe)
@@ -91,7 +94,7 @@ def test_refused_allocations(kb, n0, n1, dup, rest):
             failed = _refused(lambda: s.bulk_load(to_dev(kn), to_dev(vn)))
             asked = hook.count
             hook.refuse(lambda j: False)
-            log(f"kb={kb} {n0}->{n1} dup={dup} refuse {'from ' if rest else ''}{i}: failed={failed}")
+            log(f"kb={kb} {n0}->{n1} dup={dup} after {loads} refuse {'from ' if rest else ''}{i}: failed={failed}")
             if not failed:
                 outcomes.add("loaded")
                 assert_same_contents(s, new, kb)
