@@ -282,10 +282,11 @@ __device__ __forceinline__ u64 wave_read(u64 v, int l) {
 // Queries per wave (q or fewer) of a batch of m ranges on `waves` resident waves.
 // A range's results are copied by its wave (16 ranges of 2^18 results in one wave
 // took four times as long as in a wave each); but idle lanes cost, too, so a wave
-// takes fewer only while the batch then needs at most half the waves (20,000
-// ranges of 16 keys on 8192: 20 us with 4 per wave, 28 with 2).
+// takes fewer only while the batch then needs at most an eighth of the waves (ten
+// calls on 8192 waves, u32: 4096 ranges of up to 16 keys 103 us with four or two per
+// wave, 112 with one; 1000 of up to 64 keys 109 with four, 102 with one).
 __host__ __device__ inline u32 range_queries_per_wave(u32 q, u32 m, u32 waves) {
-  while (q > 1 && (u64)(q / 2) * waves >= 2ull * m) q >>= 1;
+  while (q > 1 && (u64)(q / 2) * waves >= 8ull * m) q >>= 1;
   return q;
 }
 
@@ -295,7 +296,8 @@ struct WaveRange {
   K hi;
   u32 b, next;   // bucket of the last node counted, and that node's link
   u32 cnt;       // keys counted
-  bool walk;     // follow chains, too (else stop at the first link of one)
+  bool walk;     // follow chains, too (else the lane does)
+  bool off;      // the lane goes on alone: at a chain, or at a stretch of empty buckets
   bool end, bad;
 };
 
@@ -303,13 +305,13 @@ struct WaveRange {
 // lanes that are left): heads of the buckets that follow, a lane each, as far as
 // they lie within the range, and links of a chain.
 template <typename K>
-__device__ __forceinline__ u32 wave_gather(const ReadArgs<K>& a, const OccLevels& occ,
-                                           WaveRange<K>& r, u32* node) {
+__device__ __forceinline__ u32 wave_gather(const ReadArgs<K>& a, WaveRange<K>& r, u32* node) {
   const u32 lane = threadIdx.x & 63u;
   u32 c = 0, n = 0;   // n lanes are taken
-  while (n < 64 && !r.end) {
+  while (n < 64 && !r.end && !r.off) {
     if (r.next != kNil) {
-      if (!r.walk) break;
+      r.off = !r.walk;
+      if (r.off) break;
       r.bad = r.bad || r.next >= a.pool;
       if (r.bad) break;
       const NodeHdr h = a.hdr[r.next];
@@ -352,11 +354,7 @@ __device__ __forceinline__ u32 wave_gather(const ReadArgs<K>& a, const OccLevels
       }
       if (nc < ns) r.next = wave_read(h.next, (int)nc);
       r.b += last + 1 - n;
-      if (!r.end && nc >= ns && !wave_ballot(mine && c != 0)) {   // a stretch of empty buckets
-        r.b = wave_read(occ_next(occ, a.nb, r.b), 0) - 1;
-        r.end = r.b + 1 >= a.nb;
-        if (n == 0) { c = 0; continue; }   // (the lanes hold nothing)
-      }
+      r.off = !r.end && nc >= ns && !wave_ballot(mine && c != 0);
       n = last + 1;
     }
   }
@@ -490,7 +488,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
       for (u32 step = 0; (left = wave_ballot(more)) != 0; ++step) {
         u32 c = 0;
         u64 src, dst;
-        if (rl < 0 && (step & 3u) == 2u) {   // (looked at now and then)
+        if (__builtin_expect(rl < 0 && (step & 3u) == 2u, 0)) {   // (looked at now and then)
           r.walk = (left & (left - 1)) == 0;
           const u64 ready =
               r.walk ? left : wave_ballot(more && h.next == kNil && run > (u32)__popcll(left));
@@ -500,13 +498,14 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
             r.b = wave_read(b[q], rl);
             r.next = wave_read(h.next, rl);
             r.cnt = wave_read(cnt, rl);
+            r.off = false;
             r.end = false;
             r.bad = false;
           }
         }
-        if (rl >= 0) {
+        if (__builtin_expect(rl >= 0, 0)) {
           u32 nd = 0;
-          const u32 got = wave_gather<K>(a, occ, r, &nd);
+          const u32 got = wave_gather<K>(a, r, &nd);
           const u32 incl = wave_scan(got);
           const u32 at = r.cnt + incl - got;
           const u32 room = at < a.maxpq ? a.maxpq - at : 0u;
@@ -514,7 +513,7 @@ __device__ __forceinline__ void direct_read(const ReadArgs<K>& a, const DirTree<
           src = (u64)nd * a.cap;
           dst = wave_read(ob, rl) + at;
           r.cnt += wave_read(incl, 63);
-          if (r.end || (r.next != kNil && !r.walk)) {
+          if (r.end || r.off) {
             if (lane == (u32)rl) {
               cnt = r.cnt;
               b[q] = r.b;
