@@ -223,8 +223,11 @@ __device__ __forceinline__ void stamp_stored(unsigned long long* at) {
   if ((threadIdx.x & 63u) == 0) atomicMax(at, (unsigned long long)wall_clock64());
 }
 
-// answers_over_keys of a read batch with these spans.
-__device__ __forceinline__ bool spans_over_keys(const BatchSpans& s, bool range) {
+// answers_over_keys of a batch (false for an update).
+template <typename K>
+__device__ __forceinline__ bool batch_over_keys(const DrainBatch& d, u32 max_batch) {
+  const BatchSpans s = batch_spans<K>(d, max_batch);
+  const bool range = d.op == kOpRange;
   bool c = false;
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -315,7 +318,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   u32 nz = 0;     // update batches processed so far: selects the histogram slot
   u32 rot = 0;    // wave that takes the next read unit
   u32 pend = 0;   // first batch since the last barrier
+  u64 over = 0;   // of 64 batches: which answer over keys still to be read
   for (u32 bi = 0; bi < a.nbatch; ++bi) {
+    if ((bi & 63u) == 0) {
+      // (a lane each: tested batch by batch, 40 mixed batches of up to 3700 u32 keys
+      // took 628 us, so 601)
+      const u32 l = bi + (threadIdx.x & 63u);
+      over = wave_ballot(l < a.nbatch && batch_over_keys<K>(a.batches[l], a.max_batch));
+    }
     const DrainBatch d = a.batches[bi];   // uniform
     const u32 n = d.n;
     if (n > a.max_batch || d.op > kOpLast) {   // rewritten descriptor out of range
@@ -332,17 +342,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // where it reads what a batch since the last barrier writes, or writes
     // what one reads or writes.  One lane compares with each of those batches
     // (at most 64).
-    bool copied = false;   // answers over keys still to be read
     {
       const u32 npend = bi - pend;
-      const BatchSpans own = batch_spans<K>(d, a.max_batch);
-      copied = !is_update && spans_over_keys(own, d.op == kOpRange);
       bool wait = npend >= 64u;
       if (!wait && npend > 0) {
         const u32 lane = threadIdx.x & 63u;
         bool c = false;
         if (lane < npend)
-          c = spans_conflict(batch_spans<K>(a.batches[pend + lane], a.max_batch), own);
+          c = spans_conflict(batch_spans<K>(a.batches[pend + lane], a.max_batch),
+                             batch_spans<K>(d, a.max_batch));
         wait = wave_ballot(c) != 0;
       }
       if (wait) {
@@ -351,6 +359,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     if (!is_update) {
+      const bool copied = (over >> (bi & 63u)) & 1u;
       if (copied) {   // to the sort's scratch, which no batch since the last barrier uses
         for (u32 i = blk * 256 + threadIdx.x; i < n; i += G * 256) a.bk[0][i] = ((const K*)d.keys)[i];
         if (grid_sync(dc, G)) return;

@@ -102,3 +102,26 @@ def test_ranges_over_their_bounds(kb, n, maxpq, how):
             assert np.array_equal(a[live], x.reshape(n, maxpq)[live])
     assert s.status() == 0
     s.close()
+
+
+@pytest.mark.parametrize("kb", [32, 64])
+def test_overlap_anywhere_in_a_long_queue(kb):
+    import torch
+    s, o, k, rng = _store(kb, 7)
+    dt = torch.int32 if kb == 32 else torch.int64
+    n = 3001
+    queue, want = [], []
+    for i in range(131):
+        q = _queries(rng, k, n, kb)
+        buf = torch.zeros(2 * n, dtype=dt, device="cuda")
+        keys = buf[:n]
+        keys.copy_(to_dev(q))
+        off = 64 if i in (0, 5, 63, 64, 66, 127, 128, 130) else n
+        queue.append(dict(op="lookup", keys=keys, out_v=buf[off: off + n]))
+        want.append(o.lookup(q))
+    log(f"drain of {len(queue)} lookups, kb={kb}")
+    s.drain(queue)
+    for i, (b, x) in enumerate(zip(queue, want)):
+        assert np.array_equal(to_host(b["out_v"], kb), x), f"batch {i}"
+    assert s.status() == 0
+    s.close()
